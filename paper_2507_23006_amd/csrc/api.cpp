@@ -211,12 +211,13 @@ size_t bin_layout(int64_t n_slots, int64_t cap, void* base, BinWs* w) {
 
 }  // namespace
 
-// segment area: work_off [T + 1] | state_off [T + 1] | stop_seg [T][256] |
-// states [capacity][kSegFields][256]
+// segment area: work_off [T + 1] | state_off [T + 1] | n_long [1] |
+// stop_seg [T][256] | states [capacity][kSegFields][256]
 size_t seg_fixed_bytes(int64_t n_tiles) {
     Carver c(nullptr);
     c.take<uint32_t>((size_t)n_tiles + 1);
     c.take<uint32_t>((size_t)n_tiles + 1);
+    c.take<uint32_t>(1);
     c.take<int32_t>((size_t)n_tiles * 256);
     return c.off;
 }
@@ -225,13 +226,14 @@ constexpr size_t kSegStateBytes = (size_t)kSegFields * 256 * sizeof(float);
 
 // a plan over `base` (NULL or too small: no segments)
 void seg_layout(void* base, size_t bytes, int64_t n_tiles, SegPlan* plan, uint32_t* capacity) {
-    *plan = SegPlan{nullptr, nullptr, nullptr, (uint32_t)n_tiles, nullptr, 0u};
+    *plan = SegPlan{nullptr, nullptr, nullptr, (uint32_t)n_tiles, nullptr, 0u, nullptr};
     *capacity = 0;
     const size_t fixed = seg_fixed_bytes(n_tiles);
     if (!base || bytes < fixed) return;
     Carver c(base);
     plan->work_off = c.take<uint32_t>((size_t)n_tiles + 1);
     plan->state_off = c.take<uint32_t>((size_t)n_tiles + 1);
+    plan->n_long = c.take<uint32_t>(1);
     plan->stop_seg = c.take<int32_t>((size_t)n_tiles * 256);
     plan->state = reinterpret_cast<float*>(static_cast<char*>(base) + fixed);
     *capacity = (uint32_t)std::min<size_t>((bytes - fixed) / kSegStateBytes, 1u << 24);

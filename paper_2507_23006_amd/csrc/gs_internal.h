@@ -257,6 +257,7 @@ struct SegPlan {
     uint32_t n_tiles;
     int32_t* stop_seg;
     uint32_t capacity;     // stored states the area holds
+    uint32_t* n_long;      // [1]: launch positions up to the last one with several segments
 };
 // plans the segments of every tile (segments disabled when they need more
 // than `capacity` stored states)

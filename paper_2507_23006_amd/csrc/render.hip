@@ -9,10 +9,10 @@
 // last composited entry, and the backward walks the list back to front,
 // recovering T_i = T_{i+1} / (1 - alpha_i).
 //
-// Backward per entry: the 12 gradient fields are summed over the wave by
-// halving lane exchanges (permlane swaps, then DPP row shifts) into an LDS
-// row; after each chunk the wave adds the rows to the per-slot 2D gradient
-// buffer with one float atomic per nonzero field.
+// Backward: the gradient fields of an entry are sums over a quadrant's pixels
+// and run on the FP32 matrix cores as a contraction over the pixels; after
+// each chunk the wave adds the sums to the per-slot 2D gradient buffer with
+// one float atomic per nonzero field.
 #include "gs_internal.h"
 
 namespace gs {
@@ -76,6 +76,12 @@ struct PixelCoords {
     int lx, ly;            // pixel within the tile
 };
 
+// a wave-uniform float in a scalar register (uniform float arithmetic is
+// done by the vector unit and would hold a vector register for the whole walk)
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
 __device__ __forceinline__ PixelCoords pixel_coords(const ViewTable& vt, int tile, int wave, int lane) {
     PixelCoords c;
     c.v = view_of_tile(vt, tile);
@@ -84,12 +90,12 @@ __device__ __forceinline__ PixelCoords pixel_coords(const ViewTable& vt, int til
     const int ty = lt / V.tiles_x, tx = lt - ty * V.tiles_x;
     const int qx0 = (wave & 1) * 8, qy0 = (wave >> 1) * 8;
     const int lx = qx0 + (lane & 7), ly = qy0 + (lane >> 3);
-    c.ox = (float)(tx * kTile);
-    c.oy = (float)(ty * kTile);
+    c.ox = uniform((float)(tx * kTile));
+    c.oy = uniform((float)(ty * kTile));
     c.fpx = (float)lx + 0.5f;
     c.fpy = (float)ly + 0.5f;
-    c.qcx = (float)qx0 + 4.0f;
-    c.qcy = (float)qy0 + 4.0f;
+    c.qcx = uniform((float)qx0 + 4.0f);
+    c.qcy = uniform((float)qy0 + 4.0f);
     const int px = tx * kTile + lx, py = ty * kTile + ly;
     c.inside = px < V.W && py < V.H;
     c.pix = V.pix_off + (int64_t)py * V.W + px;
@@ -114,9 +120,11 @@ __device__ __forceinline__ bool box_hits_quadrant(const float4 g, const float4 r
 // relaxed by 1e-5 and by 16 float32 ulps of the terms' magnitudes, which
 // covers the rounding of both this test and the kernels' own evaluation of
 // p, so an entry it rejects has alpha < 1/255 at every pixel of the quadrant.
-__device__ __forceinline__ float edge_max(float qa, float qb, float qc, float dx, float lo, float hi) {
-    // max over dy in [lo, hi] of qa dx^2 + qb dx dy + qc dy^2 (qc < 0)
-    const float dy = fminf(fmaxf(-qb * dx / (2.0f * qc), lo), hi);
+// max over dy in [lo, hi] of qa dx^2 + qb dx dy + qc dy^2 (qc < 0), m = -qb /
+// (2 qc): any dy gives a lower bound of the maximum, so the slope's rounding
+// (one ulp of v_rcp_f32) costs |qc| (dy ulp)^2 at most, far inside the margin
+__device__ __forceinline__ float edge_max(float qa, float qb, float qc, float m, float dx, float lo, float hi) {
+    const float dy = fminf(fmaxf(m * dx, lo), hi);
     return fmaf(qa, dx * dx, fmaf(qb, dx * dy, qc * (dy * dy)));
 }
 
@@ -125,8 +133,9 @@ __device__ __forceinline__ bool ellipse_hits_quadrant(const float4 g, const floa
     const float dx0 = (qcx - 3.5f) - g.x, dx1 = (qcx + 3.5f) - g.x;
     const float dy0 = (qcy - 3.5f) - g.y, dy1 = (qcy + 3.5f) - g.y;
     if (dx0 <= 0.0f && dx1 >= 0.0f && dy0 <= 0.0f && dy1 >= 0.0f) return true;
-    float m = fmaxf(edge_max(qa, qb, qc, dx0, dy0, dy1), edge_max(qa, qb, qc, dx1, dy0, dy1));
-    m = fmaxf(m, fmaxf(edge_max(qc, qb, qa, dy0, dx0, dx1), edge_max(qc, qb, qa, dy1, dx0, dx1)));
+    const float hb = -0.5f * qb, my = hb * __builtin_amdgcn_rcpf(qc), mx = hb * __builtin_amdgcn_rcpf(qa);
+    float m = fmaxf(edge_max(qa, qb, qc, my, dx0, dy0, dy1), edge_max(qa, qb, qc, my, dx1, dy0, dy1));
+    m = fmaxf(m, fmaxf(edge_max(qc, qb, qa, mx, dy0, dx0, dx1), edge_max(qc, qb, qa, mx, dy1, dx0, dx1)));
     const float DX = fmaxf(fabsf(dx0), fabsf(dx1)), DY = fmaxf(fabsf(dy0), fabsf(dy1));
     const float mag = fabsf(qa) * DX * DX + fabsf(qb) * DX * DY + fabsf(qc) * DY * DY;
     const float thr = -__log2f(255.0f * o) - 1e-5f - 16.0f * 5.9604645e-8f * mag;
@@ -184,6 +193,48 @@ __device__ __forceinline__ uint32_t last_le(const uint32_t* __restrict__ a, uint
         if (a[mid] <= v) lo = mid; else hi = mid;
     }
     return lo;
+}
+
+// The compositing kernels launch one-wave workgroups, one per (item,
+// quadrant): a workgroup of four quadrants holds its LDS and wave slots until
+// its slowest quadrant is done, which left half of the slots empty over the
+// long lists (their survivors differ from quadrant to quadrant).  Workgroups
+// go to the 8 XCDs in turn, so the four quadrants of an item lie 8 apart and
+// share an L2, and the items of a run of 8 are rotated from run to run: items
+// of a fixed residue are alike (the segments of two-segment lists alternate
+// between whole and remainder, which gave every other XCD 45 % more work).
+constexpr unsigned kXcds = 8;
+struct WaveItem {
+    uint32_t item;
+    int quad;
+};
+__device__ __forceinline__ WaveItem wave_item() {
+    const uint32_t x = blockIdx.x % kXcds, r = blockIdx.x / kXcds;
+    const uint32_t run = r / 4u;
+    return WaveItem{run * kXcds + (x + run) % kXcds, (int)(r % 4u)};
+}
+// workgroups for n items
+unsigned wave_grid(unsigned n) { return (n + kXcds - 1) / kXcds * kXcds * 4u; }
+
+// last_le by one wave, 64 probes at a time (wave-uniform arguments)
+__device__ __forceinline__ uint32_t last_le_wave(const uint32_t* __restrict__ a, uint32_t n, uint32_t v, int lane) {
+    uint32_t lo = 0, hi = n + 1;      // invariant: a[lo] <= v, answer in [lo, hi)
+    while (hi - lo > 1) {
+        const uint32_t step = (hi - lo + 63) / 64;
+        const uint32_t q = lo + (uint32_t)lane * step;
+        const bool le = lane == 0 || (q < hi && a[q] <= v);
+        const uint32_t L = 63u - (uint32_t)__clzll(__ballot(le));      // lanes 0 .. L hold: a is sorted
+        lo = lo + L * step;
+        hi = min(hi, lo + step);
+    }
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+}
+
+// work item b of a plan -> launch position: the lists with several segments
+// lie in the first n_long positions, each later position is one item
+__device__ __forceinline__ uint32_t item_position(const SegPlan& plan, uint32_t b, int lane) {
+    const uint32_t k = *plan.n_long, w = plan.work_off[k];
+    return b >= w ? k + (b - w) : last_le_wave(plan.work_off, k, b, lane);
 }
 
 // tile at launch position i (the order, when valid, else the position)
@@ -678,117 +729,117 @@ __global__ __launch_bounds__(256) void k_render_count(const float4* __restrict__
     if (pc.inside) reinterpret_cast<int2*>(n_eval)[pc.pix] = make_int2(count, count_last);
 }
 
-__device__ __forceinline__ float row_total_lane15(float x) {
-    // inclusive sums within each row of 16 lanes; lane 15 of the row ends with the row's total
-    x += __builtin_amdgcn_update_dpp(0.0f, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-    x += __builtin_amdgcn_update_dpp(0.0f, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-    x += __builtin_amdgcn_update_dpp(0.0f, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-    x += __builtin_amdgcn_update_dpp(0.0f, x, 0x128, 0xf, 0xf, false);   // row_ror:8 (lane 15 + lane 7)
-    // keeps the last add beside its DPP move (one v_add_f32_dpp) rather than
-    // sunk into the caller's lane-15 branch; emits no instruction
-    __asm__ volatile("" : "+v"(x));
-    return x;
-}
-
-// Sums 12 per-lane values over the wave by halving exchanges: the lane
-// halves swap six values (v_permlane32_swap) so that each half sums six
-// fields over lane pairs, the rows swap three (v_permlane16_swap) so that
-// each row of 16 sums three fields over 4 lanes, and DPP row shifts finish
-// the three row sums.  Lane 16 r + 15 ends with the totals of fields
-// 3r .. 3r + 2 in out[0..2] (30 VALU steps instead of 6 per field).
-__device__ __forceinline__ void wave_sum12(const float v[12], float out[3]) {
-    float a[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 6]), false,
-                                                        false);
-        // lanes 0-31: field j over (l, l + 32); lanes 32-63: field j + 6 over (l - 32, l)
-        a[j] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[j]), __float_as_uint(a[j + 3]), false,
-                                                        false);
-        // row r: field 3 r + j over the 4 lanes l, l +- 16, l +- 32 of its column
-        out[j] = row_total_lane15(__uint_as_float(p[0]) + __uint_as_float(p[1]));
-    }
-}
-
-// The same for fields 0 .. 9 (no AbsGS sums): five half swaps, three row
-// swaps (the last with zeros).  Lane 16 r + 15 ends with fields b, b + 2
-// and, for even r, b + 4 in out[0..2], where b = (r & 1) + 5 (r >> 1).
-__device__ __forceinline__ void wave_sum10(const float v[10], float out[3]) {
-    float a[5];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 5]), false,
-                                                        false);
-        // lanes 0-31: field j over (l, l + 32); lanes 32-63: field j + 5
-        a[j] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const uint32_t x = __float_as_uint(a[2 * j]), y = j < 2 ? __float_as_uint(a[2 * j + 1]) : 0u;
-        const auto p = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-        out[j] = row_total_lane15(__uint_as_float(p[0]) + __uint_as_float(p[1]));
-    }
-}
-
 constexpr int kG2 = GS_GRAD2D_FLOATS;   // per-slot 2D gradient fields
 
-// Per-field factors applied once per entry, after the wave sum: the lanes
-// sum dp (2 qa dx + qb dy), dp (qb dx + 2 qc dy), dp dx^2, dp dx dy, dp dy^2
-// and the absolute values of the first two (dp = dL/d of the exponent in
-// natural-log units), whose products with -ln2, -ln2, -1/2, -1, -1/2, ln2,
-// ln2 are the gradients of the mean, of the conic (A, B, C) and the AbsGS
-// sums.
-__device__ __forceinline__ float grad2d_field_scale(int f) {
-    return f < 2 ? -kLn2 : (f == 2 || f == 4) ? -0.5f : f == 3 ? -1.0f : f >= 10 ? kLn2 : 1.0f;
+// One wave's LDS of the backward: the chunk's surviving entries (their
+// records overwritten by their gradient sums once reduced), the per-pixel
+// values of a batch of kBatch entries, and the pixels' upstream gradients.
+constexpr int kBatch = 8;
+constexpr int kQW = 68;                 // an entry's row: dp of 64 pixels, padding, w of 64 pixels
+constexpr int kQRow = 132;              // the next entry starts 4 banks further
+template <bool kAbs>
+struct alignas(16) BwdStage {
+    float4 r[kChunk][3];       // mean, qa, qb | qc, opacity', depth, slot (bits) | r, g, b, position (1-based, bits)
+    float q[kBatch * kQRow];   // [entry of the batch][dp, w][pixel]
+    float4 up[65];             // upstream gradients by pixel, one further from y = 4 on (banks)
+    uint32_t slot[kAbs ? kChunk : 1];       // slots of the reduced rows; in word 10 of a row of 10 fields
+};
+
+// load_entry and stage_gathered for the backward; only the used half of the
+// fourth record is loaded
+struct GatherBwd {
+    float4 r0, r1, r2;
+    float2 r3;
+    uint32_t slot;
+};
+__device__ __forceinline__ GatherBwd load_entry_bwd(const float4* __restrict__ rec, uint32_t s) {
+    GatherBwd g;
+    g.slot = s;
+    if (s != kNoSlot) {
+        g.r0 = rec[4 * (size_t)s + 0];
+        g.r1 = rec[4 * (size_t)s + 1];
+        g.r2 = rec[4 * (size_t)s + 2];
+        g.r3 = *reinterpret_cast<const float2*>(rec + 4 * (size_t)s + 3);
+    } else {
+        g.r0 = g.r1 = g.r2 = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+        g.r3 = make_float2(0.0f, 0.0f);
+    }
+    return g;
+}
+template <class Stage>
+__device__ __forceinline__ int stage_gathered_bwd(const GatherBwd& e, int pos, const PixelCoords& pc, int lane,
+                                                  Stage& st) {
+    const float4 g = stage_geom(e.r0, e.r1, e.r2, pc.ox, pc.oy);
+    const bool hit = e.slot != kNoSlot &&
+                     box_hits_quadrant(g, make_float4(e.r3.x, e.r3.y, 0.0f, 0.0f), pc.qcx, pc.qcy) &&
+                     ellipse_hits_quadrant(g, e.r1, pc.qcx, pc.qcy);
+    const unsigned long long m = __ballot(hit);
+    if (hit) {
+        const int d = __popcll(m & lanes_below(lane));
+        st.r[d][0] = g;
+        st.r[d][1] = make_float4(e.r1.x, e.r1.y, e.r1.z, __uint_as_float(e.slot));
+        st.r[d][2] = make_float4(e.r2.x, e.r2.y, e.r2.z, __int_as_float(pos));
+    }
+    __builtin_amdgcn_wave_barrier();
+    return __popcll(m);
 }
 
 // Backward: each wave walks its quadrant's list back to front from the
 // deepest `last` of its pixels, in chunks staged and culled as in the
-// forward.  Per surviving entry the lanes' gradients are summed by
-// wave_sum12 into a per-wave LDS row; after each chunk the wave adds the rows to the
-// per-slot 2D gradient buffer with float atomics (zeros skipped).
-// The colour and depth behind an entry enter the gradient only through
-// their dot product with the pixel's upstream gradient, so the walk carries
-// that one scalar, S = g_rgb . R_rgb + g_depth R_depth, instead of R itself.
+// forward.  The colour and depth behind an entry enter the gradient only
+// through their dot product with the pixel's upstream gradient, so the walk
+// carries that one scalar, S = g_rgb . R_rgb + g_depth R_depth, instead of R.
+//
+// The 2D gradients of an entry are sums over the quadrant's 64 pixels of two
+// per-pixel values -- dp = dL/d(exponent) and w = alpha T -- times factors
+// that depend on the pixel and the entry's mean alone: dp times 1, dx, dy,
+// dx^2, dx dy, dy^2 and w times the pixel's upstream gradient.  The walk only
+// leaves dp and w in LDS; every 8 entries they are read back transposed, lane
+// (y, entry) taking the 8 pixels of row y, which it sums in registers with the
+// row's moments in X (the pixel centre relative to the quadrant's centre;
+// |X| <= 3.5 keeps the shift to dx near the size of what it yields) and with dy
+// constant.  Three exchanges over the 8 rows finish the sums.  That is about
+// 12 VALU instructions per entry; a sum of each field over the wave by lane
+// exchanges takes 30 and its products 14 more (0.60 ms at 6M Gaussians, 1080p,
+// bound by VALU issue).  The FP32 matrix instructions were measured too: they
+// share the vector units' time (an fma beside v_mfma_f32_16x16x4_f32 adds its
+// own) and fill a third of a product here, 27 ns per entry against 14.
+// The AbsGS sums (kAbs) come from the same rows: |dp| |2 qa dx + qb dy| and
+// |dp| |qb dx + 2 qc dy| per pixel.
+//
+// The sums overwrite staged records the walk has passed; after the chunk the
+// wave adds them to the per-slot rows, one float atomic per nonzero field.
+// (64, 5): 96 VGPRs without spills, five waves per SIMD; 19 workgroups share a
+// compute unit's LDS.
 template <bool kAbs>
-__global__ __launch_bounds__(256) void k_render_bwd(const float4* __restrict__ rec,
-                                                    const uint32_t* __restrict__ pair_vals,
-                                                    const uint2* __restrict__ ranges,
-                                                    const uint32_t* __restrict__ tile_order, ViewTable vt, OptK opt,
-                                                    const float* __restrict__ T_final,
-                                                    const int32_t* __restrict__ last_in,
-                                                    const float* __restrict__ d_rgb, const float* __restrict__ d_depth,
-                                                    const float* __restrict__ d_alpha, float* __restrict__ grad2d,
-                                                    SegPlan plan) {
-    __shared__ WaveStage stage[kWaves];
-    // one row of reduced fields per staged entry of half a chunk (10 without
-    // the AbsGS sums); the rows of a chunk's later half are flushed before
-    // its earlier half reuses them, so seven workgroups share a compute
-    // unit's LDS
-    constexpr int kRow = kAbs ? kG2 : 10;
-    constexpr int kRedRows = kChunk / 2;
-    __shared__ float s_red[kWaves][kRedRows][kRow];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+__global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__ rec,
+                                                   const uint32_t* __restrict__ pair_vals,
+                                                   const uint2* __restrict__ ranges,
+                                                   const uint32_t* __restrict__ tile_order, ViewTable vt, OptK opt,
+                                                   const float* __restrict__ T_final,
+                                                   const int32_t* __restrict__ last_in,
+                                                   const float* __restrict__ d_rgb, const float* __restrict__ d_depth,
+                                                   const float* __restrict__ d_alpha, float* __restrict__ grad2d,
+                                                   SegPlan plan) {
+    __shared__ BwdStage<kAbs> st;
+    const int lane = threadIdx.x;
+    const WaveItem wi = wave_item();
+    const uint32_t b = wi.item;
     int tile, seg = 0, nseg = 1;
     uint32_t st0 = 0;
     if (plan.work_off) {
         // work item -> (launch position, segment)
-        const uint32_t b = blockIdx.x;
         if (b >= plan.work_off[plan.n_tiles]) return;
-        const uint32_t i = last_le(plan.work_off, plan.n_tiles, b);
+        const uint32_t i = item_position(plan, b, lane);
         seg = (int)(b - plan.work_off[i]);
         nseg = (int)(plan.work_off[i + 1] - plan.work_off[i]);
         st0 = plan.state_off[i];
         tile = order_tile(tile_order, vt, i);
     } else {
-        tile = launch_tile(tile_order, vt);
+        if (b >= (uint32_t)vt.total_tiles) return;
+        tile = order_tile(tile_order, vt, b);
     }
-    const PixelCoords pc = pixel_coords(vt, tile, wave, lane);
-    WaveStage& st = stage[wave];
+    const PixelCoords pc = pixel_coords(vt, tile, wi.quad, lane);
     const uint2 rg = ranges[tile];
 
     float T = 1.0f, gC0 = 0.0f, gC1 = 0.0f, gC2 = 0.0f, gD = 0.0f, gA = 0.0f;
@@ -815,10 +866,10 @@ __global__ __launch_bounds__(256) void k_render_bwd(const float4* __restrict__ r
 
     // A segmented list: this workgroup walks segment `seg` (positions
     // (seg S, (seg + 1) S]); the state behind it comes from folding the later
-    // segments' transmittance and local colour, written by k_seg_prepass:
-    // R <- C_j + T_j R (so S <- g . C_j + T_j S), T <- T / T_j, Q <- Q T_j
-    // (segments starting at or after the pixel's last composited entry are
-    // the identity).
+    // segments' transmittance and local colour, written by the forward or
+    // k_seg_prepass: R <- C_j + T_j R (so S <- g . C_j + T_j S), T <- T / T_j,
+    // Q <- Q T_j (segments starting at or after the pixel's last composited
+    // entry are the identity).
     int lo = 0, hi = maxlast;
     if (nseg > 1) {
         const int px = pc.ly * kTile + pc.lx;
@@ -835,6 +886,103 @@ __global__ __launch_bounds__(256) void k_render_bwd(const float4* __restrict__ r
         lo = seg * kSegLen;
         hi = min((seg + 1) * kSegLen, maxlast);
     }
+    if (hi <= lo) return;
+
+    // Transposed: lane (y, j) takes row y of the quadrant of entry j of a
+    // batch.  y is spread over lane bits 5, 4 (lane swaps) and 0 (quad
+    // permutation); rows y and y + 4 of 8 entries, 16 consecutive lanes, then
+    // read from all 64 banks.
+    const int ty = (lane >> 4) | ((lane & 1) << 2), tj = (lane >> 1) & 7;
+    const float Yc = pc.qcy + ((float)ty - 3.5f);
+    st.up[lane + (lane >> 5)] = make_float4(gC0, gC1, gC2, gD);
+    __builtin_amdgcn_wave_barrier();
+    const float4* up = &st.up[8 * ty + (ty >> 2)];      // upstream gradients of the row's pixels
+
+    // Reduces the batch's nb entries: staged index of entry e in byte e of
+    // `ks`; their gradient sums go to the staged rows top - e, which the walk
+    // has passed already (top - e is not below the entry's own row).
+    constexpr int kFields = kAbs ? kG2 : 10;
+    auto reduce = [&](int nb, uint64_t ks, int top) {
+        __builtin_amdgcn_wave_barrier();
+        const int k = (int)((ks >> (8 * tj)) & 63u);
+        const float4 a = st.r[k][0], b = st.r[k][1];
+        const float* q = &st.q[tj * kQRow + 8 * ty];
+        const float4 p0 = *reinterpret_cast<const float4*>(q), p1 = *reinterpret_cast<const float4*>(q + 4);
+        const float mx = a.x - pc.qcx, dy = Yc - a.y;
+        float v[12];
+        {
+            // moments of dp over the row, from its values at +-X
+            const float s0 = p1.x + p0.w, s1 = p1.y + p0.z, s2 = p1.z + p0.y, s3 = p1.w + p0.x;
+            const float d0 = p1.x - p0.w, d1 = p1.y - p0.z, d2 = p1.z - p0.y, d3 = p1.w - p0.x;
+            const float m0 = (s0 + s1) + (s2 + s3);
+            const float m1 = fmaf(3.5f, d3, fmaf(2.5f, d2, fmaf(1.5f, d1, 0.5f * d0)));
+            const float m2 = fmaf(12.25f, s3, fmaf(6.25f, s2, fmaf(2.25f, s1, 0.25f * s0)));
+            const float sx = fmaf(-mx, m0, m1), sy = dy * m0;       // sums of dp dx, dp dy
+            v[0] = -kLn2 * fmaf(a.z + a.z, sx, a.w * sy);
+            v[1] = -kLn2 * fmaf(a.w, sx, (b.x + b.x) * sy);
+            v[2] = -0.5f * fmaf(-mx, m1 + sx, m2);                  // dp dx^2
+            v[3] = -dy * sx;
+            v[4] = -0.5f * dy * sy;
+            v[5] = m0 * __builtin_amdgcn_rcpf(b.y);                 // dp = dL/d opacity' opacity'
+        }
+        if (kAbs) {
+            const float qb = 0.5f * a.w, hx0 = qb * dy, hy0 = b.x * dy;
+            const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+            float ax = 0.0f, ay = 0.0f;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                const float dx = ((float)x - 3.5f) - mx;
+                ax = fmaf(fabsf(pv[x]), fabsf(fmaf(a.z, dx, hx0)), ax);
+                ay = fmaf(fabsf(pv[x]), fabsf(fmaf(qb, dx, hy0)), ay);
+            }
+            v[10] = (2.0f * kLn2) * ax;
+            v[11] = (2.0f * kLn2) * ay;
+        }
+        {
+            const float4 w0 = *reinterpret_cast<const float4*>(q + kQW);
+            const float4 w1 = *reinterpret_cast<const float4*>(q + kQW + 4);
+            const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+            v[6] = v[7] = v[8] = v[9] = 0.0f;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                const float4 u = up[x];
+                v[6] = fmaf(u.x, wv[x], v[6]);
+                v[7] = fmaf(u.y, wv[x], v[7]);
+                v[8] = fmaf(u.z, wv[x], v[8]);
+                v[9] = fmaf(u.w, wv[x], v[9]);
+            }
+        }
+        // sums over the rows: the lane halves swap half of the fields, the
+        // rows of 16 lanes half of what is left, lane pairs add up
+        float h[6], out[3];
+#pragma unroll
+        for (int i = 0; i < kFields / 2; ++i) {
+            const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + kFields / 2]),
+                                                            false, false);
+            h[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        }
+        if (!kAbs) h[5] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[2 * i]), __float_as_uint(h[2 * i + 1]),
+                                                            false, false);
+            const float x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+            out[i] = x + __builtin_amdgcn_update_dpp(0.0f, x, 0xB1, 0xf, 0xf, false);      // quad_perm: lane ^ 1
+        }
+        // lane row r = lane / 16 holds fields f, f + 2, f + 4 (f + 4 < its half's end)
+        const int r = lane >> 4, f = (r & 1) + (kFields / 2) * (r >> 1);
+        const uint32_t slot = __float_as_uint(b.w);
+        // every lane has read its rows before any lane overwrites one
+        __asm__ volatile("" ::"v"(out[0]), "v"(out[1]), "v"(out[2]), "v"(slot));
+        __builtin_amdgcn_wave_barrier();
+        if (tj < nb) {
+            float* row = reinterpret_cast<float*>(&st.r[0][0]) + 12 * (top - tj) + f;
+            row[(lane & 1) ? 2 : 0] = (lane & 1) ? out[1] : out[0];
+            if ((lane & 1) == 0 && (kAbs || !(r & 1))) row[4] = out[2];
+            if (kAbs ? lane < 16 : f == 0) (kAbs ? st.slot[top - tj] : reinterpret_cast<uint32_t*>(row)[10]) = slot;
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
 
     // chunk [b_end - 64, b_end) of positions, clipped at lo, walked from the
     // back; lane l of a chunk gathers position b_start + l
@@ -842,101 +990,90 @@ __global__ __launch_bounds__(256) void k_render_bwd(const float4* __restrict__ r
         const int b_start_ = max(lo, b_end_ - kChunk);
         return b_end_ > lo ? load_slot(pair_vals, rg.x + (uint32_t)(b_start_ + lane), rg.x + (uint32_t)b_end_) : kNoSlot;
     };
-    // adds the sums of staged entries [k0, k1) (one half of the staged
-    // chunk, rows k mod kRedRows) to grad2d
-    constexpr int kFields = kAbs ? kG2 : 10;
-    auto flush = [&](int k0, int k1) {
-        for (int i = lane; i < (k1 - k0) * kFields; i += 64) {
-            const int j = i / kFields, f = i - j * kFields, k = k0 + j;
-            const float sum = s_red[wave][k & (kRedRows - 1)][f];
-            if (sum != 0.0f)
-                atomicAdd(&grad2d[(size_t)(uint32_t)st.ps[k].y * kG2 + f], sum * grad2d_field_scale(f));
-        }
+    // adds the reduced rows [r0, r1) of the staged chunk to grad2d, four rows
+    // (16 lanes each) at a time
+    auto flush = [&](int r0, int r1) {
+        const int f = lane & 15;
+        if (f < kFields)
+            for (int r = r0 + (lane >> 4); r < r1; r += 4) {
+                const float* row = reinterpret_cast<const float*>(&st.r[r][0]);
+                const uint32_t slot = kAbs ? st.slot[r] : __float_as_uint(row[10]);
+                if (row[f] != 0.0f) atomicAdd(&grad2d[(size_t)slot * kG2 + f], row[f]);
+            }
         __builtin_amdgcn_wave_barrier();
     };
-    Gather cur = load_entry(rec, chunk_slot(hi));
+
+    // One entry at the lane's pixel, as far as it does not depend on the
+    // entries behind it.  An entry the pixel did not composite takes alpha =
+    // 0, which leaves T and S unchanged exactly.
+    struct Step {
+        float al, alp, r, kr, gc;
+        bool any;
+    };
+    const float K = gA * (T * Q);      // dL/dalpha_i holds g_alpha T_final / (1 - alpha_i)
+    auto step = [&](const float4& a, const float4& b, const float4& c) {
+        Step p;
+        const Eval e = eval_entry(a, b, pc.fpx, pc.fpy);
+        const bool con = __float_as_int(c.w) <= last && e.keep;      // c.w: 1-based position
+        p.any = __ballot(con) != 0;
+        p.al = con ? e.alpha : 0.0f;
+        p.alp = e.raw < kAlphaMax ? p.al : 0.0f;                     // no gradient through the clamp
+        p.r = __builtin_amdgcn_rcpf(1.0f - p.al);
+        p.kr = K * p.r;
+        p.gc = fmaf(gC0, c.x, fmaf(gC1, c.y, fmaf(gC2, c.z, gD * b.z)));   // g . (colour, depth)
+        return p;
+    };
+    GatherBwd cur = load_entry_bwd(rec, chunk_slot(hi));
     uint32_t s_next = chunk_slot(hi - kChunk);
-    int n_prev = 0;
+    int r0 = 0, r1 = 0;      // reduced rows of the staged chunk
     for (int b_end = hi; b_end > lo; b_end -= kChunk) {
         const int b_start = max(lo, b_end - kChunk);
         // Wait for this chunk's records here, then issue the previous
         // chunk's atomics: loads and atomics share one in-order counter, so
         // atomics issued before the wait would be waited for as well.
         __asm__ volatile("" ::"v"(cur.r0.x), "v"(cur.r1.x), "v"(cur.r2.x), "v"(cur.r3.x), "v"(s_next));
-        flush(0, min(n_prev, kRedRows));
-        const int n = stage_gathered(cur, b_start + lane + 1, pc, lane, st);
-        n_prev = n;
-        cur = load_entry(rec, s_next);
+        flush(r0, r1);
+        const int n = stage_gathered_bwd(cur, b_start + lane + 1, pc, lane, st);
+        r0 = r1 = n;
+        cur = load_entry_bwd(rec, s_next);
         s_next = chunk_slot(b_end - 2 * kChunk);
+        if (n == 0) continue;
+        int nb = 0;
+        uint64_t ks = 0;
+        // entry k - 1 is read from LDS during entry k's update
+        Step p = step(st.r[n - 1][0], st.r[n - 1][1], st.r[n - 1][2]);
+        const float4* rn = &st.r[n - 1][0];
+        float* q = st.q + lane;
         for (int k = n - 1; k >= 0; --k) {
-            const float4 a = st.g[k], b = st.b[k], c = st.c[k];
-            // whole-record reads at the entry's one LDS address (b.w and c.w
-            // are used only under the ballot below); emits no instruction
-            __asm__ volatile("" ::"v"(b.w), "v"(c.w));
-            const int pos = st.ps[k].x;       // 1-based
-            const Eval e = eval_entry(a, b, pc.fpx, pc.fpy);
-            const bool con = pos <= last && e.keep;
-            // an entry the pixel did not composite takes alpha = 0, which
-            // leaves S and Q unchanged exactly (x 1, + 0)
-            const float al = con ? e.alpha : 0.0f;
-            const float one_m = 1.0f - al;
-            const float Ti = T * __builtin_amdgcn_rcpf(one_m);
-            const float gc = fmaf(gC0, c.x, fmaf(gC1, c.y, fmaf(gC2, c.z, gD * b.z)));   // g . (colour, depth)
-            const float dal = Ti * fmaf(gA, Q, gc - S);
-            const float w = al * Ti;
-            float g[kG2];
-            g[6] = gC0 * w;
-            g[7] = gC1 * w;
-            g[8] = gC2 * w;
-            g[9] = gD * w;
-            const float dal_u = (con && e.raw < kAlphaMax) ? dal : 0.0f;
-            g[5] = dal_u * e.G;
-            const float dp = dal_u * al;               // dL/d power (natural-log units)
-            const float dpx = dp * e.dx, dpy = dp * e.dy;
-            g[0] = fmaf(c.w, dpx, a.w * dpy);         // dp (2 qa dx + qb dy)
-            g[1] = fmaf(a.w, dpx, b.w * dpy);         // dp (qb dx + 2 qc dy)
-            g[2] = dpx * e.dx;
-            g[3] = dpx * e.dy;
-            g[4] = dpy * e.dy;
-            if (kAbs) {
-                g[10] = fabsf(g[0]);
-                g[11] = fabsf(g[1]);
-            }
-            S = fmaf(S, one_m, gc * al);
-            Q *= one_m;
-            T = con ? Ti : T;
-            if (kAbs) {
-                // lane 16 r + 15 writes fields 3 r .. 3 r + 2 of the entry's row
-                float* row = &s_red[wave][k & (kRedRows - 1)][3 * (lane >> 4)];
-                if (__ballot(con)) {
-                    float tot[3];
-                    wave_sum12(g, tot);
-                    if ((lane & 15) == 15) {
-                        row[0] = tot[0];
-                        row[1] = tot[1];
-                        row[2] = tot[2];
-                    }
-                } else if ((lane & 15) == 15) {
-                    row[0] = row[1] = row[2] = 0.0f;
-                }
-            } else {
-                // lane 16 r + 15 writes its fields of the entry's row
-                const int r = lane >> 4;
-                float* row = &s_red[wave][k & (kRedRows - 1)][(r & 1) + 5 * (r >> 1)];
-                float tot[3] = {0.0f, 0.0f, 0.0f};
-                if (__ballot(con)) wave_sum10(g, tot);
-                if ((lane & 15) == 15) {
-                    row[0] = tot[0];
-                    row[2] = tot[1];
-                    if (!(r & 1)) row[4] = tot[2];
+            rn -= k > 0 ? 3 : 0;
+            const float4 a = rn[0], b = rn[1], c = rn[2];
+            const float Ti = T * p.r;
+            const float df = p.gc - S;
+            const float dp = fmaf(Ti, df, p.kr) * p.alp;       // dL/d power (natural-log units)
+            q[0] = dp;
+            q[kQW] = p.al * Ti;
+            S = fmaf(p.al, df, S);
+            T = Ti;
+            const bool any = p.any;
+            p = step(a, b, c);
+            if (any) {
+                ks |= (uint64_t)k << (8 * nb);
+                q += kQRow;
+                if (++nb == kBatch) {
+                    reduce(kBatch, ks, r0 - 1);
+                    r0 -= kBatch;
+                    q = st.q + lane;
+                    nb = 0;
+                    ks = 0;
                 }
             }
-            // the later half's rows go out before the earlier half reuses them
-            if (k == kRedRows) flush(kRedRows, n);
         }
-        __builtin_amdgcn_wave_barrier();
+        if (nb) {
+            reduce(nb, ks, r0 - 1);
+            r0 -= nb;
+        }
     }
-    flush(0, min(n_prev, kRedRows));
+    flush(r0, r1);
 }
 
 // exclusive scan of v over the 1024 threads of the workgroup; *total gets the sum
@@ -973,8 +1110,9 @@ constexpr int kPlanBatch = 8;
 __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ranges,
                                                    const uint32_t* __restrict__ tile_order, ViewTable vt,
                                                    uint32_t capacity, uint32_t* __restrict__ work_off,
-                                                   uint32_t* __restrict__ state_off) {
+                                                   uint32_t* __restrict__ state_off, uint32_t* __restrict__ n_long) {
     __shared__ uint32_t s_wave[16];
+    __shared__ uint32_t s_long;
     __shared__ uint16_t s_nseg[kPlanCache];
     const uint32_t n_tiles = (uint32_t)vt.total_tiles;
     // segment counts of the launch positions [ib, min(ib + kPlanBatch, end))
@@ -993,10 +1131,12 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
     };
     const uint32_t k = (n_tiles + 1023) / 1024;
     const uint32_t i0 = threadIdx.x * k, i1 = min(i0 + k, n_tiles);
+    if (threadIdx.x == 0) s_long = 0;
+    __syncthreads();
     // pass 1: the thread's segment total (cached counts below 2^16).  The
     // positions are read kPlanBatch at a time, all loads first, so a thread
     // waits for one round of gathers per batch instead of one per position
-    uint32_t mine = 0, big = 0;
+    uint32_t mine = 0, big = 0, end_long = 0;
     for (uint32_t ib = i0; ib < i1; ib += kPlanBatch) {
         uint32_t c[kPlanBatch];
         nseg_batch(ib, i1, c);
@@ -1005,10 +1145,12 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
             const uint32_t i = ib + u;
             if (i >= i1) break;
             mine += c[u];
+            if (c[u] > 1u) end_long = i + 1;
             if (i < kPlanCache) s_nseg[i] = (uint16_t)c[u];
             big |= c[u] > 0xFFFFu ? 1u : 0u;
         }
     }
+    if (end_long) atomicMax(&s_long, end_long);
     // the threads' prefix and the total (do the states fit?), and whether
     // any count was too large for the cache
     uint32_t total_seg = 0, total_big = 0;
@@ -1036,6 +1178,7 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
     if (threadIdx.x == 1023) {
         work_off[n_tiles] = on ? total_seg : n_tiles;
         state_off[n_tiles] = on ? total_need : 0u;
+        *n_long = on ? s_long : 0u;      // every position from here on holds one segment
     }
 }
 
@@ -1117,7 +1260,7 @@ hipError_t launch_render_fwd(const Projected& proj, const uint32_t* pair_vals, c
         hipLaunchKernelGGL(k_render_fwd_persistent, dim3(grid), dim3(256), 0, s, proj.rec, pair_vals, ranges,
                            proj.tile_order, vt, opt, rgb, depth, alpha, T_final, last, work);
     } else {
-        const SegPlan none{nullptr, nullptr, nullptr, (uint32_t)vt.total_tiles, nullptr, 0u};
+        const SegPlan none{nullptr, nullptr, nullptr, (uint32_t)vt.total_tiles, nullptr, 0u, nullptr};
         hipLaunchKernelGGL(k_render_fwd, dim3(vt.total_tiles), dim3(256), 0, s, proj.rec, pair_vals, ranges,
                            proj.tile_order, vt, opt, rgb, depth, alpha, T_final, last, plan ? *plan : none);
         if (plan && plan->capacity) {
@@ -1146,7 +1289,7 @@ hipError_t launch_render_count(const Projected& proj, const uint32_t* pair_vals,
 hipError_t launch_seg_plan(const Projected& proj, const uint2* ranges, const ViewTable& vt, uint32_t capacity,
                            const SegPlan& plan, hipStream_t s) {
     hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(1024), 0, s, ranges, proj.tile_order, vt, capacity, plan.work_off,
-                       plan.state_off);
+                       plan.state_off, plan.n_long);
     return hipGetLastError();
 }
 
@@ -1166,13 +1309,13 @@ hipError_t launch_render_bwd(const Projected& proj, const uint32_t* pair_vals, c
                              const float* d_rgb, const float* d_depth, const float* d_alpha, float* grad2d,
                              const SegPlan& plan, uint32_t capacity, bool abs_sums, hipStream_t s) {
     // with a plan, blocks beyond the planned work items exit at once
-    const unsigned blocks = (unsigned)vt.total_tiles + (plan.work_off ? capacity : 0u);
+    const unsigned blocks = wave_grid((unsigned)vt.total_tiles + (plan.work_off ? capacity : 0u));
     const hipEvent_t timed_ = timer_begin(GS_KERNEL_RENDER_BWD, s);
     if (abs_sums)
-        hipLaunchKernelGGL(k_render_bwd<true>, dim3(blocks), dim3(256), 0, s, proj.rec, pair_vals, ranges,
+        hipLaunchKernelGGL(k_render_bwd<true>, dim3(blocks), dim3(64), 0, s, proj.rec, pair_vals, ranges,
                            proj.tile_order, vt, opt, T_final, last, d_rgb, d_depth, d_alpha, grad2d, plan);
     else
-        hipLaunchKernelGGL(k_render_bwd<false>, dim3(blocks), dim3(256), 0, s, proj.rec, pair_vals, ranges,
+        hipLaunchKernelGGL(k_render_bwd<false>, dim3(blocks), dim3(64), 0, s, proj.rec, pair_vals, ranges,
                            proj.tile_order, vt, opt, T_final, last, d_rgb, d_depth, d_alpha, grad2d, plan);
     timer_end(timed_, s);
     return hipGetLastError();
