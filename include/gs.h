@@ -205,21 +205,21 @@ int gs_render_count(const gs_projected *proj, const uint32_t *pair_vals, const u
 /* Workspace of the backward: gs_render_bwd_workspace_size(n_slots) bytes of
  * per-slot 2D gradients, optionally followed (gs_render_bwd) or given
  * separately (gs_composite_bwd's seg_ws) by gs_seg_workspace_size(n_tiles,
- * n_pairs) bytes for the segmented walk: tile lists longer than 512
- * positions are then walked in 512-position segments by separate
- * workgroups, each starting from the transmittance and colour behind it
+ * n_pairs) bytes for the segmented walk: tile lists longer than a segment
+ * (512 positions, 128 for launches of at most 4096 tiles) are then walked in
+ * segments by separate workgroups, each starting from the transmittance and colour behind it
  * (folded from per-segment states a pre-pass computes), so the longest
  * lists no longer serialise the launch.  A smaller or absent segment area
  * walks every list whole; results agree to float rounding either way. */
 size_t gs_render_bwd_workspace_size(int64_t n_slots);
 size_t gs_seg_workspace_size(int64_t n_tiles, int64_t n_pairs);
 
-/* Compositing (Eq. 2) with the lists longer than 512 positions split into
- * 512-position segments walked by several workgroups, in the segment area
+/* Compositing (Eq. 2) with long lists split into segments (512 positions,
+ * 128 for launches of at most 4096 tiles) walked by several workgroups, in the segment area
  * seg_ws (gs_seg_workspace_size(n_tiles, n_pairs) bytes, 256-byte aligned;
  * a smaller area, or one too small for the states, walks every list whole
  * as gs_render_fwd does).  A long list's workgroup walks its first two
- * segments with the stop rule; for the pixels still compositing, one
+ * segments (1024 positions when no list is longer) with the stop rule; for the pixels still compositing, one
  * workgroup per later segment keeps the segment's state with T restarted
  * at 1; one thread per such pixel folds the segments (T only decreases, so
  * the pixel stops in segment j exactly when T T_seg_j < 1e-4) and the stop

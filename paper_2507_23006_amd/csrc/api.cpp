@@ -211,29 +211,37 @@ size_t bin_layout(int64_t n_slots, int64_t cap, void* base, BinWs* w) {
 
 }  // namespace
 
-// segment area: work_off [T + 1] | state_off [T + 1] | n_long [1] |
+// segment area: work_off [T + 1] | state_off [T + 1] | info [2] |
 // stop_seg [T][256] | states [capacity][kSegFields][256]
 size_t seg_fixed_bytes(int64_t n_tiles) {
     Carver c(nullptr);
     c.take<uint32_t>((size_t)n_tiles + 1);
     c.take<uint32_t>((size_t)n_tiles + 1);
-    c.take<uint32_t>(1);
+    c.take<uint32_t>(2);
     c.take<int32_t>((size_t)n_tiles * 256);
     return c.off;
 }
 
 constexpr size_t kSegStateBytes = (size_t)kSegFields * 256 * sizeof(float);
 
+// The backward's walk of a segment is a serial chain (0.3 us an entry with one
+// wave per SIMD), so a launch of few tiles takes short segments: 4096 Gaussians
+// at 160x120 (80 tiles, lists to 600) k_render_bwd 78 -> 34 us; 250k Gaussians
+// in three views (2720 tiles, lists to 4000) 103 -> 50 us and the forward
+// passes 138 -> 62 us.  From about 4096 tiles on the waves fill the device
+// either way, and a segment's set-up and 6 KB of states count instead.
+int32_t seg_len_of(int64_t n_tiles) { return n_tiles <= 4096 ? kSegLenSmall : kSegLen; }
+
 // a plan over `base` (NULL or too small: no segments)
-void seg_layout(void* base, size_t bytes, int64_t n_tiles, SegPlan* plan, uint32_t* capacity) {
-    *plan = SegPlan{nullptr, nullptr, nullptr, (uint32_t)n_tiles, nullptr, 0u, nullptr};
+void seg_layout(void* base, size_t bytes, int64_t n_tiles, int32_t seg_len, SegPlan* plan, uint32_t* capacity) {
+    *plan = SegPlan{nullptr, nullptr, nullptr, (uint32_t)n_tiles, nullptr, 0u, nullptr, (uint32_t)seg_len};
     *capacity = 0;
     const size_t fixed = seg_fixed_bytes(n_tiles);
     if (!base || bytes < fixed) return;
     Carver c(base);
     plan->work_off = c.take<uint32_t>((size_t)n_tiles + 1);
     plan->state_off = c.take<uint32_t>((size_t)n_tiles + 1);
-    plan->n_long = c.take<uint32_t>(1);
+    plan->info = c.take<uint32_t>(2);
     plan->stop_seg = c.take<int32_t>((size_t)n_tiles * 256);
     plan->state = reinterpret_cast<float*>(static_cast<char*>(base) + fixed);
     *capacity = (uint32_t)std::min<size_t>((bytes - fixed) / kSegStateBytes, 1u << 24);
@@ -517,7 +525,7 @@ const float* gs_render_bwd_grad2d(void* ws) { return static_cast<const float*>(w
 size_t gs_seg_workspace_size(int64_t n_tiles, int64_t n_pairs) {
     if (n_tiles < 1) n_tiles = 1;
     if (n_pairs < 0) n_pairs = 0;
-    return seg_fixed_bytes(n_tiles) + ((size_t)n_pairs / kSegLen + 1) * kSegStateBytes;
+    return seg_fixed_bytes(n_tiles) + ((size_t)n_pairs / seg_len_of(n_tiles) + 1) * kSegStateBytes;
 }
 
 int gs_render_fwd_seg(const gs_projected* proj, const uint32_t* pair_vals, const uint32_t* tile_ranges,
@@ -535,7 +543,7 @@ int gs_render_fwd_seg(const gs_projected* proj, const uint32_t* pair_vals, const
         hipStream_t s = (hipStream_t)stream;
         SegPlan plan;
         uint32_t cap;
-        seg_layout(seg_ws, seg_ws_bytes, vt.total_tiles, &plan, &cap);
+        seg_layout(seg_ws, seg_ws_bytes, vt.total_tiles, seg_len_of(vt.total_tiles), &plan, &cap);
         const Projected pr = to_proj(proj);
         const uint2* rg = reinterpret_cast<const uint2*>(tile_ranges);
         if (plan.work_off) GS_HIP(launch_seg_plan(pr, rg, vt, cap, plan, s));
@@ -570,7 +578,7 @@ int gs_render_bwd(const gs_gaussians* g, const gs_camera* cams, int32_t n_views,
         float* grad2d = static_cast<float*>(ws);
         SegPlan plan;
         uint32_t cap;
-        seg_layout(static_cast<char*>(ws) + g2_bytes, ws_bytes - g2_bytes, vt.total_tiles, &plan, &cap);
+        seg_layout(static_cast<char*>(ws) + g2_bytes, ws_bytes - g2_bytes, vt.total_tiles, seg_len_of(vt.total_tiles), &plan, &cap);
         GS_HIP(zero_seen_grad2d(proj->tiles, grad2d, n_slots, s));
         const Projected pr = to_proj(proj);
         const uint2* rg = reinterpret_cast<const uint2*>(tile_ranges);
@@ -604,7 +612,7 @@ int gs_composite_bwd(const gs_projected* proj, const uint32_t* pair_vals, const 
         hipStream_t s = (hipStream_t)stream;
         SegPlan plan;
         uint32_t cap;
-        seg_layout(seg_ws, seg_ws_bytes, vt.total_tiles, &plan, &cap);
+        seg_layout(seg_ws, seg_ws_bytes, vt.total_tiles, seg_len_of(vt.total_tiles), &plan, &cap);
         GS_HIP(zero_seen_grad2d(proj->tiles, grad2d, n_slots, s));
         const Projected pr = to_proj(proj);
         const uint2* rg = reinterpret_cast<const uint2*>(tile_ranges);

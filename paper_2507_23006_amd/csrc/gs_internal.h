@@ -239,8 +239,10 @@ hipError_t launch_bin_counts(const unsigned long long* total, const unsigned lon
 // tile launch order for compositing, longest lists first
 hipError_t launch_tile_order(const uint32_t* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t s);
 
-// Segmented compositing: lists longer than kSegLen positions are walked in
-// segments of kSegLen by separate workgroups, forward and backward.
+// Segmented compositing: lists longer than seg_len positions are walked in
+// segments of seg_len by separate workgroups, forward (past the head, the
+// first two segments, or kHeadLen positions when no list is longer) and
+// backward.
 // work_off [T + 1] and state_off [T + 1] are exclusive prefix sums, over the
 // tiles in launch order, of the work items (segments) and of the stored
 // segment states (segments 1 .. n - 1 of a segmented tile); state holds
@@ -248,7 +250,11 @@ hipError_t launch_tile_order(const uint32_t* ranges, uint32_t n_tiles, uint32_t*
 // b), D_seg and (int) the position of the segment's last entry; stop_seg
 // [T][256] (by tile) is the segment a pixel stops in, -1 for none, for the
 // segmented forward.
-constexpr int kSegLen = 512;
+constexpr int kSegLen = 512;          // segments of a large launch (seg_len_of)
+constexpr int kSegLenSmall = 128;     // and of a small one
+constexpr int kHeadLen = 1024;        // a multiple of both
+constexpr int kPlanLong = 0;          // SegPlan::info: launch positions up to the last one with several segments
+constexpr int kPlanHead = 1;          // segments in the head
 constexpr int kSegFields = 6;
 struct SegPlan {
     uint32_t* work_off;    // null: one work item per tile, no segments
@@ -257,7 +263,8 @@ struct SegPlan {
     uint32_t n_tiles;
     int32_t* stop_seg;
     uint32_t capacity;     // stored states the area holds
-    uint32_t* n_long;      // [1]: launch positions up to the last one with several segments
+    uint32_t* info;        // [2]: kPlanLong, kPlanHead
+    uint32_t seg_len;      // list positions per segment (a power of two, at least 64)
 };
 // plans the segments of every tile (segments disabled when they need more
 // than `capacity` stored states)

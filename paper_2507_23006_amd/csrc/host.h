@@ -55,7 +55,9 @@ int build_opt(const gs_options* o, OptK* k);
 // fixed part's bytes, and the plan over an area (NULL or smaller than the
 // fixed part: no segments)
 size_t seg_fixed_bytes(int64_t n_tiles);
-void seg_layout(void* base, size_t bytes, int64_t n_tiles, SegPlan* plan, uint32_t* capacity);
+void seg_layout(void* base, size_t bytes, int64_t n_tiles, int32_t seg_len, SegPlan* plan, uint32_t* capacity);
+// positions per segment for a launch of n_tiles tiles
+int32_t seg_len_of(int64_t n_tiles);
 
 // workspace bytes of bin_sort_slots
 size_t bin_workspace_bytes(int64_t n_slots, int64_t pair_capacity);

@@ -185,17 +185,7 @@ __device__ __forceinline__ int stage_chunk(const float4* __restrict__ rec, const
     return __popcll(m);
 }
 
-// largest i in [0, n] with a[i] <= v (a non-decreasing, a[0] <= v)
-__device__ __forceinline__ uint32_t last_le(const uint32_t* __restrict__ a, uint32_t n, uint32_t v) {
-    uint32_t lo = 0, hi = n + 1;      // invariant: a[lo] <= v, answer in [lo, hi)
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (a[mid] <= v) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// The compositing kernels launch one-wave workgroups, one per (item,
+// The compositing backward launches one-wave workgroups, one per (item,
 // quadrant): a workgroup of four quadrants holds its LDS and wave slots until
 // its slowest quadrant is done, which left half of the slots empty over the
 // long lists (their survivors differ from quadrant to quadrant).  Workgroups
@@ -216,7 +206,8 @@ __device__ __forceinline__ WaveItem wave_item() {
 // workgroups for n items
 unsigned wave_grid(unsigned n) { return (n + kXcds - 1) / kXcds * kXcds * 4u; }
 
-// last_le by one wave, 64 probes at a time (wave-uniform arguments)
+// largest i in [0, n] with a[i] <= v (a non-decreasing, a[0] <= v), by one
+// wave, 64 probes at a time (wave-uniform arguments)
 __device__ __forceinline__ uint32_t last_le_wave(const uint32_t* __restrict__ a, uint32_t n, uint32_t v, int lane) {
     uint32_t lo = 0, hi = n + 1;      // invariant: a[lo] <= v, answer in [lo, hi)
     while (hi - lo > 1) {
@@ -231,9 +222,9 @@ __device__ __forceinline__ uint32_t last_le_wave(const uint32_t* __restrict__ a,
 }
 
 // work item b of a plan -> launch position: the lists with several segments
-// lie in the first n_long positions, each later position is one item
+// lie in the first info[kPlanLong] positions, each later position is one item
 __device__ __forceinline__ uint32_t item_position(const SegPlan& plan, uint32_t b, int lane) {
-    const uint32_t k = *plan.n_long, w = plan.work_off[k];
+    const uint32_t k = plan.info[kPlanLong], w = plan.work_off[k];
     return b >= w ? k + (b - w) : last_le_wave(plan.work_off, k, b, lane);
 }
 
@@ -294,19 +285,17 @@ __device__ __forceinline__ int stage_gathered(const Gather& e, int pos, const Pi
     return __popcll(m);
 }
 
-// segmented forward: stop_seg value of a pixel still compositing after
-// the head; segments in the head (walked by the tile's workgroup)
+// segmented forward: stop_seg value of a pixel still compositing after the head
 constexpr int32_t kSegAlive = 0x7fffffff;
-constexpr int kHeadSegs = 2;
 
 // One wave composites quadrant `quad` of `tile` (staging in its LDS slice
 // `st`) and writes its pixels: the whole list, front to back.  With
 // head_stop (the tile's stop_seg row; a list the plan segments) only the
-// head, the first kHeadSegs segments: pixels that stop there (or whose list
+// head, the first head_len positions: pixels that stop there (or whose list
 // ends there) get their outputs and stop_seg = -1, the others their state
 // after it (rgb without background, depth, T, last) and stop_seg =
-// kSegAlive.  The head also writes the backward's states of its segments
-// 1 .. kHeadSegs - 1 (head_states: the tile's first stored state) from the
+// kSegAlive.  The head also writes the backward's states of its segments from
+// 1 on (seg_len positions; head_states: the tile's first stored state) from the
 // pixel's (T, C, D) at the segment's ends: T_seg = T_end / T_start and
 // C_seg = (C_end - C_start) / T_start -- the segment's composite with T
 // restarted at 1; the backward uses C_seg scaled back by T_start, so the
@@ -319,10 +308,11 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
                                                     float* __restrict__ alpha_out, float* __restrict__ T_out,
                                                     int32_t* __restrict__ last_out,
                                                     int32_t* __restrict__ head_stop = nullptr,
-                                                    float* __restrict__ head_states = nullptr) {
+                                                    float* __restrict__ head_states = nullptr,
+                                                    uint32_t seg_len = kSegLen, uint32_t head_len = kHeadLen) {
     const PixelCoords pc = pixel_coords(vt, tile, quad, lane);
     const uint2 rg = ranges[tile];
-    const uint32_t end = head_stop ? min(rg.x + (uint32_t)(kHeadSegs * kSegLen), rg.y) : rg.y;
+    const uint32_t end = head_stop ? min(rg.x + head_len, rg.y) : rg.y;
 
     float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, D = 0.0f;
     int last = 0;
@@ -343,7 +333,7 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
     Gather cur = load_entry(rec, load_slot(pair_vals, rg.x + lane, end));
     uint32_t s_next = load_slot(pair_vals, rg.x + kChunk + lane, end);
     for (uint32_t j0 = rg.x; j0 < end; j0 += kChunk) {
-        if (head_states && j0 != rg.x && (j0 - rg.x) % (uint32_t)kSegLen == 0) {
+        if (head_states && j0 != rg.x && ((j0 - rg.x) & (seg_len - 1u)) == 0) {
             if (seg >= 1) seg_state();
             ++seg;
             sT = T;
@@ -398,8 +388,8 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
     last_out[p] = last;
 }
 
-// Segmented forward, pass 2: one wave walks segment `seg` >= kHeadSegs
-// (list positions [seg S, (seg + 1) S), S = kSegLen) of a long list for the
+// Segmented forward, pass 2: one wave walks segment `seg` past the head
+// (list positions [seg S, (seg + 1) S), S = seg_len) of a long list for the
 // pixels of its quadrant still compositing after the head (`on`),
 // and keeps, over the entries that pass the alpha test, the segment's
 // state with T restarted at 1: T_seg = prod (1 - alpha), C_seg = sum c
@@ -412,9 +402,9 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
 // redoes), and the wave stops when all its pixels are.
 __device__ __forceinline__ void render_fwd_segment(const float4* __restrict__ rec,
                                                    const uint32_t* __restrict__ pair_vals, const uint2 rg,
-                                                   const PixelCoords& pc, bool on, int seg, int lane, WaveStage& st,
-                                                   float* __restrict__ state_row) {
-    const uint32_t lo = rg.x + (uint32_t)seg * kSegLen, hi = min(lo + (uint32_t)kSegLen, rg.y);
+                                                   const PixelCoords& pc, bool on, int seg, uint32_t seg_len, int lane,
+                                                   WaveStage& st, float* __restrict__ state_row) {
+    const uint32_t lo = rg.x + (uint32_t)seg * seg_len, hi = min(lo + seg_len, rg.y);
     float Tl = 1.0f, l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, Dl = 0.0f;
     int last = 0;
     Gather cur = load_entry(rec, load_slot(pair_vals, lo + lane, hi));
@@ -456,9 +446,9 @@ struct SegItem {
     uint32_t i;
     int seg, nseg;
 };
-__device__ __forceinline__ SegItem stored_seg(const SegPlan& plan, uint32_t b) {
+__device__ __forceinline__ SegItem stored_seg(const SegPlan& plan, uint32_t b, int lane) {
     SegItem it;
-    it.i = last_le(plan.state_off, plan.n_tiles, b);
+    it.i = last_le_wave(plan.state_off, plan.info[kPlanLong], b, lane);      // no states past it
     it.seg = (int)(b - plan.state_off[it.i]) + 1;
     it.nseg = (int)(plan.work_off[it.i + 1] - plan.work_off[it.i]);
     return it;
@@ -479,7 +469,9 @@ __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict_
     const int tile = launch_tile(tile_order, vt);
     int32_t* head_stop = nullptr;
     float* head_states = nullptr;
+    uint32_t head_len = kHeadLen;
     if (plan.work_off) {
+        head_len = plan.info[kPlanHead] * plan.seg_len;
         const uint32_t i = blockIdx.x;
         if (plan.work_off[i + 1] - plan.work_off[i] > 1u) {
             head_stop = plan.stop_seg + (size_t)tile * 256;
@@ -487,7 +479,8 @@ __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict_
         }
     }
     render_fwd_quadrant(rec, pair_vals, ranges, vt, opt, tile, wave, lane, stage[wave], rgb, depth, alpha_out, T_out,
-                        last_out, head_stop, head_states);
+                        last_out, head_stop, head_states, plan.seg_len,
+                        head_len);
 }
 
 // Pass 2, one workgroup per stored segment: the segment's state for the
@@ -501,14 +494,14 @@ __global__ __launch_bounds__(256, 7) void k_fwd_segments(const float4* __restric
     __shared__ WaveStage stage[kWaves];
     const uint32_t b = blockIdx.x;
     if (b >= plan.state_off[plan.n_tiles]) return;
-    const SegItem it = stored_seg(plan, b);
-    if (it.seg < kHeadSegs) return;        // the head's segments
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const SegItem it = stored_seg(plan, b, lane);
+    if (it.seg < (int)plan.info[kPlanHead]) return;        // the head's segments
     const int tile = order_tile(tile_order, vt, it.i);
     const PixelCoords pc = pixel_coords(vt, tile, wave, lane);
     const bool on = pc.inside && plan.stop_seg[(size_t)tile * 256 + pc.ly * kTile + pc.lx] == kSegAlive;
     if (__ballot(on) == 0) return;
-    render_fwd_segment(rec, pair_vals, ranges[tile], pc, on, it.seg, lane, stage[wave],
+    render_fwd_segment(rec, pair_vals, ranges[tile], pc, on, it.seg, plan.seg_len, lane, stage[wave],
                        plan.state + (size_t)b * kSegFields * 256);
 }
 
@@ -535,20 +528,34 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const uint32_t* __restrict_
     int last = last_out[p];
     int stop = -1;
     const uint32_t st0 = plan.state_off[i];
-    for (int j = kHeadSegs; j < nseg; ++j) {
-        const float* r = plan.state + (size_t)(st0 + (uint32_t)(j - 1)) * kSegFields * 256;
-        const float Ts = r[px];
-        if (T * Ts < kTMin) {
-            stop = j;
-            break;
+    // kFold segments' states are read together, so that the fold waits for
+    // one round of loads per kFold of them
+    constexpr int kFold = 4;
+    for (int j0 = (int)plan.info[kPlanHead]; j0 < nseg && stop < 0; j0 += kFold) {
+        float s[kFold][5];
+        int sl[kFold];
+#pragma unroll
+        for (int u = 0; u < kFold; ++u) {
+            const int j = min(j0 + u, nseg - 1);
+            const float* r = plan.state + (size_t)(st0 + (uint32_t)(j - 1)) * kSegFields * 256;
+#pragma unroll
+            for (int q = 0; q < 5; ++q) s[u][q] = r[q * 256 + px];
+            sl[u] = reinterpret_cast<const int32_t*>(r)[5 * 256 + px];
         }
-        c0 = fmaf(T, r[1 * 256 + px], c0);
-        c1 = fmaf(T, r[2 * 256 + px], c1);
-        c2 = fmaf(T, r[3 * 256 + px], c2);
-        D = fmaf(T, r[4 * 256 + px], D);
-        T *= Ts;
-        const int lj = reinterpret_cast<const int32_t*>(r)[5 * 256 + px];
-        last = lj > 0 ? lj : last;
+#pragma unroll
+        for (int u = 0; u < kFold; ++u) {
+            if (j0 + u >= nseg || stop >= 0) continue;
+            if (T * s[u][0] < kTMin) {
+                stop = j0 + u;
+                continue;
+            }
+            c0 = fmaf(T, s[u][1], c0);
+            c1 = fmaf(T, s[u][2], c1);
+            c2 = fmaf(T, s[u][3], c2);
+            D = fmaf(T, s[u][4], D);
+            T *= s[u][0];
+            last = sl[u] > 0 ? sl[u] : last;
+        }
     }
     stop_row[px] = stop;
     if (stop < 0) {
@@ -582,8 +589,8 @@ __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ r
     __shared__ WaveStage stage[kWaves];
     const uint32_t b = blockIdx.x;
     if (b >= plan.state_off[plan.n_tiles]) return;
-    const SegItem it = stored_seg(plan, b);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const SegItem it = stored_seg(plan, b, lane);
     const int tile = order_tile(tile_order, vt, it.i);
     const PixelCoords pc = pixel_coords(vt, tile, wave, lane);
     const int px = pc.ly * kTile + pc.lx;
@@ -603,7 +610,7 @@ __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ r
         D0 = depth[p];
         last = last_out[p];
     }
-    const uint32_t lo = rg.x + (uint32_t)it.seg * kSegLen, hi = min(lo + (uint32_t)kSegLen, rg.y);
+    const uint32_t lo = rg.x + (uint32_t)it.seg * plan.seg_len, hi = min(lo + plan.seg_len, rg.y);
     float Tl = 1.0f, l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, Dl = 0.0f;
     Gather cur = load_entry(rec, load_slot(pair_vals, lo + lane, hi));
     uint32_t s_next = load_slot(pair_vals, lo + kChunk + lane, hi);
@@ -874,7 +881,7 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
     if (nseg > 1) {
         const int px = pc.ly * kTile + pc.lx;
         for (int j = nseg - 1; j > seg; --j) {
-            if (j * kSegLen >= last) continue;
+            if (j * (int)plan.seg_len >= last) continue;
             const float* sj = plan.state + (size_t)(st0 + (uint32_t)(j - 1)) * kSegFields * 256;
             const float Ts = sj[0 * 256 + px];
             const float gcs = fmaf(gC0, sj[1 * 256 + px],
@@ -883,8 +890,8 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
             T = T / Ts;
             Q = Q * Ts;
         }
-        lo = seg * kSegLen;
-        hi = min((seg + 1) * kSegLen, maxlast);
+        lo = seg * (int)plan.seg_len;
+        hi = min(lo + (int)plan.seg_len, maxlast);
     }
     if (hi <= lo) return;
 
@@ -1098,8 +1105,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_wave
     return before + x - v;
 }
 
-// One workgroup: segments per tile in launch order (ceil(L / kSegLen) for a
-// list of L > kSegLen positions, else 1) and the stored states (segments
+// One workgroup: segments per tile in launch order (ceil(L / seg_len) for a
+// list of L > seg_len positions, else 1) and the stored states (segments
 // 1 .. n - 1); exclusive prefix sums into work_off / state_off.  When the
 // states would exceed `capacity`, every tile keeps a single segment.  Thread
 // t takes the consecutive positions [t k, t k + k), so the prefix sums need
@@ -1109,10 +1116,11 @@ constexpr uint32_t kPlanCache = 32640;
 constexpr int kPlanBatch = 8;
 __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ranges,
                                                    const uint32_t* __restrict__ tile_order, ViewTable vt,
-                                                   uint32_t capacity, uint32_t* __restrict__ work_off,
-                                                   uint32_t* __restrict__ state_off, uint32_t* __restrict__ n_long) {
+                                                   uint32_t seg_len, uint32_t capacity,
+                                                   uint32_t* __restrict__ work_off,
+                                                   uint32_t* __restrict__ state_off, uint32_t* __restrict__ info) {
     __shared__ uint32_t s_wave[16];
-    __shared__ uint32_t s_long;
+    __shared__ uint32_t s_long, s_max;
     __shared__ uint16_t s_nseg[kPlanCache];
     const uint32_t n_tiles = (uint32_t)vt.total_tiles;
     // segment counts of the launch positions [ib, min(ib + kPlanBatch, end))
@@ -1126,17 +1134,17 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
 #pragma unroll
         for (int u = 0; u < kPlanBatch; ++u) {
             const uint32_t L = r[u].y - r[u].x;
-            c[u] = L > (uint32_t)kSegLen ? (L + kSegLen - 1) / kSegLen : 1u;
+            c[u] = L > seg_len ? (L + seg_len - 1) / seg_len : 1u;
         }
     };
     const uint32_t k = (n_tiles + 1023) / 1024;
     const uint32_t i0 = threadIdx.x * k, i1 = min(i0 + k, n_tiles);
-    if (threadIdx.x == 0) s_long = 0;
+    if (threadIdx.x == 0) s_long = s_max = 0;
     __syncthreads();
     // pass 1: the thread's segment total (cached counts below 2^16).  The
     // positions are read kPlanBatch at a time, all loads first, so a thread
     // waits for one round of gathers per batch instead of one per position
-    uint32_t mine = 0, big = 0, end_long = 0;
+    uint32_t mine = 0, big = 0, end_long = 0, most = 0;
     for (uint32_t ib = i0; ib < i1; ib += kPlanBatch) {
         uint32_t c[kPlanBatch];
         nseg_batch(ib, i1, c);
@@ -1146,11 +1154,20 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
             if (i >= i1) break;
             mine += c[u];
             if (c[u] > 1u) end_long = i + 1;
+            most = max(most, c[u]);
             if (i < kPlanCache) s_nseg[i] = (uint16_t)c[u];
             big |= c[u] > 0xFFFFu ? 1u : 0u;
         }
     }
-    if (end_long) atomicMax(&s_long, end_long);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        end_long = max(end_long, (uint32_t)__shfl_xor((int)end_long, off, 64));
+        most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0 && end_long) {
+        atomicMax(&s_long, end_long);
+        atomicMax(&s_max, most);
+    }
     // the threads' prefix and the total (do the states fit?), and whether
     // any count was too large for the cache
     uint32_t total_seg = 0, total_big = 0;
@@ -1178,7 +1195,10 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
     if (threadIdx.x == 1023) {
         work_off[n_tiles] = on ? total_seg : n_tiles;
         state_off[n_tiles] = on ? total_need : 0u;
-        *n_long = on ? s_long : 0u;      // every position from here on holds one segment
+        info[kPlanLong] = on ? s_long : 0u;
+        // lists up to kHeadLen are composited by the head alone when none is
+        // longer: the later passes cost more than a head that long
+        info[kPlanHead] = s_max * seg_len > (uint32_t)kHeadLen ? 2u : (uint32_t)kHeadLen / seg_len;
     }
 }
 
@@ -1195,10 +1215,10 @@ __global__ __launch_bounds__(256) void k_seg_prepass(const float4* __restrict__ 
     __shared__ WaveStage stage[kWaves];
     const uint32_t b = blockIdx.x;
     if (b >= plan.state_off[plan.n_tiles]) return;
-    const uint32_t i = last_le(plan.state_off, plan.n_tiles, b);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t i = last_le_wave(plan.state_off, plan.info[kPlanLong], b, lane);
     const int j = (int)(b - plan.state_off[i]) + 1;
     const int tile = order_tile(tile_order, vt, i);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const PixelCoords pc = pixel_coords(vt, tile, wave, lane);
     WaveStage& st = stage[wave];
     const uint2 rg = ranges[tile];
@@ -1206,7 +1226,7 @@ __global__ __launch_bounds__(256) void k_seg_prepass(const float4* __restrict__ 
     int maxlast = last;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, off, 64));
-    const int lo = j * kSegLen, hi = min((j + 1) * kSegLen, maxlast);
+    const int lo = j * (int)plan.seg_len, hi = min(lo + (int)plan.seg_len, maxlast);
     float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, D = 0.0f;
     for (int b0 = lo; b0 < hi; b0 += kChunk) {
         const Gather e = load_entry(rec, load_slot(pair_vals, rg.x + (uint32_t)(b0 + lane), rg.x + (uint32_t)hi));
@@ -1260,7 +1280,7 @@ hipError_t launch_render_fwd(const Projected& proj, const uint32_t* pair_vals, c
         hipLaunchKernelGGL(k_render_fwd_persistent, dim3(grid), dim3(256), 0, s, proj.rec, pair_vals, ranges,
                            proj.tile_order, vt, opt, rgb, depth, alpha, T_final, last, work);
     } else {
-        const SegPlan none{nullptr, nullptr, nullptr, (uint32_t)vt.total_tiles, nullptr, 0u, nullptr};
+        const SegPlan none{nullptr, nullptr, nullptr, (uint32_t)vt.total_tiles, nullptr, 0u, nullptr, (uint32_t)kSegLen};
         hipLaunchKernelGGL(k_render_fwd, dim3(vt.total_tiles), dim3(256), 0, s, proj.rec, pair_vals, ranges,
                            proj.tile_order, vt, opt, rgb, depth, alpha, T_final, last, plan ? *plan : none);
         if (plan && plan->capacity) {
@@ -1288,8 +1308,8 @@ hipError_t launch_render_count(const Projected& proj, const uint32_t* pair_vals,
 
 hipError_t launch_seg_plan(const Projected& proj, const uint2* ranges, const ViewTable& vt, uint32_t capacity,
                            const SegPlan& plan, hipStream_t s) {
-    hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(1024), 0, s, ranges, proj.tile_order, vt, capacity, plan.work_off,
-                       plan.state_off, plan.n_long);
+    hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(1024), 0, s, ranges, proj.tile_order, vt, plan.seg_len, capacity,
+                       plan.work_off, plan.state_off, plan.info);
     return hipGetLastError();
 }
 

@@ -429,10 +429,11 @@ int launch_batch(Worker* w, BufSet& b, Request* r, int nb, bool full_bound = fal
         GS_HIP(launch_tile_order(b.ranges, (uint32_t)vt.total_tiles, b.proj.tile_order, w->render));
     }
     // long lists composited in segments (one workgroup per tile when the
-    // compositing is persistent)
+    // compositing is persistent), of one length whatever the batch: their
+    // length groups the products, and an image does not depend on its batch
     SegPlan plan;
     uint32_t cap = 0;
-    seg_layout(b.seg, b.seg_bytes, vt.total_tiles, &plan, &cap);
+    seg_layout(b.seg, b.seg_bytes, vt.total_tiles, kSegLen, &plan, &cap);
     const bool segmented = plan.work_off && slots > 0 && s->cfg.persistent_ctas == 0;
     if (segmented)
         GS_HIP(launch_seg_plan(b.proj, reinterpret_cast<const uint2*>(b.ranges), vt, cap, plan, w->render));
