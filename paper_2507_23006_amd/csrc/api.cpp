@@ -170,18 +170,17 @@ int tile_bits(int64_t n_tiles) {
     return b;
 }
 
-constexpr int kTotals = 16 + 16 * kBinPairParts;
-
 struct BinWs {
     uint32_t *dkeys, *dvals, *dkeys_alt, *dvals_alt;
     uint4* desc;
-    uint32_t *tiles_s, *offsets;
+    uint32_t *tiles_s, *offsets, *chunk_first;
     uint2* rect_s;
     uint64_t* mask_s;
     uint32_t* slot_s;
     uint32_t* hist;
     uint32_t* scan_tmp;
-    unsigned long long* total;
+    uint32_t* vis;          // visible slots and pairs per kBinVisTile slots
+    unsigned long long* vis_pairs;
     uint32_t* cnt;          // effective visible and pair counts on the device
     uint32_t *pkeys, *pkeys_alt, *pvals_alt;
 };
@@ -196,12 +195,15 @@ size_t bin_layout(int64_t n_slots, int64_t cap, void* base, BinWs* w) {
     w->desc = c.take<uint4>(2 * N);
     w->tiles_s = c.take<uint32_t>(N);
     w->offsets = c.take<uint32_t>(N);
+    w->chunk_first = c.take<uint32_t>((Pc + kEmitChunk - 1) / kEmitChunk);
     w->rect_s = c.take<uint2>(N);
     w->mask_s = c.take<uint64_t>(N);
     w->slot_s = c.take<uint32_t>(N);
     w->hist = c.take<uint32_t>(radix_hist_elems((uint32_t)(N > Pc ? N : Pc)));
     w->scan_tmp = c.take<uint32_t>(scan_tmp_elems((uint32_t)N));
-    w->total = c.take<unsigned long long>(kTotals);   // [0] visible, [8] offsets total, [16 + 16k] pair parts
+    const size_t vis_tiles = (N + kBinVisTile - 1) / kBinVisTile;
+    w->vis = c.take<uint32_t>(vis_tiles);
+    w->vis_pairs = c.take<unsigned long long>(vis_tiles);
     w->cnt = c.take<uint32_t>(4);
     w->pkeys = c.take<uint32_t>(Pc);
     w->pkeys_alt = c.take<uint32_t>(Pc);
@@ -268,14 +270,10 @@ int bin_sort_slots(const Projected& pr, const ViewTable& vt, int64_t n_slots, in
     const uint32_t N = (uint32_t)n_slots, Pc = (uint32_t)pair_capacity;
     const hipEvent_t timed = timer_begin(GS_KERNEL_BIN_SORT, s);
 
-    // 1. visible slots in slot order (scan of tiles > 0, scatter) with the
-    //    pair count summed in the same pass; the counts stay on the device:
-    //    every later launch is sized by N or the pair capacity and reads
-    //    them there
-    GS_HIP(fill_u32(reinterpret_cast<uint32_t*>(w.total), 0u, 2 * kTotals, s));
-    GS_HIP(exclusive_scan_nonzero_u32(pr.tiles, w.offsets, N, w.scan_tmp, w.total, w.total + 16, s));
-    GS_HIP(launch_bin_counts(w.total, w.total + 16, Pc, n_pairs_dev, w.cnt, s));
-    GS_HIP(launch_compact_visible(pr, w.offsets, N, w.dkeys, w.dvals, w.desc, s));
+    // 1. visible slots in slot order with the pair count; the counts stay on
+    //    the device: every later launch is sized by N or the pair capacity and
+    //    reads them there
+    GS_HIP(launch_compact_visible(pr, N, Pc, w.vis, w.vis_pairs, w.dkeys, w.desc, n_pairs_dev, w.cnt, s));
     // 2. depth order of the visible slots (stable: ties stay in slot order,
     //    which is compaction order); per depth rank its tile count, rectangle,
     //    mask and slot; exclusive scan -> pair offsets.  A visible slot emits
@@ -284,18 +282,20 @@ int bin_sort_slots(const Projected& pr, const ViewTable& vt, int64_t n_slots, in
     //    over visible slots are sized by that bound
     const uint32_t Nv = (uint32_t)std::min<int64_t>(n_slots, std::max<int64_t>(pair_capacity, 1));
     bool alt = false;
+    if (radix_passes(Nv, 0, 32) == 0) GS_HIP(fill_u32(w.dvals, 0u, 1, s));      // one slot: its position
     GS_HIP(radix_sort_pairs(w.dkeys, w.dvals, w.dkeys_alt, w.dvals_alt, Nv, 0, 32, w.hist, s, &alt, w.cnt,
-                            /*small_tiles=*/true));
+                            /*small_tiles=*/true, /*vals_are_positions=*/true));
     const uint32_t* sorted_pos = alt ? w.dvals_alt : w.dvals;
-    GS_HIP(launch_gather_sorted(sorted_pos, w.desc, Nv, w.cnt, w.tiles_s, w.rect_s, w.mask_s, w.slot_s, s));
-    GS_HIP(exclusive_scan_u32(w.tiles_s, w.offsets, Nv, w.scan_tmp, w.total + 8, s, w.cnt));
+    GS_HIP(launch_gather_sorted(sorted_pos, w.desc, Nv, w.cnt, w.tiles_s, w.rect_s, w.mask_s, w.slot_s, w.scan_tmp, s));
+    GS_HIP(exclusive_scan_sums_u32(w.tiles_s, w.offsets, Nv, w.cnt, w.scan_tmp, w.chunk_first, kEmitChunk, s));
     // 3. expand into (tile, slot) pairs in depth order, then stable sort by tile id
     const int bits = tile_bits(vt.total_tiles);
     const int passes = radix_passes(Pc, 0, bits);
     uint32_t* vals_primary = (passes % 2 == 0) ? pair_vals : w.pvals_alt;
     uint32_t* vals_alt = (passes % 2 == 0) ? w.pvals_alt : pair_vals;
-    GS_HIP(launch_emit_pairs(w.offsets, w.rect_s, pr.tile_mask ? w.mask_s : nullptr, w.slot_s, Nv, Pc, w.cnt, w.pkeys,
-                             vals_primary, s));
+    GS_HIP(launch_emit_pairs(w.offsets, w.chunk_first, w.rect_s, pr.tile_mask ? w.mask_s : nullptr, w.slot_s, Nv, Pc, w.cnt,
+                             w.pkeys,
+                             vals_primary, tile_ranges, (uint32_t)vt.total_tiles, s));
     bool palt = false;
     GS_HIP(radix_sort_pairs(w.pkeys, vals_primary, w.pkeys_alt, vals_alt, Pc, 0, bits, w.hist, s, &palt, w.cnt + 1));
     const uint32_t* sorted_keys = palt ? w.pkeys_alt : w.pkeys;

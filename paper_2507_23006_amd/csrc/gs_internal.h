@@ -199,43 +199,46 @@ size_t radix_hist_elems(uint32_t n);        // counters needed per pass
 int radix_passes(uint32_t n, int begin_bit, int end_bit);
 hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                             uint32_t n, int begin_bit, int end_bit, uint32_t* hist, hipStream_t s,
-                            bool* result_in_alt, const uint32_t* n_dev = nullptr, bool small_tiles = false);
+                            bool* result_in_alt, const uint32_t* n_dev = nullptr, bool small_tiles = false,
+                            bool vals_are_positions = false);
 size_t scan_tmp_elems(uint32_t n);
-// with n_dev, the scanned count is ceil(*n_dev / div) * mul, at most n
 hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                              unsigned long long* total, hipStream_t s, const uint32_t* n_dev = nullptr,
-                              uint32_t div = 1, uint32_t mul = 1);
-// exclusive scan of (in[i] != 0); the sum of in[] itself is added to
-// sum_parts (kBinPairParts partial sums, 16 u64 apart, zeroed by the caller)
-hipError_t exclusive_scan_nonzero_u32(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                                      unsigned long long* total, unsigned long long* sum_parts, hipStream_t s);
+                              unsigned long long* total, hipStream_t s);
+// the same without a total, with the sums of every kScanTileElems elements
+// given (written by the kernel that wrote the elements); the elements count
+// items, and chunk_first[c] gets the element that holds item c * chunk
+constexpr int kScanTileElems = 2048;
+hipError_t exclusive_scan_sums_u32(const uint32_t* in, uint32_t* out, uint32_t n, const uint32_t* n_dev,
+                                   const uint32_t* tile_sums, uint32_t* chunk_first, uint32_t chunk, hipStream_t s);
+constexpr uint32_t kEmitChunk = 1024;       // pairs per workgroup of the emission
 hipError_t fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
 // zero the [12]-float 2D-gradient rows of slots with tiles > 0
 hipError_t zero_seen_grad2d(const uint32_t* tiles, float* grad2d, int64_t n_slots, hipStream_t s);
 
 // binning (bin.hip)
-// pair counts are summed into kBinPairParts partial sums, 16 u64 apart
-constexpr int kBinPairParts = 64;
-// compaction of the visible slots: depth keys, their positions as sort
-// values, and per position a 32-byte descriptor (uint4 pair: rect.x, rect.y,
-// mask lo, mask hi; tiles, slot, 0, 0)
-hipError_t launch_compact_visible(const Projected& proj, const uint32_t* pos, uint32_t n_slots, uint32_t* keys,
-                                  uint32_t* vals, uint4* desc, hipStream_t s);
-hipError_t launch_gather_sorted(const uint32_t* sorted_pos, const uint4* desc, uint32_t n_visible, const uint32_t* counts,
-                                uint32_t* tiles_s, uint2* rect_s, uint64_t* mask_s, uint32_t* slot_s, hipStream_t s);
+// compaction of the visible slots: depth keys (the sort values are their
+// positions) and per position a 32-byte descriptor (uint4 pair: rect.x, rect.y,
+// mask lo, mask hi; tiles, slot, 0, 0); vis and pairs hold a count per
+// kBinVisTile slots.  The pair count goes to n_pairs_out; the effective counts
+// counts[0] (visible) and counts[1] (pairs) are 0 when the pairs exceed capacity
+constexpr uint32_t kBinVisTile = 2048;
+hipError_t launch_compact_visible(const Projected& proj, uint32_t n_slots, unsigned long long capacity, uint32_t* vis,
+                                  unsigned long long* pairs, uint32_t* keys, uint4* desc, int64_t* n_pairs_out,
+                                  uint32_t* counts, hipStream_t s);
 // gather, emission and ranges take their counts from the device (counts[0]
-// visible ranks, counts[1] pairs, from launch_bin_counts) when counts is
-// set, within the launch bounds n_visible / n_slots, n_pairs
-hipError_t launch_emit_pairs(const uint32_t* offsets, const uint2* rect_s, const uint64_t* mask_s,
+// visible ranks, counts[1] pairs), within the launch bounds n_visible /
+// n_slots, n_pairs; the emission also zeroes the tile ranges
+hipError_t launch_gather_sorted(const uint32_t* sorted_pos, const uint4* desc, uint32_t n_visible, const uint32_t* counts,
+                                uint32_t* tiles_s, uint2* rect_s, uint64_t* mask_s, uint32_t* slot_s,
+                                uint32_t* tile_sums, hipStream_t s);
+// chunk_first: the depth rank that holds pair c * kEmitChunk
+hipError_t launch_emit_pairs(const uint32_t* offsets, const uint32_t* chunk_first, const uint2* rect_s,
+                             const uint64_t* mask_s,
                              const uint32_t* sorted_slot, uint32_t n_slots, uint32_t n_pairs, const uint32_t* counts,
-                             uint32_t* pair_key, uint32_t* pair_val, hipStream_t s);
+                             uint32_t* pair_key, uint32_t* pair_val, uint32_t* ranges, uint32_t n_tiles,
+                             hipStream_t s);
 hipError_t launch_tile_ranges(const uint32_t* sorted_keys, uint32_t n_pairs, const uint32_t* counts, uint32_t* ranges,
                               uint32_t n_tiles, hipStream_t s);
-// total[0] = visible slots, parts = kBinPairParts pair-count parts (16
-// apart): writes the pair count to n_pairs_out and the effective counts
-// counts[0..1], 0 when the pairs exceed capacity
-hipError_t launch_bin_counts(const unsigned long long* total, const unsigned long long* parts,
-                             unsigned long long capacity, int64_t* n_pairs_out, uint32_t* counts, hipStream_t s);
 // tile launch order for compositing, longest lists first
 hipError_t launch_tile_order(const uint32_t* ranges, uint32_t n_tiles, uint32_t* order, hipStream_t s);
 

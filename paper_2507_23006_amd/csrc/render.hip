@@ -1108,12 +1108,11 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_wave
 // One workgroup: segments per tile in launch order (ceil(L / seg_len) for a
 // list of L > seg_len positions, else 1) and the stored states (segments
 // 1 .. n - 1); exclusive prefix sums into work_off / state_off.  When the
-// states would exceed `capacity`, every tile keeps a single segment.  Thread
-// t takes the consecutive positions [t k, t k + k), so the prefix sums need
-// one workgroup scan of the threads' totals, not one per 1024 tiles; the
-// counts of up to kPlanCache tiles stay in LDS between the two passes.
-constexpr uint32_t kPlanCache = 32640;
-constexpr int kPlanBatch = 8;
+// states would exceed `capacity`, every tile keeps a single segment.  The
+// positions are taken kPlanPer consecutive ones per thread, 8192 at a time, so
+// that the order is read and the offsets are written in whole lines and a
+// chunk waits for one round of range gathers (100k tiles: 300 -> 159 us; the gathers of one compute unit bound it).
+constexpr int kPlanPer = 8;
 __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ranges,
                                                    const uint32_t* __restrict__ tile_order, ViewTable vt,
                                                    uint32_t seg_len, uint32_t capacity,
@@ -1121,42 +1120,35 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
                                                    uint32_t* __restrict__ state_off, uint32_t* __restrict__ info) {
     __shared__ uint32_t s_wave[16];
     __shared__ uint32_t s_long, s_max;
-    __shared__ uint16_t s_nseg[kPlanCache];
     const uint32_t n_tiles = (uint32_t)vt.total_tiles;
-    // segment counts of the launch positions [ib, min(ib + kPlanBatch, end))
-    auto nseg_batch = [&](uint32_t ib, uint32_t end, uint32_t* c) {
-        int t[kPlanBatch];
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; ++u) t[u] = ib + u < end ? order_tile(tile_order, vt, ib + u) : -1;
-        uint2 r[kPlanBatch];
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; ++u) r[u] = t[u] >= 0 ? ranges[t[u]] : make_uint2(0u, 0u);
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; ++u) {
-            const uint32_t L = r[u].y - r[u].x;
-            c[u] = L > seg_len ? (L + seg_len - 1) / seg_len : 1u;
-        }
-    };
-    const uint32_t k = (n_tiles + 1023) / 1024;
-    const uint32_t i0 = threadIdx.x * k, i1 = min(i0 + k, n_tiles);
     if (threadIdx.x == 0) s_long = s_max = 0;
-    __syncthreads();
-    // pass 1: the thread's segment total (cached counts below 2^16).  The
-    // positions are read kPlanBatch at a time, all loads first, so a thread
-    // waits for one round of gathers per batch instead of one per position
-    uint32_t mine = 0, big = 0, end_long = 0, most = 0;
-    for (uint32_t ib = i0; ib < i1; ib += kPlanBatch) {
-        uint32_t c[kPlanBatch];
-        nseg_batch(ib, i1, c);
+    uint32_t end_long = 0, most = 0, before = 0;      // segments of the earlier chunks
+    for (uint32_t c0 = 0; c0 < n_tiles; c0 += 1024 * kPlanPer) {
+        const uint32_t i0 = c0 + threadIdx.x * kPlanPer;
+        int t[kPlanPer];
 #pragma unroll
-        for (int u = 0; u < kPlanBatch; ++u) {
-            const uint32_t i = ib + u;
-            if (i >= i1) break;
-            mine += c[u];
-            if (c[u] > 1u) end_long = i + 1;
+        for (int u = 0; u < kPlanPer; ++u) t[u] = i0 + u < n_tiles ? order_tile(tile_order, vt, i0 + u) : -1;
+        uint2 r[kPlanPer];
+#pragma unroll
+        for (int u = 0; u < kPlanPer; ++u) r[u] = t[u] >= 0 ? ranges[t[u]] : make_uint2(0u, 0u);
+        uint32_t c[kPlanPer], mine = 0;
+#pragma unroll
+        for (int u = 0; u < kPlanPer; ++u) {
+            const uint32_t L = r[u].y - r[u].x;
+            c[u] = t[u] < 0 ? 0u : L > seg_len ? (L + seg_len - 1) / seg_len : 1u;
+            if (c[u] > 1u) end_long = i0 + u + 1;
             most = max(most, c[u]);
-            if (i < kPlanCache) s_nseg[i] = (uint16_t)c[u];
-            big |= c[u] > 0xFFFFu ? 1u : 0u;
+            mine += c[u];
+        }
+        uint32_t total = 0;
+        uint32_t w = before + block_excl_scan(mine, s_wave, &total);
+        before += total;
+#pragma unroll
+        for (int u = 0; u < kPlanPer; ++u) {
+            if (t[u] < 0) break;
+            work_off[i0 + u] = w;
+            state_off[i0 + u] = w - (i0 + u);
+            w += c[u];
         }
     }
 #pragma unroll
@@ -1164,38 +1156,23 @@ __global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ran
         end_long = max(end_long, (uint32_t)__shfl_xor((int)end_long, off, 64));
         most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
     }
-    if ((threadIdx.x & 63) == 0 && end_long) {
+    __syncthreads();      // s_long and s_max are zero
+    if ((threadIdx.x & 63) == 0) {
         atomicMax(&s_long, end_long);
         atomicMax(&s_max, most);
     }
-    // the threads' prefix and the total (do the states fit?), and whether
-    // any count was too large for the cache
-    uint32_t total_seg = 0, total_big = 0;
-    const uint32_t before_seg = block_excl_scan(mine, s_wave, &total_seg);
-    (void)block_excl_scan(big, s_wave, &total_big);      // its barriers also publish s_nseg
-    const uint32_t total_need = total_seg - n_tiles;
-    const bool on = total_need <= capacity;
-    const bool cached = total_big == 0;
-    // pass 2: each position's offsets from the thread's exclusive prefix
-    uint32_t w = on ? before_seg : i0, st = on ? before_seg - i0 : 0u;
-    for (uint32_t ib = i0; ib < i1; ib += kPlanBatch) {
-        uint32_t c[kPlanBatch];
-        if (on && !(cached && ib + kPlanBatch <= kPlanCache)) nseg_batch(ib, i1, c);
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; ++u) {
-            const uint32_t i = ib + u;
-            if (i >= i1) break;
-            const uint32_t ci = on ? (cached && i < kPlanCache ? (uint32_t)s_nseg[i] : c[u]) : 1u;
-            work_off[i] = w;
-            state_off[i] = st;
-            w += ci;
-            st += ci - 1u;
+    __syncthreads();
+    const uint32_t need = before - n_tiles;
+    const bool on = need <= capacity;      // do the states fit?
+    if (!on)
+        for (uint32_t i = threadIdx.x; i < n_tiles; i += 1024) {
+            work_off[i] = i;
+            state_off[i] = 0;
         }
-    }
-    if (threadIdx.x == 1023) {
-        work_off[n_tiles] = on ? total_seg : n_tiles;
-        state_off[n_tiles] = on ? total_need : 0u;
-        info[kPlanLong] = on ? s_long : 0u;
+    if (threadIdx.x == 0) {
+        work_off[n_tiles] = on ? before : n_tiles;
+        state_off[n_tiles] = on ? need : 0u;
+        info[kPlanLong] = on ? (s_max > 1u ? s_long : 0u) : 0u;
         // lists up to kHeadLen are composited by the head alone when none is
         // longer: the later passes cost more than a head that long
         info[kPlanHead] = s_max * seg_len > (uint32_t)kHeadLen ? 2u : (uint32_t)kHeadLen / seg_len;

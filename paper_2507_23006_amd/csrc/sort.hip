@@ -1,18 +1,22 @@
 // Device-wide primitives for binning: a stable LSD radix sort of
 // (uint32 key, uint32 value) pairs and an exclusive scan of uint32 -- gfx950.
 //
-// Radix pass = three steps, four launches (reduce-then-scan, no
-// inter-workgroup waiting, so no kernel can hang on a missing predecessor):
+// Radix pass = two or three launches, none of which waits for another
+// workgroup (so no kernel can hang on a missing predecessor):
 //   1. upsweep: each workgroup counts the digits of its tile (1024 or 2048
-//      keys); counts go to a digit-major table hist[digit][tile];
-//   2. the table is exclusive-scanned in digit-major order (two launches),
-//      which yields the global output offset of every (digit, tile);
-//   3. downsweep: each wave64 ranks its keys in rounds of 64 with
-//      ballot-based digit matching (lanes with equal digits find each other
-//      through one __ballot per digit bit; rank = popcount of lower peers),
-//      keeping per-wave running digit counters in LDS.  Keys and values are
-//      then scattered into LDS in digit order and written out in runs, so
-//      global stores are contiguous per digit.
+//      keys) into a table of [digit][tile];
+//   2. row scan: one workgroup per digit scans its row of the table in place
+//      and leaves the row's total;
+//   3. downsweep: every workgroup scans the row totals, which with its column
+//      of the table gives the output offset of each of its digits; each wave64
+//      ranks its keys in rounds of 64 with ballot-based digit matching (lanes
+//      with equal digits find each other through one __ballot per digit bit;
+//      rank = popcount of lower peers), keeping per-wave running digit counters
+//      in LDS.  Keys and values are then scattered into LDS in digit order and
+//      written out in runs, so global stores are contiguous per digit.
+// Sorts of at most kFewTiles tiles leave out the row scan: the table is laid
+// out [tile][digit] and the downsweep adds up the earlier tiles' counts itself
+// (64 coalesced loads in flight, about 2 us, against a launch of 4 us).
 // Stability: inside a wave items are ranked in (round, lane) order, waves
 // and tiles are concatenated in order, so equal keys keep input order.
 #include "gs_internal.h"
@@ -28,6 +32,8 @@ constexpr int kMaxRadixBits = 8;
 // ones take 8 (fewer digit-table entries to scan).
 constexpr uint32_t kSmallSortMax = 1u << 21;
 constexpr int kMinSortTile = kSortThreads * 4;      // digit tables are sized for this
+constexpr uint32_t kFewTiles = 64;
+constexpr uint32_t kLongRow = 4096;      // tiles from which the row scan takes 1024 threads
 
 __device__ __forceinline__ unsigned long long lanemask_lt() {
     const unsigned lane = __lane_id();
@@ -51,21 +57,10 @@ __device__ __forceinline__ uint32_t count_of(uint32_t n, const uint32_t* __restr
     return n_dev ? min(*n_dev, n) : n;
 }
 
-// The element count of a scan over a table derived from a device count:
-// ceil(*n_dev / div) * mul (the digit table of a sort: tiles x radix), at
-// most n; n itself without n_dev.
-__device__ __forceinline__ uint32_t scaled_count_of(uint32_t n, const uint32_t* __restrict__ n_dev, uint32_t div,
-                                                    uint32_t mul) {
-    if (!n_dev) return n;
-    const uint64_t c = ((uint64_t)*n_dev + div - 1) / div * mul;
-    return c < n ? (uint32_t)c : n;
-}
-
-template <int kSortIpt>
+template <int kSortIpt, bool kFew>
 __global__ __launch_bounds__(kSortThreads) void k_radix_upsweep(const uint32_t* __restrict__ keys, uint32_t n_max,
                                                                 const uint32_t* __restrict__ n_dev, int shift,
-                                                                int bits, uint32_t* __restrict__ hist,
-                                                                uint32_t n_tiles) {
+                                                                int bits, uint32_t* __restrict__ hist) {
     constexpr int kSortTile = kSortThreads * kSortIpt, kWaveItems = 64 * kSortIpt;
     __shared__ uint32_t cnt[4][1 << kMaxRadixBits];
     // the digit table has one column per tile that holds keys: its row
@@ -74,42 +69,104 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_upsweep(const uint32_t* 
     const uint32_t n = count_of(n_max, n_dev);
     const uint32_t n_tab = (uint32_t)(((uint64_t)n + kSortTile - 1) / kSortTile);
     if (blockIdx.x >= n_tab) return;
-    (void)n_tiles;
     const int radix = 1 << bits;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t base = blockIdx.x * kSortTile + wave * kWaveItems;
+    uint32_t key[kSortIpt];
+#pragma unroll
+    for (int r = 0; r < kSortIpt; ++r) key[r] = base + r * 64 + lane < n ? keys[base + r * 64 + lane] : 0u;
     // rows are (1 << kMaxRadixBits) apart: clear the whole table, not 4 * radix entries
     for (int i = threadIdx.x; i < 4 * (1 << kMaxRadixBits); i += kSortThreads) (&cnt[0][0])[i] = 0;
     __syncthreads();
-    const uint32_t base = blockIdx.x * kSortTile + wave * kWaveItems;
     const uint32_t mask = (uint32_t)radix - 1;
+#pragma unroll
     for (int r = 0; r < kSortIpt; ++r) {
-        const uint32_t idx = base + r * 64 + lane;
-        const bool valid = idx < n;
-        const uint32_t d = valid ? (keys[idx] >> shift) & mask : 0u;
+        const bool valid = base + r * 64 + lane < n;
+        const uint32_t d = (key[r] >> shift) & mask;
         const unsigned long long m = match_digit(d, valid, bits);
         if (valid && lane == __ffsll((unsigned long long)m) - 1) cnt[wave][d] += (uint32_t)__popcll(m);
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     for (int d = threadIdx.x; d < radix; d += kSortThreads)
-        hist[(size_t)d * n_tab + blockIdx.x] = cnt[0][d] + cnt[1][d] + cnt[2][d] + cnt[3][d];
+        hist[kFew ? (size_t)blockIdx.x * radix + d : (size_t)d * n_tab + blockIdx.x] =
+            cnt[0][d] + cnt[1][d] + cnt[2][d] + cnt[3][d];
 }
 
-template <int kSortIpt>
+// One workgroup per digit: exclusive scan of its row of the table (one count
+// per tile) in place; its total goes to row_total.  A row is walked in chunks
+// of 8 per thread, one after another: long rows (76M pairs: 37k tiles) take
+// 1024 threads (4 waves walk such a row in 39 us).
+constexpr int kRowIpt = 8;
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_radix_rowscan(uint32_t* __restrict__ hist, uint32_t n_max,
+                                                            const uint32_t* __restrict__ n_dev, uint32_t sort_tile,
+                                                            uint32_t* __restrict__ row_total) {
+    constexpr int kWaves = kThreads / 64;
+    __shared__ uint32_t s_w[2][kWaves];
+    const uint32_t n = count_of(n_max, n_dev);
+    const uint32_t n_tab = (uint32_t)(((uint64_t)n + sort_tile - 1) / sort_tile);
+    uint32_t* row = hist + (size_t)blockIdx.x * n_tab;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    uint32_t before = 0;
+    int buf = 0;
+    uint32_t v[kRowIpt];
+    auto load = [&](uint32_t c0) {
+        // kRowIpt consecutive entries per thread
+        const uint32_t i0 = c0 + threadIdx.x * kRowIpt;
+#pragma unroll
+        for (int r = 0; r < kRowIpt; ++r) v[r] = i0 + r < n_tab ? row[i0 + r] : 0u;
+    };
+    load(0);
+    for (uint32_t c0 = 0; c0 < n_tab; c0 += kThreads * kRowIpt) {
+        uint32_t cur[kRowIpt], sum = 0;
+#pragma unroll
+        for (int r = 0; r < kRowIpt; ++r) {
+            cur[r] = v[r];
+            sum += v[r];
+        }
+        load(c0 + kThreads * kRowIpt);      // the next chunk, beside this one's scan
+        uint32_t incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += y;
+        }
+        if (lane == 63) s_w[buf][wave] = incl;
+        __syncthreads();
+        uint32_t pre = before + incl - sum;
+        for (int w = 0; w < kWaves; ++w) {
+            const uint32_t x = s_w[buf][w];
+            pre += w < wave ? x : 0u;
+            before += x;
+        }
+        buf ^= 1;      // the other buffer is written before the next barrier
+        const uint32_t i0 = c0 + threadIdx.x * kRowIpt;
+#pragma unroll
+        for (int r = 0; r < kRowIpt; ++r) {
+            if (i0 + r < n_tab) row[i0 + r] = pre;
+            pre += cur[r];
+        }
+    }
+    if (threadIdx.x == 0) row_total[blockIdx.x] = before;
+}
+
+// vin NULL: the values are the input positions
+template <int kSortIpt, bool kFew>
 __global__ __launch_bounds__(kSortThreads) void k_radix_downsweep(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
     uint32_t* __restrict__ vout, uint32_t n_max, const uint32_t* __restrict__ n_dev, int shift, int bits,
-    const uint32_t* __restrict__ hist_scan, uint32_t n_tiles) {
+    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ row_total) {
     constexpr int kSortTile = kSortThreads * kSortIpt, kWaveItems = 64 * kSortIpt;
     const uint32_t n = count_of(n_max, n_dev);
     if (blockIdx.x * (uint32_t)kSortTile >= n) return;     // no keys in this tile
     const uint32_t n_tab = (uint32_t)(((uint64_t)n + kSortTile - 1) / kSortTile);   // digit-table stride
-    (void)n_tiles;
     __shared__ uint32_t s_keys[kSortTile];
     __shared__ uint32_t s_vals[kSortTile];
     __shared__ uint32_t s_wcnt[4][1 << kMaxRadixBits];
     __shared__ uint32_t s_bstart[1 << kMaxRadixBits];
     __shared__ uint32_t s_goff[1 << kMaxRadixBits];
-    __shared__ uint32_t s_wsum[4];
+    __shared__ uint32_t s_wsum[4], s_gsum[4];
 
     const int radix = 1 << bits;
     const uint32_t mask = (uint32_t)radix - 1;
@@ -125,7 +182,22 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_downsweep(
         const uint32_t idx = base + r * 64 + lane;
         const bool valid = idx < n;
         key[r] = valid ? kin[idx] : 0u;
-        val[r] = valid ? vin[idx] : 0u;
+        val[r] = !vin ? idx : valid ? vin[idx] : 0u;
+    }
+    // this thread's digit: its keys in earlier tiles, and in all
+    uint32_t earlier = 0, all = 0;
+    if ((int)threadIdx.x < radix) {
+        if (kFew) {
+#pragma unroll 16
+            for (uint32_t c = 0; c < n_tab; ++c) {
+                const uint32_t h = hist[(size_t)c * radix + threadIdx.x];
+                all += h;
+                earlier += c < blockIdx.x ? h : 0u;
+            }
+        } else {
+            all = row_total[threadIdx.x];
+            earlier = hist[(size_t)threadIdx.x * n_tab + blockIdx.x];
+        }
     }
     const unsigned long long lt = lanemask_lt();
 #pragma unroll
@@ -146,8 +218,8 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_downsweep(
     }
     __syncthreads();
 
-    // per digit: exclusive prefix over waves, block total, then an exclusive
-    // scan of the block totals over digits
+    // per digit: exclusive prefix over waves and block total, then exclusive
+    // scans over the digits of the block totals and of the counts in all
     uint32_t total = 0;
     if ((int)threadIdx.x < radix) {
         const int d = threadIdx.x;
@@ -157,20 +229,31 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_downsweep(
         s_wcnt[2][d] = c0 + c1;
         s_wcnt[3][d] = c0 + c1 + c2;
         total = c0 + c1 + c2 + c3;
-        s_goff[d] = hist_scan[(size_t)d * n_tab + blockIdx.x];
     }
-    // block-wide exclusive scan of `total` (thread d holds digit d)
-    uint32_t incl = total;
+    // thread d holds digit d
+    uint32_t incl = total, gincl = all;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += y;
+        const uint32_t y = __shfl_up(incl, off, 64), g = __shfl_up(gincl, off, 64);
+        if (lane >= off) {
+            incl += y;
+            gincl += g;
+        }
     }
-    if (lane == 63) s_wsum[wave] = incl;
+    if (lane == 63) {
+        s_wsum[wave] = incl;
+        s_gsum[wave] = gincl;
+    }
     __syncthreads();
-    uint32_t wpre = 0;
-    for (int w = 0; w < wave; ++w) wpre += s_wsum[w];
-    if ((int)threadIdx.x < radix) s_bstart[threadIdx.x] = wpre + incl - total;
+    uint32_t wpre = 0, gpre = 0;
+    for (int w = 0; w < wave; ++w) {
+        wpre += s_wsum[w];
+        gpre += s_gsum[w];
+    }
+    if ((int)threadIdx.x < radix) {
+        s_bstart[threadIdx.x] = wpre + incl - total;
+        s_goff[threadIdx.x] = gpre + gincl - all + earlier;
+    }
     __syncthreads();
 
 #pragma unroll
@@ -199,9 +282,9 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_downsweep(
 // ---------------------------------------------------------------- scan
 
 constexpr int kScanThreads = 256;
-constexpr int kScanSumParts = kBinPairParts;
-constexpr int kScanIpt = 16;
+constexpr int kScanIpt = 8;
 constexpr int kScanTile = kScanThreads * kScanIpt;
+static_assert(kScanTile == kScanTileElems, "tile sums are written by other kernels too");
 
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
     const int lane = threadIdx.x & 63;
@@ -214,83 +297,53 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
 }
 
 // tile sums
-// The scanned value of element i: in[i], or with kFlags, 1 where in[i] != 0.
-template <bool kFlags>
-__device__ __forceinline__ uint32_t scan_value(uint32_t x) {
-    return kFlags ? (x != 0u ? 1u : 0u) : x;
-}
-
-// Tile sums.  With kFlags the raw values are also summed (64-bit) into
-// kScanSumParts counters 16 apart (one atomic address would serialise
-// thousands of workgroups from all XCDs); the counters must start at 0.
-template <bool kFlags>
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ in, uint32_t n_max,
-                                                              const uint32_t* __restrict__ n_dev, uint32_t div,
-                                                              uint32_t mul, uint32_t* __restrict__ tsum,
-                                                              unsigned long long* __restrict__ raw_parts) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ in, uint32_t n,
+                                                              uint32_t* __restrict__ tsum) {
     __shared__ uint32_t s_w[4];
-    __shared__ unsigned long long s_raw[4];
-    const uint32_t n = scaled_count_of(n_max, n_dev, div, mul);
-    // workgroups past the count exit (the first always runs)
-    if (blockIdx.x > 0 && blockIdx.x * (uint32_t)kScanTile >= n) return;
     const uint32_t base = blockIdx.x * kScanTile;
     uint32_t acc = 0;
-    unsigned long long raw = 0;
 #pragma unroll
     for (int r = 0; r < kScanIpt; ++r) {
         const uint32_t idx = base + r * kScanThreads + threadIdx.x;
-        const uint32_t x = idx < n ? in[idx] : 0u;
-        acc += scan_value<kFlags>(x);
-        if (kFlags) raw += x;
+        acc += idx < n ? in[idx] : 0u;
     }
     const uint32_t w = wave_incl_scan(acc);
     if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = w;
-    if (kFlags) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) raw += __shfl_xor(raw, off, 64);
-        if ((threadIdx.x & 63) == 0) s_raw[threadIdx.x >> 6] = raw;
-    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        tsum[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-        if (kFlags) {
-            const unsigned long long b = s_raw[0] + s_raw[1] + s_raw[2] + s_raw[3];
-            if (b) atomicAdd(&raw_parts[16 * (blockIdx.x % kScanSumParts)], b);   // one 128-byte line each
-        }
-    }
+    if (threadIdx.x == 0) tsum[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
 }
 
 // per-tile exclusive scan plus the tile's offset; items are blocked per
-// thread (16 consecutive) so that the in-thread prefix is sequential.  The
+// thread (consecutive) so that the in-thread prefix is sequential.  The
 // tile's offset is the sum of the earlier tiles' sums, which every
 // workgroup adds up itself (64-bit, at most a few thousand values) rather
 // than waiting for a separate one-workgroup launch; the last workgroup
 // that holds elements (the first, for none) writes the 64-bit total.
-template <bool kFlags>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* __restrict__ in,
                                                             uint32_t* __restrict__ out, uint32_t n_max,
-                                                            const uint32_t* __restrict__ n_dev, uint32_t div,
-                                                            uint32_t mul, const uint32_t* __restrict__ tsum,
-                                                            unsigned long long* __restrict__ total) {
+                                                            const uint32_t* __restrict__ n_dev,
+                                                            const uint32_t* __restrict__ tsum,
+                                                            unsigned long long* __restrict__ total,
+                                                            uint32_t* __restrict__ chunk_first, uint32_t chunk) {
     __shared__ uint32_t s_buf[kScanTile];
-    const uint32_t n = scaled_count_of(n_max, n_dev, div, mul);
+    const uint32_t n = count_of(n_max, n_dev);
     const uint32_t n_act = (uint32_t)(((uint64_t)n + kScanTile - 1) / kScanTile);
     const uint32_t last_wg = n_act > 0 ? n_act - 1 : 0;
     if (blockIdx.x > last_wg) return;
     __shared__ uint32_t s_w[4];
     __shared__ unsigned long long s_off[4];
     const uint32_t base = blockIdx.x * kScanTile;
+#pragma unroll
+    for (int r = 0; r < kScanIpt; ++r) {
+        const uint32_t i = r * kScanThreads + threadIdx.x;
+        s_buf[i] = base + i < n ? in[base + i] : 0u;
+    }
     {
         unsigned long long acc = 0;
         for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kScanThreads) acc += tsum[t];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
         if ((threadIdx.x & 63) == 0) s_off[threadIdx.x >> 6] = acc;
-    }
-#pragma unroll
-    for (int r = 0; r < kScanIpt; ++r) {
-        const uint32_t i = r * kScanThreads + threadIdx.x;
-        s_buf[i] = (base + i < n) ? scan_value<kFlags>(in[base + i]) : 0u;
     }
     __syncthreads();
     uint32_t v[kScanIpt];
@@ -304,12 +357,17 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* __re
     if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = incl;
     __syncthreads();
     const unsigned long long tile_off = s_off[0] + s_off[1] + s_off[2] + s_off[3];
-    if (blockIdx.x == last_wg && threadIdx.x == 0) *total = tile_off + tsum[blockIdx.x];
+    if (blockIdx.x == last_wg && threadIdx.x == 0 && total)
+        *total = tile_off + s_w[0] + s_w[1] + s_w[2] + s_w[3];
     uint32_t pre = (uint32_t)tile_off + incl - acc;
     for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) pre += s_w[w];
 #pragma unroll
     for (int r = 0; r < kScanIpt; ++r) {
         s_buf[threadIdx.x * kScanIpt + r] = pre;
+        // the chunks of the counted items that start in this element's
+        if (chunk_first && v[r])
+            for (uint32_t c = (pre + chunk - 1) / chunk; c <= (pre + v[r] - 1) / chunk; ++c)
+                chunk_first[c] = base + threadIdx.x * kScanIpt + r;
         pre += v[r];
     }
     __syncthreads();
@@ -327,19 +385,18 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, size_t n) {
 
 }  // namespace
 
+// the digit table and the row totals
 size_t radix_hist_elems(uint32_t n) {
     // sized for the smallest tile, so that the size grows with n
-    const size_t tiles = (n + kMinSortTile - 1) / kMinSortTile;
-    return (tiles ? tiles : 1) * (size_t)(1 << kMaxRadixBits) + scan_tmp_elems((uint32_t)(tiles * 256));
+    const size_t tiles = ((size_t)n + kMinSortTile - 1) / kMinSortTile;
+    return ((tiles ? tiles : 1) + 1) * (size_t)(1 << kMaxRadixBits);
 }
 
-// tile sums, padded to an even count, then the 64-bit total
-static size_t scan_sums_elems(uint32_t n) {
-    const size_t t = (n + kScanTile - 1) / kScanTile;
-    return ((t ? t : 1) + 1) & ~size_t(1);
+// tile sums
+size_t scan_tmp_elems(uint32_t n) {
+    const size_t t = ((size_t)n + kScanTile - 1) / kScanTile;
+    return t ? t : 1;
 }
-
-size_t scan_tmp_elems(uint32_t n) { return scan_sums_elems(n) + 2; }
 
 hipError_t fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
     if (!n) return hipSuccess;
@@ -350,31 +407,24 @@ hipError_t fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
 }
 
 hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                              unsigned long long* total, hipStream_t s, const uint32_t* n_dev, uint32_t div,
-                              uint32_t mul) {
-    const uint32_t nt = (n + kScanTile - 1) / kScanTile;
+                              unsigned long long* total, hipStream_t s) {
+    const uint32_t nt = (uint32_t)(((uint64_t)n + kScanTile - 1) / kScanTile);
     if (n == 0) {
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t*)total, 0u, (size_t)2);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_scan_reduce<false>, dim3(nt), dim3(kScanThreads), 0, s, in, n, n_dev, div, mul, tmp,
-                       (unsigned long long*)nullptr);
-    hipLaunchKernelGGL(k_scan_down<false>, dim3(nt), dim3(kScanThreads), 0, s, in, out, n, n_dev, div, mul, tmp,
-                       total);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp);
+    hipLaunchKernelGGL(k_scan_down, dim3(nt), dim3(kScanThreads), 0, s, in, out, n, (const uint32_t*)nullptr, tmp,
+                       total, (uint32_t*)nullptr, 1u);
     return hipGetLastError();
 }
 
-hipError_t exclusive_scan_nonzero_u32(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                                      unsigned long long* total, unsigned long long* sum_parts, hipStream_t s) {
-    const uint32_t nt = (n + kScanTile - 1) / kScanTile;
-    if (n == 0) {
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t*)total, 0u, (size_t)2);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_scan_reduce<true>, dim3(nt), dim3(kScanThreads), 0, s, in, n, (const uint32_t*)nullptr, 1u,
-                       1u, tmp, sum_parts);
-    hipLaunchKernelGGL(k_scan_down<true>, dim3(nt), dim3(kScanThreads), 0, s, in, out, n, (const uint32_t*)nullptr,
-                       1u, 1u, tmp, total);
+hipError_t exclusive_scan_sums_u32(const uint32_t* in, uint32_t* out, uint32_t n, const uint32_t* n_dev,
+                                   const uint32_t* tile_sums, uint32_t* chunk_first, uint32_t chunk, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    const uint32_t nt = (uint32_t)(((uint64_t)n + kScanTile - 1) / kScanTile);
+    hipLaunchKernelGGL(k_scan_down, dim3(nt), dim3(kScanThreads), 0, s, in, out, n, n_dev, tile_sums,
+                       (unsigned long long*)nullptr, chunk_first, chunk);
     return hipGetLastError();
 }
 
@@ -387,43 +437,56 @@ int radix_passes(uint32_t n, int begin_bit, int end_bit) {
 // buffers; *result_in_alt says which.  `hist` needs radix_hist_elems(n).
 // With n_dev the key count is read on the device (at most n, which sizes
 // the launches), so the sort needs no host knowledge of it: the digit
-// table and its scan cover only the tiles that hold keys.  small_tiles
-// forces 1024-key tiles (for a device count expected well below n).
+// table and its scan cover only the tiles that hold keys.  small_tiles: a
+// device count expected well below n, 1024-key tiles up to four times the n.
+// vals_are_positions: the input values are 0, 1, 2, ... and `vals` is not
+// read (at least one pass has to run).
 hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, uint32_t n,
                             int begin_bit, int end_bit, uint32_t* hist, hipStream_t s, bool* result_in_alt,
-                            const uint32_t* n_dev, bool small_tiles) {
+                            const uint32_t* n_dev, bool small_tiles, bool vals_are_positions) {
     *result_in_alt = false;
     if (radix_passes(n, begin_bit, end_bit) == 0) return hipSuccess;
     const int total_bits = end_bit - begin_bit;
     const int passes = (total_bits + kMaxRadixBits - 1) / kMaxRadixBits;
-    const bool small = small_tiles || n <= kSmallSortMax;
+    const bool small = n <= (small_tiles ? 4 * kSmallSortMax : kSmallSortMax);
     const uint32_t sort_tile = (uint32_t)kSortThreads * (small ? 4u : 8u);
-    const uint32_t tiles = (n + sort_tile - 1) / sort_tile;
-    const size_t hist_elems = (size_t)tiles * (1 << kMaxRadixBits);
-    uint32_t* scan_tmp = hist + hist_elems;
-    unsigned long long* total = reinterpret_cast<unsigned long long*>(scan_tmp + scan_sums_elems((uint32_t)hist_elems));
+    const uint32_t tiles = (uint32_t)(((uint64_t)n + sort_tile - 1) / sort_tile);
+    const bool few = tiles <= kFewTiles;      // then small as well
+    uint32_t* row_total = hist + (size_t)tiles * (1 << kMaxRadixBits);
     uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
+    bool iota = vals_are_positions;
+    auto rowscan = [&](int bits) {
+        if (tiles < kLongRow)
+            hipLaunchKernelGGL(k_radix_rowscan<256>, dim3(1u << bits), dim3(256), 0, s, hist, n, n_dev, sort_tile,
+                               row_total);
+        else
+            hipLaunchKernelGGL(k_radix_rowscan<1024>, dim3(1u << bits), dim3(1024), 0, s, hist, n, n_dev, sort_tile,
+                               row_total);
+    };
     int shift = begin_bit;
     for (int p = 0; p < passes; ++p) {
         const int remaining = end_bit - shift;
         const int bits = (remaining + (passes - p) - 1) / (passes - p);
-        const uint32_t radix_elems = (uint32_t)tiles << bits;
-        if (small)
-            hipLaunchKernelGGL(k_radix_upsweep<4>, dim3(tiles), dim3(kSortThreads), 0, s, ki, n, n_dev, shift, bits,
-                               hist, tiles);
-        else
-            hipLaunchKernelGGL(k_radix_upsweep<8>, dim3(tiles), dim3(kSortThreads), 0, s, ki, n, n_dev, shift, bits,
-                               hist, tiles);
-        hipError_t e = exclusive_scan_u32(hist, hist, radix_elems, scan_tmp, total, s, n_dev, sort_tile, 1u << bits);
+        const dim3 grid(tiles), wg(kSortThreads);
+        const uint32_t* v = iota ? nullptr : vi;
+        if (few) {
+            hipLaunchKernelGGL((k_radix_upsweep<4, true>), grid, wg, 0, s, ki, n, n_dev, shift, bits, hist);
+            hipLaunchKernelGGL((k_radix_downsweep<4, true>), grid, wg, 0, s, ki, v, ko, vo, n, n_dev, shift, bits,
+                               hist, row_total);
+        } else if (small) {
+            hipLaunchKernelGGL((k_radix_upsweep<4, false>), grid, wg, 0, s, ki, n, n_dev, shift, bits, hist);
+            rowscan(bits);
+            hipLaunchKernelGGL((k_radix_downsweep<4, false>), grid, wg, 0, s, ki, v, ko, vo, n, n_dev, shift, bits,
+                               hist, row_total);
+        } else {
+            hipLaunchKernelGGL((k_radix_upsweep<8, false>), grid, wg, 0, s, ki, n, n_dev, shift, bits, hist);
+            rowscan(bits);
+            hipLaunchKernelGGL((k_radix_downsweep<8, false>), grid, wg, 0, s, ki, v, ko, vo, n, n_dev, shift, bits,
+                               hist, row_total);
+        }
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (small)
-            hipLaunchKernelGGL(k_radix_downsweep<4>, dim3(tiles), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n, n_dev,
-                               shift, bits, hist, tiles);
-        else
-            hipLaunchKernelGGL(k_radix_downsweep<8>, dim3(tiles), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n, n_dev,
-                               shift, bits, hist, tiles);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        iota = false;
         shift += bits;
         uint32_t* t;
         t = ki; ki = ko; ko = t;
