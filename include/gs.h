@@ -271,7 +271,7 @@ int gs_project_bwd(const gs_gaussians *g, const gs_camera *cams, int32_t n_views
                    float *mean2d_grad_norm, float *absgrad, int32_t grads_zeroed, void *stream);
 /* Zeroes the parameter-gradient arrays of n Gaussians (d_app too when not
  * NULL), device pointers as in gs_gaussians_grad, with launches of at most
- * 64 workgroups each.  With it, gs_project_bwd's grads_zeroed = 1 writes
+ * 128 workgroups each.  With it, gs_project_bwd's grads_zeroed = 1 writes
  * only the rows of Gaussians some view sees (the others are 84 % of the
  * rows of a large street-level scene): enqueued on a second stream after
  * gs_composite_bwd, which is bound by instruction issue and leaves most of
