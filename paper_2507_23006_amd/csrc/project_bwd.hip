@@ -1,27 +1,28 @@
 // Backward of projection and colour -- gfx950.
 //
-// A workgroup owns a span of 1024 consecutive Gaussians.  It first finds
-// which of them some view sees (tiles > 0), writes the per-view statistics
-// and the zero colour-coefficient rows of the others with coalesced stores,
-// and packs the seen ones into an LDS list; then one thread per listed
-// Gaussian reads its parameters once, recomputes the projection in FP64 for
-// each view that sees it, chains that view's 2D gradients (mean2d, conic,
-// opacity', colour, depth) back to the parameters, and writes the sums once:
-// the coefficient rows directly, the one-float-per-Gaussian rows (means,
-// scales, quats, opacity, appearance) into LDS rows of the span that start
-// at zero and are streamed out whole at the end, so every cache line of
-// those arrays is written once and completely instead of in two partial
-// halves (zeros, then the seen Gaussians' values).  When the outputs were
-// zeroed beforehand (k_zero_floats on a second stream beside the
-// compositing backward), the chain writes the seen Gaussians' entries
-// directly and the unseen ones are left alone.  Only a small fraction of a
-// large scene is in view, so the compaction keeps the FP64 chain on full
-// waves and the parameter reads on the Gaussians that need them; 2D
-// gradients of unseen slots are never read.  With
+// Each workgroup is one wave that scans chunks of 256 consecutive Gaussians:
+// it writes the zeros and statistics of those no view sees and packs the
+// others into an LDS list.  Whenever the list holds 64 (384 with several
+// views, grouped by the views that see them), the wave runs the chain, one
+// lane per listed Gaussian: it reads the parameters once, recomputes the
+// projection in FP64 for each view that sees the Gaussian, chains that view's
+// 2D gradients (mean2d, conic, opacity', colour, depth) back to the
+// parameters, and writes the sums once.  Only a small fraction of a large
+// scene is in view, so the list keeps the chain on full waves, and without
+// barriers one wave's reads run beside another's arithmetic.  When the
+// outputs were zeroed beforehand (k_zero_floats on a second stream beside the
+// compositing backward), the unseen rows are left alone.  2D gradients of
+// unseen slots are never read.  With
 // Sigma_2D = V V^T and V = (J W) M, M = R(q) diag(s), the covariance
 // gradient flows as dV = 2 G V, d(JW) = dV M^T, dM += (JW)^T dV; dM is
 // accumulated over views and pushed through R(q) and s once at the end.
 // HBM-bound; geometry in FP64 for the same reason as the forward.
+//
+// Measured (workgroups of 256 threads over spans of 1024 before, one wave
+// now): 1M Gaussians, most of them seen, one view: 175 -> 119 us, 4.6 TB/s of
+// the 0.55 GB that rows and parameters hold; 4096: 34 -> 7 us; 12M in eight
+// views 6570 -> 2860 us; 6M with 16 % seen 310 -> 292 us, where 128-byte lines
+// of which one or two Gaussians are wanted make 1.1 GB of the traffic.
 //
 // Paper: backward of Eq. 1 and of the projection of §3.1; the per-view
 // |dL/d mean2d| is the image-space statistic that densification thresholds
@@ -64,69 +65,249 @@ __device__ __forceinline__ void sh_basis_grad(float x, float y, float z, int k, 
 typedef float F4 __attribute__((ext_vector_type(4)));
 
 constexpr int kG2 = GS_GRAD2D_FLOATS;
-constexpr int kPB = 256;                  // threads per workgroup
-constexpr int kSpanPer = 4;               // Gaussians per thread in the scan
-constexpr int kSpan = kPB * kSpanPer;     // Gaussians per workgroup
+constexpr int kChunkPer = 4;               // Gaussians per lane in the scan of a chunk
+constexpr int kMaxWaves = 2048;            // two per SIMD, what the chain's registers allow
+// listed Gaussians from which a wave runs the chain: one batch, or with
+// several views enough for batches seen by the same views
+__host__ __device__ constexpr uint32_t fill_of(bool multi) { return multi ? 384u : 64u; }
 
-// gradient rows staged in LDS per workgroup span: means (3), scales (3),
-// quats (4), opacity (1), appearance offsets (4)
-constexpr int kStageRows = 15;
-constexpr int kStageApp = 11;
+constexpr int kRowApp = 11;
 
-// Destinations of a seen Gaussian's one-float gradients, by row c (means
-// 0-2, scales 3-5, quats 6-9, opacity 10, appearance offsets 11-14): the
-// span's LDS rows, or the output arrays themselves
-struct StageRows {
-    float* s;
-    int loc;
-    __device__ void put(int c, float v) const { s[c * kSpan + loc] = v; }
+// row c of the one-float gradients (means 0-2, scales 3-5, quats 6-9,
+// opacity 10, appearance offsets 11-14) of Gaussian g
+__device__ __forceinline__ float* grad_row(const GradPtrs& out, int64_t n, int64_t g, int c) {
+    return c < 3 ? out.means + c * n + g : c < 6 ? out.scales + (c - 3) * n + g
+         : c < 10 ? out.quats + (c - 6) * n + g : c == 10 ? out.opac + g : out.app + 4 * g + (c - kRowApp);
+}
+
+// Parameters of one Gaussian as stored, but for the coefficient row; app holds
+// the appearance offsets (or the polynomial's constant and 0)
+struct GaussIn {
+    float mu[3], s[3], q[4], o;
+    float4 app;
 };
-struct OutRows {
-    const GradPtrs& out;
-    int64_t n, g;
-    __device__ void put(int c, float v) const {
-        float* p = c < 3 ? out.means + c * n + g : c < 6 ? out.scales + (c - 3) * n + g
-                 : c < 10 ? out.quats + (c - 6) * n + g : c == 10 ? out.opac + g : out.app + 4 * g + (c - kStageApp);
-        __builtin_nontemporal_store(v, p);
+
+__device__ __forceinline__ GaussIn load_gauss(const GaussPtrs& gp, int64_t n, int64_t g) {
+    GaussIn in;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) in.mu[c] = gp.means[c * n + g];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) in.s[c] = gp.scales[c * n + g];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) in.q[c] = gp.quats[c * n + g];
+    in.o = gp.opac[g];
+    in.app = gp.app ? reinterpret_cast<const float4*>(gp.app)[g] : make_float4(0.5f, 0.5f, 0.5f, 0.0f);
+    return in;
+}
+
+// orders a wave's LDS accesses before and after it
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wave's 64 coefficient rows (192 bytes each) between memory and LDS.  A lane
+// reading its own row touches two cache lines with each of its twelve 16-byte
+// loads, 16 KB of lines per instruction and wave, which the compute unit's L1
+// does not hold until the next piece is read; here twelve neighbouring lanes
+// move a row's pieces.  Rows lie 13 pieces apart in LDS, so that a piece of all
+// rows spreads over all banks.
+constexpr int kRowF4 = 13;
+constexpr int kWaveRows = 64 * kRowF4;     // float4s of LDS per wave
+
+struct RowLanes {
+    int rc[3], qc[3];      // row (of 16) and piece that the lane moves in step c of three
+    __device__ explicit RowLanes(int lane) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            rc[c] = (64 * c + lane) / 12;
+            qc[c] = 64 * c + lane - 12 * rc[c];
+        }
     }
 };
 
-// full chain for one seen Gaussian g; vis = mask of the views that see it.
-// Writes its SH coefficient gradients to out.sh and the other gradients to
-// `rows`.
-template <class Rows>
-__device__ __forceinline__ void project_bwd_one(const GaussPtrs& gp, int64_t n, const ViewTable& vt,
-                                                const OptK& opt, const float* __restrict__ grad2d,
-                                                const GradPtrs& out, int64_t g, uint32_t vis, const Rows& rows) {
-    const int nb = (opt.sh_degree + 1) * (opt.sh_degree + 1);
-    const int nq = (3 * nb + 3) >> 2;    // float4s of a coefficient row in use
-    const float4* shq = reinterpret_cast<const float4*>(gp.sh) + 12 * g;
-    float4* dshq = reinterpret_cast<float4*>(out.sh) + 12 * g;
-    const double mu0 = gp.means[g], mu1 = gp.means[n + g], mu2 = gp.means[2 * n + g];
-    const double s0 = gp.scales[g], s1 = gp.scales[n + g], s2 = gp.scales[2 * n + g];
-    const double q0 = gp.quats[g], q1 = gp.quats[n + g], q2 = gp.quats[2 * n + g], q3 = gp.quats[3 * n + g];
-    const double qn = sqrt(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
-    const double w = q0 / qn, x = q1 / qn, y = q2 / qn, z = q3 / qn;
-    double M[9];   // R(q) diag(s)
-    M[0] = (1.0 - 2.0 * (y * y + z * z)) * s0; M[1] = 2.0 * (x * y - w * z) * s1; M[2] = 2.0 * (x * z + w * y) * s2;
-    M[3] = 2.0 * (x * y + w * z) * s0; M[4] = (1.0 - 2.0 * (x * x + z * z)) * s1; M[5] = 2.0 * (y * z - w * x) * s2;
-    M[6] = 2.0 * (x * z - w * y) * s0; M[7] = 2.0 * (y * z + w * x) * s1; M[8] = (1.0 - 2.0 * (x * x + y * y)) * s2;
-    // appearance offsets: colour constant dc (else 1/2), opacity o (1 - do)
-    const float4 app = gp.app ? reinterpret_cast<const float4*>(gp.app)[g] : make_float4(0.5f, 0.5f, 0.5f, 0.0f);
-    const double o_raw = gp.opac[g];
-    const double o = o_raw * (gp.app ? 1.0 - (double)app.w : 1.0);
-    float dcb0 = 0.0f, dcb1 = 0.0f, dcb2 = 0.0f;
+// rows of the Gaussians g (one per lane) into s
+__device__ __forceinline__ void load_rows(const float* __restrict__ sh, uint32_t g, int nq,
+                                          const RowLanes& rl, F4* s) {
+    const F4* src = reinterpret_cast<const F4*>(sh);
+    F4 piece[12];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+        const uint32_t r = __shfl(g, 16 * (i / 3) + rl.rc[i % 3]);
+        piece[i] = rl.qc[i % 3] < nq ? src[(int64_t)12 * r + rl.qc[i % 3]] : F4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int i = 0; i < 12; ++i) s[(16 * (i / 3) + rl.rc[i % 3]) * kRowF4 + rl.qc[i % 3]] = piece[i];
+    wave_sync();
+}
 
-    double dmu[3] = {0.0, 0.0, 0.0};
+// the first m rows of s to those of their Gaussians
+__device__ __forceinline__ void store_rows(float* __restrict__ sh, uint32_t g, int m, const RowLanes& rl,
+                                           const F4* s) {
+    F4* dst = reinterpret_cast<F4*>(sh);
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+        const int r = 16 * (i / 3) + rl.rc[i % 3];
+        const uint32_t to = __shfl(g, r);
+        if (r < m) __builtin_nontemporal_store(s[r * kRowF4 + rl.qc[i % 3]], dst + (int64_t)12 * to + rl.qc[i % 3]);
+    }
+    wave_sync();
+}
+
+// band L of the polynomial: its part of the colour and of S_c = sum_k sh_kc
+// grad Y_k
+template <int L>
+__device__ __forceinline__ void band_colour(const float r[48], const float Y[16], float x, float y, float z,
+                                            float raw[3], float S[3][3]) {
+#pragma unroll
+    for (int k = L * L; k < (L + 1) * (L + 1); ++k) {
+        float bx, by, bz;
+        sh_basis_grad(x, y, z, k, bx, by, bz);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            raw[c] = fmaf(r[3 * k + c], Y[k], raw[c]);
+            if (L > 0) {
+                S[c][0] = fmaf(r[3 * k + c], bx, S[c][0]);
+                S[c][1] = fmaf(r[3 * k + c], by, S[c][1]);
+                S[c][2] = fmaf(r[3 * k + c], bz, S[c][2]);
+            }
+        }
+    }
+}
+
+// d sh_kc += gr_c Y_k for band L
+template <int L>
+__device__ __forceinline__ void band_grad(const float gr[3], const float Y[16], float d[48]) {
+#pragma unroll
+    for (int k = L * L; k < (L + 1) * (L + 1); ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[3 * k + c] += gr[c] * Y[k];
+}
+
+// Colour chain of one seen Gaussian; vis = mask of the views that see it, g2
+// = its 2D gradients in view 0 (those of the next view g2_stride floats on):
+// replaces its coefficient row in LDS by the row's gradients, and returns its
+// part of the mean's gradient (through the view direction) in dmu and of the
+// colour constant's in dcb.  The row stays in LDS and the sum of its gradients
+// in registers over the views, so each row is read and written once: adding
+// to the row in memory view by view read 17 and wrote 7 GB per step of 12M
+// Gaussians in eight views.
+template <bool kMulti>
+__device__ __forceinline__ void colour_bwd_one(const GaussIn& in, const ViewTable& vt, const OptK& opt,
+                                               const float* __restrict__ grad2d, int64_t g2_stride, uint32_t vis,
+                                               F4* __restrict__ row, double dmu[3], float dcb[3]) {
+    const double mu0 = in.mu[0], mu1 = in.mu[1], mu2 = in.mu[2];
+    float d[48];
+#pragma unroll
+    for (int k = 0; k < 48; ++k) d[k] = 0.0f;
+    const int n_views = kMulti ? vt.n_views : 1;
+    int v0 = 0;      // opaque: the views' constants are read here, not held in registers from batch to batch
+    asm volatile("" : "+s"(v0));
+    for (int v = 0; v < n_views; ++v) {
+        if (kMulti && !(vis & (1u << v))) continue;
+        const ViewK& V = vt.v[v + v0];
+        const float* g2 = grad2d + v * g2_stride;
+        const float gc[3] = {g2[6], g2[7], g2[8]};
+        const double e0d = mu0 - V.campos[0], e1d = mu1 - V.campos[1], e2d = mu2 - V.campos[2];
+        const double dn = sqrt(e0d * e0d + e1d * e1d + e2d * e2d);
+        const double inv = 1.0 / dn;
+        const float d0 = (float)(e0d * inv), d1 = (float)(e1d * inv), d2 = (float)(e2d * inv);
+        float Y[16];
+        sh_eval_basis<float>(d0, d1, d2, opt.sh_degree, Y);
+        // colour: raw = sum_k sh_k Y_k(dhat) + dc, clamped at 0 (SH in FP32).
+        // One pass over the coefficient row gives the colour and, per
+        // channel c, S_c = sum_k sh_kc grad Y_k, so that the direction
+        // gradient is sum_c gr_c S_c (coefficient e of the row is channel
+        // e % 3 of basis e / 3)
+        float raw[3] = {in.app.x, in.app.y, in.app.z};
+        float S[3][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+        float r[48];
+#pragma unroll
+        for (int q = 0; q < 12; ++q) {
+            const F4 t = row[q];
+            r[4 * q + 0] = t.x; r[4 * q + 1] = t.y; r[4 * q + 2] = t.z; r[4 * q + 3] = t.w;
+        }
+        // band by band, so that a degree is one branch
+        const int deg = opt.sh_degree;
+        band_colour<0>(r, Y, d0, d1, d2, raw, S);
+        if (deg > 0) band_colour<1>(r, Y, d0, d1, d2, raw, S);
+        if (deg > 1) band_colour<2>(r, Y, d0, d1, d2, raw, S);
+        if (deg > 2) band_colour<3>(r, Y, d0, d1, d2, raw, S);
+        const float gr[3] = {raw[0] < 0.0f ? 0.0f : gc[0], raw[1] < 0.0f ? 0.0f : gc[1], raw[2] < 0.0f ? 0.0f : gc[2]};
+        dcb[0] += gr[0]; dcb[1] += gr[1]; dcb[2] += gr[2];
+        const float e0 = gr[0] * S[0][0] + gr[1] * S[1][0] + gr[2] * S[2][0];
+        const float e1 = gr[0] * S[0][1] + gr[1] * S[1][1] + gr[2] * S[2][1];
+        const float e2 = gr[0] * S[0][2] + gr[1] * S[1][2] + gr[2] * S[2][2];
+        // d sh_kc = gr_c Y_k, summed over the views
+        band_grad<0>(gr, Y, d);
+        if (deg > 0) band_grad<1>(gr, Y, d);
+        if (deg > 1) band_grad<2>(gr, Y, d);
+        if (deg > 2) band_grad<3>(gr, Y, d);
+        const double dd = (double)e0 * d0 + (double)e1 * d1 + (double)e2 * d2;
+        dmu[0] += ((double)e0 - d0 * dd) * inv;
+        dmu[1] += ((double)e1 - d1 * dd) * inv;
+        dmu[2] += ((double)e2 - d2 * dd) * inv;
+    }
+#pragma unroll
+    for (int q = 0; q < 12; ++q) row[q] = F4{d[4 * q + 0], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]};
+}
+
+struct Rotation {      // unit quaternion and 1 / |q|
+    double w, x, y, z, inv;
+    __device__ explicit Rotation(const float q[4]) {
+        const double q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+        inv = 1.0 / sqrt(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
+        w = q0 * inv; x = q1 * inv; y = q2 * inv; z = q3 * inv;
+    }
+};
+
+// Geometry chain of one seen Gaussian; dmu and dcb hold the colour chain's
+// sums.  Writes every gradient but the coefficients', and the per-view
+// statistics of the views that see it.
+template <bool kZeroed, bool kMulti>
+__device__ __forceinline__ void geometry_bwd_one(const GaussIn& in, bool has_app, const ViewTable& vt, const OptK& opt,
+                                                 const float* __restrict__ grad2d, int64_t g2_stride, uint32_t vis,
+                                                 double dmu[3], const float dcb[3], const GradPtrs& out, int64_t n,
+                                                 int64_t g, float* __restrict__ mean2d_norm,
+                                                 float* __restrict__ absgrad) {
+    const double mu0 = in.mu[0], mu1 = in.mu[1], mu2 = in.mu[2];
+    double M[9];   // R(q) diag(s)
+    {
+        const Rotation R(in.q);
+        const double s0 = in.s[0], s1 = in.s[1], s2 = in.s[2];
+        M[0] = (1.0 - 2.0 * (R.y * R.y + R.z * R.z)) * s0;
+        M[1] = 2.0 * (R.x * R.y - R.w * R.z) * s1;
+        M[2] = 2.0 * (R.x * R.z + R.w * R.y) * s2;
+        M[3] = 2.0 * (R.x * R.y + R.w * R.z) * s0;
+        M[4] = (1.0 - 2.0 * (R.x * R.x + R.z * R.z)) * s1;
+        M[5] = 2.0 * (R.y * R.z - R.w * R.x) * s2;
+        M[6] = 2.0 * (R.x * R.z - R.w * R.y) * s0;
+        M[7] = 2.0 * (R.y * R.z + R.w * R.x) * s1;
+        M[8] = (1.0 - 2.0 * (R.x * R.x + R.y * R.y)) * s2;
+    }
+    // appearance offsets: opacity o (1 - do)
+    const double o = has_app ? (double)in.o * (1.0 - (double)in.app.w) : (double)in.o;
+
     double dM[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     double dop = 0.0;
-    bool first = true;    // the first visible view writes d_sh, later ones add to it
 
-    for (int v = 0; v < vt.n_views; ++v) {
-        if (!(vis & (1u << v))) continue;
-        const ViewK& V = vt.v[v];
-        const int64_t slot = (int64_t)v * n + g;
-        const float* g2 = grad2d + slot * kG2;
+    const int n_views = kMulti ? vt.n_views : 1;
+    int v0 = 0;      // opaque: the views' constants are read here, not held in registers from batch to batch
+    asm volatile("" : "+s"(v0));
+    for (int v = 0; v < n_views; ++v) {
+        if (kMulti && !(vis & (1u << v))) continue;
+        const ViewK& V = vt.v[v + v0];
+        const float* g2 = grad2d + v * g2_stride;
+        if (kMulti) {
+            const int64_t slot = v * n + g;
+            mean2d_norm[slot] = sqrtf(g2[0] * g2[0] + g2[1] * g2[1]);
+            if (absgrad) {
+                absgrad[2 * slot] = g2[10];
+                absgrad[2 * slot + 1] = g2[11];
+            }
+        }
         const double gmx = g2[0], gmy = g2[1], gA = g2[2], gB = g2[3], gC = g2[4], gop = g2[5];
         const double gz = g2[9];
         float W[9];
@@ -137,75 +318,12 @@ __device__ __forceinline__ void project_bwd_one(const GaussPtrs& gp, int64_t n, 
         const double tz = W[6] * mu0 + W[7] * mu1 + W[8] * mu2 + (double)V.t[2];
         const double fx = V.fx, fy = V.fy;
 
-        // ---- colour: raw = sum_k sh_k Y_k(dhat) + dc, clamped at 0 (SH in FP32)
-        {
-            const double e0d = mu0 - V.campos[0], e1d = mu1 - V.campos[1], e2d = mu2 - V.campos[2];
-            const double dn = sqrt(e0d * e0d + e1d * e1d + e2d * e2d);
-            const double inv = 1.0 / dn;
-            const float d0 = (float)(e0d * inv), d1 = (float)(e1d * inv), d2 = (float)(e2d * inv);
-            float Y[16];
-            sh_eval_basis<float>(d0, d1, d2, opt.sh_degree, Y);
-            // one pass over the coefficient row gives the colour and, per
-            // channel c, S_c = sum_k sh_kc grad Y_k, so that the direction
-            // gradient is sum_c gr_c S_c and the row is not held in registers
-            // (coefficient e of the row is channel e % 3 of basis e / 3)
-            float raw[3] = {app.x, app.y, app.z};
-            float S[3][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-#pragma unroll
-            for (int q = 0; q < 12; ++q) {
-                if (q < nq) {
-                    const float4 t = shq[q];
-                    const float tv[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int k = (4 * q + j) / 3, c = (4 * q + j) % 3;
-                        if (k < nb) {
-                            raw[c] = fmaf(tv[j], Y[k], raw[c]);
-                            if (k > 0) {
-                                float bx, by, bz;
-                                sh_basis_grad(d0, d1, d2, k, bx, by, bz);
-                                S[c][0] = fmaf(tv[j], bx, S[c][0]);
-                                S[c][1] = fmaf(tv[j], by, S[c][1]);
-                                S[c][2] = fmaf(tv[j], bz, S[c][2]);
-                            }
-                        }
-                    }
-                }
-            }
-            const float gr[3] = {raw[0] < 0.0f ? 0.0f : g2[6], raw[1] < 0.0f ? 0.0f : g2[7],
-                                 raw[2] < 0.0f ? 0.0f : g2[8]};
-            dcb0 += gr[0]; dcb1 += gr[1]; dcb2 += gr[2];
-            const float e0 = gr[0] * S[0][0] + gr[1] * S[1][0] + gr[2] * S[2][0];
-            const float e1 = gr[0] * S[0][1] + gr[1] * S[1][1] + gr[2] * S[2][1];
-            const float e2 = gr[0] * S[0][2] + gr[1] * S[1][2] + gr[2] * S[2][2];
-            // d sh_kc = gr_c Y_k, added to the earlier views' sums
-#pragma unroll
-            for (int q = 0; q < 12; ++q) {
-                float d[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = (4 * q + j) / 3, c = (4 * q + j) % 3;
-                    d[j] = k < nb ? gr[c] * Y[k] : 0.0f;
-                }
-                float4 t = make_float4(d[0], d[1], d[2], d[3]);
-                if (!first && q < nq) {
-                    const float4 p = dshq[q];
-                    t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
-                }
-                if (first || q < nq) dshq[q] = t;
-            }
-            first = false;
-            const double dd = (double)e0 * d0 + (double)e1 * d1 + (double)e2 * d2;
-            dmu[0] += ((double)e0 - d0 * dd) * inv;
-            dmu[1] += ((double)e1 - d1 * dd) * inv;
-            dmu[2] += ((double)e2 - d2 * dd) * inv;
-        }
-
-        // ---- geometry, recomputed as in the forward
-        const double u = tx / tz, vv = ty / tz;
+        // recomputed as in the forward, but with 1 / tz once
+        const double itz = 1.0 / tz, itz2 = itz * itz;
+        const double u = tx * itz, vv = ty * itz;
         const bool ucl = u < V.ulo || u > V.uhi, vcl = vv < V.vlo || vv > V.vhi;
         const double uc = fmin(fmax(u, V.ulo), V.uhi), vc = fmin(fmax(vv, V.vlo), V.vhi);
-        const double j00 = fx / tz, j02 = -fx * uc / tz, j11 = fy / tz, j12 = -fy * vc / tz;
+        const double j00 = fx * itz, j02 = -j00 * uc, j11 = fy * itz, j12 = -j11 * vc;
         double Tm[6];
         Tm[0] = j00 * W[0] + j02 * W[6]; Tm[1] = j00 * W[1] + j02 * W[7]; Tm[2] = j00 * W[2] + j02 * W[8];
         Tm[3] = j11 * W[3] + j12 * W[6]; Tm[4] = j11 * W[4] + j12 * W[7]; Tm[5] = j11 * W[5] + j12 * W[8];
@@ -228,10 +346,10 @@ __device__ __forceinline__ void project_bwd_one(const GaussPtrs& gp, int64_t n, 
 
         double dt0 = 0.0, dt1 = 0.0, dt2 = 0.0;
         // mean2d = (fx tx/tz + cx, fy ty/tz + cy), depth = tz
-        dt0 += gmx * fx / tz;
-        dt2 -= gmx * fx * tx / (tz * tz);
-        dt1 += gmy * fy / tz;
-        dt2 -= gmy * fy * ty / (tz * tz);
+        dt0 += gmx * j00;
+        dt2 -= gmx * j00 * u;
+        dt1 += gmy * j11;
+        dt2 -= gmy * j11 * vv;
         dt2 += gz;
         // conic = inverse of [[ad, cb], [cb, cd]]
         double ga = gA * (-A * A) + gB * (-A * B) + gC * (-B * B);
@@ -264,19 +382,19 @@ __device__ __forceinline__ void project_bwd_one(const GaussPtrs& gp, int64_t n, 
         const double dJ02 = dTm[0] * W[6] + dTm[1] * W[7] + dTm[2] * W[8];
         const double dJ11 = dTm[3] * W[3] + dTm[4] * W[4] + dTm[5] * W[5];
         const double dJ12 = dTm[3] * W[6] + dTm[4] * W[7] + dTm[5] * W[8];
-        const double tz2 = tz * tz;
-        dt2 += dJ00 * (-fx / tz2) + dJ11 * (-fy / tz2);
+        const double fxz2 = fx * itz2, fyz2 = fy * itz2;
+        dt2 -= dJ00 * fxz2 + dJ11 * fyz2;
         if (!ucl) {
-            dt0 += dJ02 * (-fx / tz2);
-            dt2 += dJ02 * (2.0 * fx * tx / (tz2 * tz));
+            dt0 -= dJ02 * fxz2;
+            dt2 += dJ02 * (2.0 * fxz2 * u);
         } else {
-            dt2 += dJ02 * (fx * uc / tz2);
+            dt2 += dJ02 * (fxz2 * uc);
         }
         if (!vcl) {
-            dt1 += dJ12 * (-fy / tz2);
-            dt2 += dJ12 * (2.0 * fy * ty / (tz2 * tz));
+            dt1 -= dJ12 * fyz2;
+            dt2 += dJ12 * (2.0 * fyz2 * vv);
         } else {
-            dt2 += dJ12 * (fy * vc / tz2);
+            dt2 += dJ12 * (fyz2 * vc);
         }
         // t = W mu + t_w
         dmu[0] += W[0] * dt0 + W[3] * dt1 + W[6] * dt2;
@@ -284,14 +402,31 @@ __device__ __forceinline__ void project_bwd_one(const GaussPtrs& gp, int64_t n, 
         dmu[2] += W[2] * dt0 + W[5] * dt1 + W[8] * dt2;
     }
 
+    // (opaque copies, so that the quaternion's and the scales' doubles are
+    // computed again here and not held over the views)
+    float qf[4], sf[3];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        qf[c] = in.q[c];
+        asm volatile("" : "+v"(qf[c]));
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        sf[c] = in.s[c];
+        asm volatile("" : "+v"(sf[c]));
+    }
+    const Rotation R(qf);
+    const double w = R.w, x = R.x, y = R.y, z = R.z, iqn = R.inv;
     // M = R(q) diag(s): ds_c = sum_r dM[r][c] R[r][c], dR[r][c] = dM[r][c] s_c
-    const double sc[3] = {s0, s1, s2};
+    const double sc[3] = {sf[0], sf[1], sf[2]};
     double dR[9], ds[3] = {0.0, 0.0, 0.0};
-    for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) {
-            ds[c] += dM[3 * r + c] * M[3 * r + c] / sc[c];
+    for (int c = 0; c < 3; ++c) {
+        for (int r = 0; r < 3; ++r) {
+            ds[c] += dM[3 * r + c] * M[3 * r + c];
             dR[3 * r + c] = dM[3 * r + c] * sc[c];
         }
+        ds[c] /= sc[c];
+    }
     // rotation of the unit quaternion (w, x, y, z)
     double dq[4];
     dq[0] = 2.0 * (-z * dR[1] + y * dR[2] + z * dR[3] - x * dR[5] - y * dR[6] + x * dR[7]);
@@ -301,119 +436,175 @@ __device__ __forceinline__ void project_bwd_one(const GaussPtrs& gp, int64_t n, 
     // normalisation q / |q|
     const double dot = dq[0] * w + dq[1] * x + dq[2] * y + dq[3] * z;
     const double qh[4] = {w, x, y, z};
-    for (int c = 0; c < 3; ++c) rows.put(c, (float)dmu[c]);
-    for (int c = 0; c < 3; ++c) rows.put(3 + c, (float)ds[c]);
-    for (int c = 0; c < 4; ++c) rows.put(6 + c, (float)((dq[c] - qh[c] * dot) / qn));
+    const auto put = [&](int c, float v) {
+        float* p = grad_row(out, n, g, c);
+        // plain stores meet in L2: with the zeros that the scan wrote to the
+        // line, or, with several views, with those of other batches
+        if (kZeroed && !kMulti) __builtin_nontemporal_store(v, p);
+        else *p = v;
+    };
+    for (int c = 0; c < 3; ++c) put(c, (float)dmu[c]);
+    for (int c = 0; c < 3; ++c) put(3 + c, (float)ds[c]);
+    for (int c = 0; c < 4; ++c) put(6 + c, (float)((dq[c] - qh[c] * dot) * iqn));
     // dop is the gradient with respect to o (1 - do)
-    rows.put(10, (float)(gp.app ? dop * (1.0 - (double)app.w) : dop));
+    put(10, (float)(has_app ? dop * (1.0 - (double)in.app.w) : dop));
     if (out.app) {
-        rows.put(kStageApp + 0, dcb0);
-        rows.put(kStageApp + 1, dcb1);
-        rows.put(kStageApp + 2, dcb2);
-        rows.put(kStageApp + 3, (float)(-dop * o_raw));
+        put(kRowApp + 0, dcb[0]);
+        put(kRowApp + 1, dcb[1]);
+        put(kRowApp + 2, dcb[2]);
+        put(kRowApp + 3, (float)(-dop * (double)in.o));
     }
 }
 
 
 // kZeroed: the gradient outputs already hold zeros (gs_grads_zero, run
 // beside the compositing backward), so only the entries of Gaussians some
-// view sees are written, straight from the chain (scattered either way):
-// no LDS rows, so more workgroups fit on a compute unit
-template <bool kZeroed>
-__global__ __launch_bounds__(kPB) void k_project_bwd(GaussPtrs gp, int64_t n, ViewTable vt, OptK opt,
-                                                     Projected proj, const float* __restrict__ grad2d, GradPtrs out,
-                                                     float* __restrict__ mean2d_norm, float* __restrict__ absgrad) {
-    __shared__ uint32_t s_list[kSpan];     // local index | view mask << 16
-    __shared__ uint32_t s_group[kSpan];    // the list grouped by view mask (several views)
-    __shared__ uint32_t s_hist[256];
-    __shared__ uint8_t s_seen[kSpan];
-    __shared__ uint32_t s_count;
-    // the span's gradient rows: zeros, then the chain's values, then one
-    // coalesced write of every row (each cache line written once, whole)
-    __shared__ float s_grad[kZeroed ? 1 : kStageRows * kSpan];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int64_t g0 = (int64_t)blockIdx.x * kSpan;
-    if (tid == 0) s_count = 0;
-    __syncthreads();
-
-    // pass 1: statistics, visibility, zeroed LDS rows, compaction
-    for (int i = 0; i < kSpanPer; ++i) {
-        const int loc = i * kPB + tid;
-        const int64_t g = g0 + loc;
-        uint32_t vis = 0;
-        if (g < n) {
-            for (int v = 0; v < vt.n_views; ++v) {
-                const int64_t slot = (int64_t)v * n + g;
-                const bool seen = proj.tiles[slot] != 0;
-                float nrm = 0.0f, ax = 0.0f, ay = 0.0f;
-                if (seen) {
-                    const float* g2 = grad2d + slot * kG2;
-                    const float dmx = g2[0], dmy = g2[1];
-                    nrm = sqrtf(dmx * dmx + dmy * dmy);
-                    ax = g2[10];
-                    ay = g2[11];
-                    vis |= 1u << v;
+// view sees are written.  One wave per workgroup; chunk k of the wave is
+// chunk blockIdx.x + k gridDim.x of 64 * per Gaussians (per <= kChunkPer, at
+// most 256 chunks per wave).
+template <bool kZeroed, bool kMulti>
+__global__ __launch_bounds__(64, 2) void k_project_bwd(GaussPtrs gp, uint32_t n, ViewTable vt, OptK opt, Projected proj,
+                                                       const float* __restrict__ grad2d, GradPtrs out,
+                                                       float* __restrict__ mean2d_norm, float* __restrict__ absgrad,
+                                                       int per) {
+    constexpr uint32_t kFill = fill_of(kMulti), kCap = kFill + 64 * kChunkPer;
+    __shared__ uint32_t s_list[kCap];      // index in the chunk | chunk of the wave << 8 | view mask << 16
+    __shared__ uint32_t s_group[kMulti ? kCap : 1];    // the list grouped by view mask (several views)
+    __shared__ uint32_t s_hist[kMulti ? 256 : 1];
+    __shared__ F4 s_rows[kWaveRows];
+    const int lane = threadIdx.x;
+    const int n_views = kMulti ? vt.n_views : 1;
+    const uint32_t span = 64u * (uint32_t)per, n_chunks = (n + span - 1) / span;
+    const int nq = (3 * (opt.sh_degree + 1) * (opt.sh_degree + 1) + 3) >> 2;    // float4s of a row in use
+    const RowLanes rl(lane);
+    uint32_t cnt = 0, k = 0, chunk = blockIdx.x;
+    // one view: the next chunk's tile counts are read ahead of the chain
+    uint32_t ahead[kChunkPer];
+    const auto read_ahead = [&](uint32_t c) {
+#pragma unroll
+        for (int i = 0; i < kChunkPer; ++i) {
+            const uint64_t g = (uint64_t)c * span + 64 * i + lane;
+            ahead[i] = i < per && g < n ? proj.tiles[g] : 0u;
+        }
+    };
+    if (!kMulti) read_ahead(chunk);
+    for (;;) {
+        // scan: list the seen Gaussians; zeros for the others
+        while (cnt < kFill && chunk < n_chunks) {
+            const uint32_t g0 = chunk * span;
+            uint32_t ln = lane;      // opaque: no address is held over the chain
+            asm volatile("" : "+v"(ln));
+            uint32_t vis[kChunkPer];
+            if (kMulti) {
+                uint32_t t[GS_MAX_VIEWS][kChunkPer];
+#pragma unroll
+                for (int v = 0; v < GS_MAX_VIEWS; ++v)
+#pragma unroll
+                    for (int i = 0; i < kChunkPer; ++i) {
+                        const uint64_t g = (uint64_t)g0 + 64 * i + ln;
+                        t[v][i] = v < n_views && i < per && g < n ? proj.tiles[(int64_t)v * n + g] : 0u;
+                    }
+#pragma unroll
+                for (int i = 0; i < kChunkPer; ++i) {
+                    vis[i] = 0;
+#pragma unroll
+                    for (int v = 0; v < GS_MAX_VIEWS; ++v) vis[i] |= t[v][i] ? 1u << v : 0u;
                 }
-                __builtin_nontemporal_store(nrm, mean2d_norm + slot);
-                if (absgrad) {
-                    __builtin_nontemporal_store(ax, absgrad + 2 * slot);
-                    __builtin_nontemporal_store(ay, absgrad + 2 * slot + 1);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kChunkPer; ++i) vis[i] = ahead[i] ? 1u : 0u;
+            }
+            uint64_t seen[kChunkPer];
+#pragma unroll
+            for (int i = 0; i < kChunkPer; ++i) {
+                const uint32_t loc = 64 * i + ln;
+                const bool in = i < per && (uint64_t)g0 + loc < n;
+                seen[i] = __ballot(vis[i] != 0);
+                if (vis[i]) {
+                    const uint32_t m = __builtin_amdgcn_mbcnt_hi((uint32_t)(seen[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)seen[i], 0));
+                    s_list[cnt + m] = loc | k << 8 | vis[i] << 16;
+                }
+                cnt += (uint32_t)__popcll(seen[i]);
+                // statistics: of every Gaussian, a whole line at a time, with
+                // one view; with several the chain writes the seen ones'
+                for (int v = 0; v < n_views; ++v)
+                    if (in && (!kMulti || !(vis[i] & (1u << v)))) {
+                        const int64_t slot = (int64_t)v * n + g0 + loc;
+                        const bool read = !kMulti && vis[i];
+                        const float* g2 = grad2d + slot * kG2;
+                        const float gx = read ? g2[0] : 0.0f, gy = read ? g2[1] : 0.0f;
+                        const float ax = read && absgrad ? g2[10] : 0.0f, ay = read && absgrad ? g2[11] : 0.0f;
+                        if (kMulti) {
+                            mean2d_norm[slot] = 0.0f;
+                            if (absgrad) absgrad[2 * slot] = absgrad[2 * slot + 1] = 0.0f;
+                        } else {
+                            __builtin_nontemporal_store(sqrtf(gx * gx + gy * gy), mean2d_norm + slot);
+                            if (absgrad) {
+                                __builtin_nontemporal_store(ax, absgrad + 2 * slot);
+                                __builtin_nontemporal_store(ay, absgrad + 2 * slot + 1);
+                            }
+                        }
+                    }
+                if (!kZeroed && in && !vis[i]) {
+#pragma unroll
+                    for (int c = 0; c < 11; ++c) *grad_row(out, n, g0 + loc, c) = 0.0f;
+                    if (out.app) reinterpret_cast<float4*>(out.app)[g0 + loc] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 }
             }
-        }
-        if (!kZeroed) {
+            if (!kZeroed) {
+                // zero coefficient rows, twelve neighbouring lanes to a row
+                F4* dsh = reinterpret_cast<F4*>(out.sh) + (int64_t)12 * g0 + ln;
 #pragma unroll
-            for (int c = 0; c < kStageRows; ++c) s_grad[c * kSpan + loc] = 0.0f;
+                for (int i = 0; i < kChunkPer; ++i)
+                    for (int a = 0; a < 4 && i < per; ++a)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            const int r = 16 * a + rl.rc[c];
+                            if ((uint64_t)g0 + 64 * i + r < n && !((seen[i] >> r) & 1))
+                                __builtin_nontemporal_store(F4{0.0f, 0.0f, 0.0f, 0.0f}, dsh + 768 * i + 192 * a + 64 * c);
+                        }
+            }
+            chunk += gridDim.x;
+            ++k;
+            if (!kMulti) read_ahead(chunk);
         }
-        s_seen[loc] = vis ? 1 : 0;
-        const uint64_t m = __ballot(vis != 0);
-        if (m) {
-            const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&s_count, (uint32_t)__popcll(m));
-            base = __shfl(base, 0);
-            if (vis) s_list[base + below] = (uint32_t)loc | (vis << 16);
+        wave_sync();
+        const bool last = chunk >= n_chunks;
+        const uint32_t* lst = s_list;
+        if (kMulti) {
+            group_by_views(s_list, cnt, s_group, s_hist);
+            lst = s_group;
         }
+        // the chain, 64 listed Gaussians at a time (with several views,
+        // those seen by the same views side by side); lanes past the end
+        // work on the last one and write nothing
+        uint32_t b = 0;
+        for (; b + 64 <= cnt || (last && b < cnt); b += 64) {
+            const int m = cnt - b < 64u ? (int)(cnt - b) : 64;
+            const uint32_t e = lst[b + (lane < m ? lane : m - 1)];
+            uint32_t g = (((e >> 8) & 255u) * gridDim.x + blockIdx.x) * span + (e & 255u);
+            const GaussIn in = load_gauss(gp, n, g);
+            double dmu[3] = {0.0, 0.0, 0.0};
+            float dcb[3] = {0.0f, 0.0f, 0.0f};
+            load_rows(gp.sh, g, nq, rl, s_rows);
+            colour_bwd_one<kMulti>(in, vt, opt, grad2d + (int64_t)g * kG2, (int64_t)n * kG2, e >> 16,
+                                   s_rows + lane * kRowF4, dmu, dcb);
+            store_rows(out.sh, g, m, rl, s_rows);
+            // (opaque, so that no address of the geometry's outputs is held
+            // over the colour chain)
+            asm volatile("" : "+v"(g) : : "memory");
+            if (lane < m)
+                geometry_bwd_one<kZeroed, kMulti>(in, gp.app != nullptr, vt, opt, grad2d + (int64_t)g * kG2, (int64_t)n * kG2,
+                                         e >> 16, dmu, dcb, out, n, g, mean2d_norm, absgrad);
+        }
+        if (last) return;
+        // what is left over, to the front
+        const uint32_t left = cnt - b;
+        const uint32_t e = lst[b + ((uint32_t)lane < left ? lane : 0)];
+        wave_sync();
+        if ((uint32_t)lane < left) s_list[lane] = e;
+        cnt = left;
     }
-    __syncthreads();
-
-    // zero coefficient rows of unseen Gaussians: coalesced 16-byte stores
-    const int64_t rows = n - g0 < kSpan ? n - g0 : kSpan;
-    F4* dsh = reinterpret_cast<F4*>(out.sh) + 12 * g0;
-    if (!kZeroed)
-        for (int q = tid; q < 12 * rows; q += kPB)
-            if (!s_seen[q / 12]) __builtin_nontemporal_store(F4{0.0f, 0.0f, 0.0f, 0.0f}, dsh + q);
-
-    // pass 2: the chain, one thread per seen Gaussian (with several views,
-    // Gaussians seen by the same views side by side)
-    const uint32_t cnt = s_count;
-    const uint32_t* lst = s_list;
-    if (vt.n_views > 1) {
-        group_by_views(s_list, cnt, s_group, s_hist);
-        lst = s_group;
-    }
-    for (uint32_t j = tid; j < cnt; j += kPB) {
-        const uint32_t e = lst[j];
-        const int64_t g = g0 + (e & 0xFFFFu);
-        if (kZeroed)
-            project_bwd_one(gp, n, vt, opt, grad2d, out, g, e >> 16, OutRows{out, n, g});
-        else
-            project_bwd_one(gp, n, vt, opt, grad2d, out, g, e >> 16, StageRows{s_grad, (int)(e & 0xFFFFu)});
-    }
-    if (kZeroed) return;
-    __syncthreads();
-
-    // pass 3: the span's rows, streamed out (not read again here)
-    for (int c = 0; c < 11; ++c) {
-        float* row = c < 3 ? out.means + c * n : c < 6 ? out.scales + (c - 3) * n
-                   : c < 10 ? out.quats + (c - 6) * n : out.opac;
-        for (int loc = tid; loc < rows; loc += kPB) __builtin_nontemporal_store(s_grad[c * kSpan + loc], row + g0 + loc);
-    }
-    if (out.app)
-        for (int loc = tid; loc < rows; loc += kPB)
-            __builtin_nontemporal_store(F4{s_grad[(kStageApp + 0) * kSpan + loc], s_grad[(kStageApp + 1) * kSpan + loc],
-                                           s_grad[(kStageApp + 2) * kSpan + loc], s_grad[(kStageApp + 3) * kSpan + loc]},
-                                        reinterpret_cast<F4*>(out.app) + g0 + loc);
 }
 
 }  // namespace
@@ -421,14 +612,18 @@ __global__ __launch_bounds__(kPB) void k_project_bwd(GaussPtrs gp, int64_t n, Vi
 hipError_t launch_project_bwd(const GaussPtrs& g, int64_t n, const ViewTable& vt, const OptK& opt,
                               const Projected& proj, const float* grad2d, const GradPtrs& out, float* mean2d_norm,
                               float* absgrad, hipStream_t s, bool grads_zeroed) {
-    const unsigned blocks = (unsigned)((n + kSpan - 1) / kSpan);
+    if (n > 0xFFFFFFFFLL) return hipErrorInvalidValue;     // Gaussians are kept as 32-bit indices
+    if (!n) return hipSuccess;
+    // chunks of 256 Gaussians when that leaves every wave several, else of 64
+    const int per = n >= (int64_t)kMaxWaves * 64 * kChunkPer ? kChunkPer : 1;
+    const int64_t chunks = (n + 64 * per - 1) / (64 * per);
+    int64_t blocks = chunks < kMaxWaves ? chunks : kMaxWaves;
+    if (blocks * 256 < chunks) blocks = (chunks + 255) / 256;
     const hipEvent_t timed_ = timer_begin(GS_KERNEL_PROJECT_BWD, s);
-    if (grads_zeroed)
-        hipLaunchKernelGGL(k_project_bwd<true>, dim3(blocks), dim3(kPB), 0, s, g, n, vt, opt, proj, grad2d, out,
-                           mean2d_norm, absgrad);
-    else
-        hipLaunchKernelGGL(k_project_bwd<false>, dim3(blocks), dim3(kPB), 0, s, g, n, vt, opt, proj, grad2d, out,
-                           mean2d_norm, absgrad);
+    const auto kernel = grads_zeroed ? (vt.n_views > 1 ? k_project_bwd<true, true> : k_project_bwd<true, false>)
+                                     : (vt.n_views > 1 ? k_project_bwd<false, true> : k_project_bwd<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), 0, s, g, (uint32_t)n, vt, opt, proj, grad2d, out, mean2d_norm,
+                       absgrad, per);
     timer_end(timed_, s);
     return hipGetLastError();
 }
