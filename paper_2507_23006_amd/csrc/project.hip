@@ -13,7 +13,10 @@
 // Paper: §3.1 (Eq. 1 for Sigma = R S S^T R^T; the projection to 2D Gaussians
 // G' in the text after it), §3.5.4 (anti-aliasing dilation and opacity
 // compensation), colour c of §3.1 as degree-3 SH.
+#include <math.h>
+
 #include "gs_internal.h"
+#include "rows.h"
 
 namespace gs {
 
@@ -57,45 +60,63 @@ __device__ __forceinline__ bool load_shape(const GaussPtrs& gp, int64_t n, int64
     return true;
 }
 
+// square root within an ulp for r in the range that projected sizes have (0
+// below 1e-200): one step from the reciprocal root's estimate squares its
+// 2^-26 error twice over, a third of the instructions of the general sqrt
+__device__ __forceinline__ double root(double r) {
+    const double s = __builtin_amdgcn_rsq(r);
+    double g = r * s;
+    double h = 0.5 * s;
+    double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    e = fma(-g, g, r);
+    g = fma(e, h, g);
+    return !(r <= 1e-200) ? g : 0.0;
+}
+
 // Exact tile culling of a rectangle of w x h <= 64 tiles at (ix0, iy0): bit
 // (ty - iy0) w + (tx - ix0) is set when the alpha ellipse
 // q(d) = A dx^2 + 2 B dx dy + C dy^2 <= L, L = 2 tau (1 + 4e-6), reaches the
 // tile's pixel-centre rectangle widened by 1e-3 px.  Row by row: the ellipse
 // within a row's strip is convex, so it meets a tile iff its x-extent over the
-// strip meets the tile's columns.  For fixed y the ellipse spans
-// x = (-B y -+ sqrt(A L - det y^2)) / A; the upper end is concave in y and
-// peaks at the rightmost point (X, -B X / C), X = sqrt(L C / det), the lower
-// end is convex with its minimum at (-X, B X / C), so over a strip (clipped
-// to the ellipse's y-extent +-sqrt(L A / det)) both come from those y clamped
-// into it.  O(rows) square roots per Gaussian instead of work per tile, so a
-// wave is not held by its widest lane.  Plain IEEE operations in a fixed
-// order (no contraction).
+// strip meets the tile's columns, a run of tiles found by division.  For fixed y
+// the ellipse spans x = (-B y -+ sqrt(A L - det y^2)) / A; the upper end is
+// concave in y and peaks at the rightmost point (X, -B X / C), X = sqrt(L C /
+// det), the lower end is convex with its minimum at (-X, B X / C), so over a
+// strip (clipped to the ellipse's y-extent +-sqrt(L A / det)) both come from
+// those y clamped into it.  Two square roots a row, whose count (the tallest
+// rectangle of the wave's) bounds the projection's arithmetic: with IEEE roots
+// and divisions and a loop over the columns they were two thirds of it.
 __device__ uint64_t covered_tiles(const ViewK& V, double mx, double my, double A, double B, double C, double tau,
                                   int ix0, int iy0, int w, int h) {
-#pragma clang fp contract(off)
     const double L = 2.0 * tau * (1.0 + 4e-6);
     const double det = A * C - B * B;
-    const double X = sqrt(L * C / det), Y = sqrt(L * A / det), yr = -B / C * X;
+    const double id = 1.0 / det, iA = 1.0 / A;
+    const double X = root(L * C * id), Y = root(L * A * id), yr = -B / C * X;
+    const double AL = A * L, BA = -B * iA;
+    // in units of tiles from the rectangle's first column: the first column's
+    // first pixel centre less the margin, its last pixel centre with the
+    // margin, and the image's last
+    const double x0 = mx - ((double)(ix0 * kTile) + 0.5 - 1e-3), x1 = mx - ((double)(ix0 * kTile + kTile - 1) + 0.5 + 1e-3);
+    const double xe = (double)(V.W - 1) + 0.5 + 1e-3 - mx;
     uint64_t m = 0;
-    for (int j = 0; j < h; ++j) {
-        const int ty = iy0 + j;
-        int py1 = ty * kTile + kTile - 1;
+    double ylo = (double)(iy0 * kTile) + 0.5 - 1e-3 - my;
+    for (int j = 0; j < h; ++j, ylo += (double)kTile) {
+        int py1 = (iy0 + j) * kTile + kTile - 1;
         if (py1 > V.H - 1) py1 = V.H - 1;
-        const double ylo = (double)(ty * kTile) + 0.5 - 1e-3 - my, yhi = (double)py1 + 0.5 + 1e-3 - my;
-        const double a = ylo > -Y ? ylo : -Y, b = yhi < Y ? yhi : Y;
+        const double yhi = (double)py1 + 0.5 + 1e-3 - my;
+        const double a = fmax(ylo, -Y), b = fmin(yhi, Y);
         if (a > b) continue;
-        const double y1 = yr < a ? a : (yr > b ? b : yr);
-        const double y2 = -yr < a ? a : (-yr > b ? b : -yr);
-        const double r1 = A * L - det * y1 * y1, r2 = A * L - det * y2 * y2;
-        const double xhi_e = (-B * y1 + sqrt(r1 > 0.0 ? r1 : 0.0)) / A;
-        const double xlo_e = (-B * y2 - sqrt(r2 > 0.0 ? r2 : 0.0)) / A;
-        for (int i = 0; i < w; ++i) {
-            const int tx = ix0 + i;
-            int px1 = tx * kTile + kTile - 1;
-            if (px1 > V.W - 1) px1 = V.W - 1;
-            const double xlo = (double)(tx * kTile) + 0.5 - 1e-3 - mx, xhi = (double)px1 + 0.5 + 1e-3 - mx;
-            if (xlo <= xhi_e && xhi >= xlo_e) m |= 1ull << (j * w + i);
-        }
+        const double y1 = fmin(fmax(yr, a), b), y2 = fmin(fmax(-yr, a), b);
+        const double xhi_e = fma(BA, y1, root(fma(-det * y1, y1, AL)) * iA);
+        const double xlo_e = fma(BA, y2, -root(fma(-det * y2, y2, AL)) * iA);
+        if (xlo_e > xe) continue;      // past the image's last pixel centre
+        // column i: 16 i <= xhi_e + x0 and 16 i >= xlo_e + x1
+        const double dw = (double)(w - 1);
+        const int i1 = (int)fmax(fmin(floor((xhi_e + x0) * (1.0 / kTile)), dw), -1.0);
+        const int i0 = (int)fmin(fmax(ceil((xlo_e + x1) * (1.0 / kTile)), 0.0), 64.0);
+        if (i0 <= i1) m |= (~0ull >> (63 - (i1 - i0))) << (j * w + i0);
     }
     return m;
 }
@@ -110,10 +131,11 @@ __device__ __forceinline__ uint32_t project_view(const ViewK& V, const OptK& opt
     const double W0 = V.R[0], W1 = V.R[1], W2 = V.R[2], W3 = V.R[3], W4 = V.R[4], W5 = V.R[5], W6 = V.R[6],
                  W7 = V.R[7], W8 = V.R[8];
     const double fx = V.fx, fy = V.fy;
-    const double u = tx / tz, vv = ty / tz;
+    const double itz = 1.0 / tz;
+    const double u = tx * itz, vv = ty * itz;
     const double uc = fmin(fmax(u, V.ulo), V.uhi);
     const double vc = fmin(fmax(vv, V.vlo), V.vhi);
-    const double j00 = fx / tz, j02 = -fx * uc / tz, j11 = fy / tz, j12 = -fy * vc / tz;
+    const double j00 = fx * itz, j02 = -j00 * uc, j11 = fy * itz, j12 = -j11 * vc;
     // Tm = J W (2x3), Vm = Tm M (2x3): Sigma_2D = Vm Vm^T
     const double T0 = j00 * W0 + j02 * W6, T1 = j00 * W1 + j02 * W7, T2 = j00 * W2 + j02 * W8;
     const double T3 = j11 * W3 + j12 * W6, T4 = j11 * W4 + j12 * W7, T5 = j11 * W5 + j12 * W8;
@@ -133,8 +155,8 @@ __device__ __forceinline__ uint32_t project_view(const ViewK& V, const OptK& opt
     const double ad = ca + dil, cd = cc + dil;
     const double detd = det2 + dil * (ca + cc) + dil * dil;
     const double mx = fx * u + (double)V.cx, my = fy * vv + (double)V.cy;
-    const double lmax = 0.5 * (ad + cd) + sqrt(0.25 * (ad - cd) * (ad - cd) + cb * cb);
-    const double ext = 3.0 * sqrt(lmax);
+    const double lmax = 0.5 * (ad + cd) + root(0.25 * (ad - cd) * (ad - cd) + cb * cb);
+    const double ext = 3.0 * root(lmax);
     if (!(detd > 0.0 && isfinite(ext) && isfinite(mx) && isfinite(my))) return 0;
     const double r = ceil(ext);
     const int TW = V.tiles_x, TH = V.tiles_y;
@@ -151,12 +173,13 @@ __device__ __forceinline__ uint32_t project_view(const ViewK& V, const OptK& opt
     // 1e-6 and 1e-3 px), the box keeps the tiles whose pixel centres it
     // reaches; the rectangle drops the others, which no entry could change.
     // The box also travels in the record for the per-quadrant culling.
-    const double rho = opt.aa ? (det2 > 0.0 ? sqrt(det2 / detd) : 0.0) : 1.0;
+    const double invd = 1.0 / detd;
+    const double rho = opt.aa ? root(det2 * invd) : 1.0;
     const double o2 = opac * rho;
     if (!((float)o2 >= kAlphaMin)) return 0;     // below the skip threshold everywhere
     const double tau = log(255.0 * o2) + 1e-5;
-    const double hxd = sqrt(2.0 * tau * ad) * (1.0 + 1e-6) + 1e-3;
-    const double hyd = sqrt(2.0 * tau * cd) * (1.0 + 1e-6) + 1e-3;
+    const double hxd = root(2.0 * tau * ad) * (1.0 + 1e-6) + 1e-3;
+    const double hyd = root(2.0 * tau * cd) * (1.0 + 1e-6) + 1e-3;
     x0t = fmax(x0t, floor(ceil(mx - hxd - 0.5) * (1.0 / kTile)));
     x1t = fmin(x1t, floor(floor(mx + hxd - 0.5) * (1.0 / kTile)));
     y0t = fmax(y0t, floor(ceil(my - hyd - 0.5) * (1.0 / kTile)));
@@ -164,18 +187,17 @@ __device__ __forceinline__ uint32_t project_view(const ViewK& V, const OptK& opt
     if (!(x0t <= x1t && y0t <= y1t)) return 0;
     const int ix0 = (int)x0t, iy0 = (int)y0t, ix1 = (int)x1t, iy1 = (int)y1t;
     const int w = ix1 - ix0 + 1, h = iy1 - iy0 + 1;
+    const double A = cd * invd, B = -cb * invd, C = ad * invd;
     uint32_t covered = (uint32_t)(w * h);
     if (out.tile_mask) {
         uint64_t m = 0;
         if (w * h <= 64) {
-            m = covered_tiles(V, mx, my, cd / detd, -cb / detd, ad / detd, tau, ix0, iy0, w, h);
+            m = covered_tiles(V, mx, my, A, B, C, tau, ix0, iy0, w, h);
             if (!m) return 0;     // the ellipse reaches no pixel centre of the image
             covered = (uint32_t)__popcll(m);
         }
         out.tile_mask[slot] = m;
     }
-    const double invd = 1.0 / detd;
-    const double A = cd * invd, B = -cb * invd, C = ad * invd;
     // mean = integer part (exact in float32) + fraction, so that the
     // compositing kernels can form a tile-relative mean without the
     // rounding of a large absolute pixel coordinate
@@ -193,7 +215,7 @@ __device__ __forceinline__ uint32_t project_view(const ViewK& V, const OptK& opt
 // read as 16-byte vectors; cb is the constant of the polynomial (1/2, or
 // the appearance colour offset)
 __device__ __forceinline__ void colour_view(const ViewK& V, const OptK& opt, double mu0, double mu1, double mu2,
-                                            const float4* __restrict__ shq, float4 cb, const Projected& out,
+                                            const F4* __restrict__ shq, float4 cb, const Projected& out,
                                             int64_t slot, float yfrac) {
     const int nb = (opt.sh_degree + 1) * (opt.sh_degree + 1);
     const int nq = (3 * nb + 3) >> 2;    // float4s that hold the used coefficients
@@ -206,7 +228,7 @@ __device__ __forceinline__ void colour_view(const ViewK& V, const OptK& opt, dou
     float shv[48];
 #pragma unroll
     for (int q = 0; q < 12; ++q) {
-        const float4 t = q < nq ? shq[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const F4 t = q < nq ? shq[q] : F4{0.0f, 0.0f, 0.0f, 0.0f};
         shv[4 * q + 0] = t.x; shv[4 * q + 1] = t.y; shv[4 * q + 2] = t.z; shv[4 * q + 3] = t.w;
     }
     float c[3] = {cb.x, cb.y, cb.z};
@@ -221,38 +243,58 @@ __device__ __forceinline__ void colour_view(const ViewK& V, const OptK& opt, dou
     out.rec[4 * slot + 2] = make_float4(fmaxf(c[0], 0.0f), fmaxf(c[1], 0.0f), fmaxf(c[2], 0.0f), yfrac);
 }
 
-// Conservative pre-test of project_view: false only when the Gaussian
+// Conservative pre-test of project_view in FP32: false only when the Gaussian
 // certainly covers no tile.  With M = R(q) diag(s), R orthonormal,
-// lambda_max(Sigma_2D) = |J W M|^2 <= |J|_F^2 s_max^2, so the 3-sigma radius
-// is at most 3 sqrt(|J|_F^2 s_max^2 + dilation); if even that rectangle
-// misses the image, or the opacity is below the skip threshold (o' = o rho
-// <= o), the exact test culls too.
-__device__ __forceinline__ bool may_cover(const ViewK& V, const OptK& opt, double tx, double ty, double tz,
-                                          double smax, float opac) {
-    if (!(opac >= kAlphaMin)) return false;
-    const double u = tx / tz, vv = ty / tz;
-    const double uc = fmin(fmax(u, V.ulo), V.uhi), vc = fmin(fmax(vv, V.vlo), V.vhi);
-    const double fx = V.fx, fy = V.fy;
-    const double jf2 = (fx * fx * (1.0 + uc * uc) + fy * fy * (1.0 + vc * vc)) / (tz * tz);
-    const double rb = ceil(3.0 * sqrt(jf2 * smax * smax + (double)opt.dilation) * (1.0 + 1e-6)) + 1.0;
-    const double mx = fx * u + (double)V.cx, my = fy * vv + (double)V.cy;
-    if (!(isfinite(rb) && isfinite(mx) && isfinite(my))) return true;    // the exact path decides
-    const double fmx = floor(mx), fmy = floor(my);
-    return fmx + rb >= 0.0 && fmx - rb <= (double)(V.tiles_x * kTile - 1) && fmy + rb >= 0.0 &&
-           fmy - rb <= (double)(V.tiles_y * kTile - 1);
+// lambda_max(Sigma_2D) = |J W M|^2 <= |J|_F^2 |W|^2 s_max^2, and |J|_F <=
+// sqrt(fx^2 (1 + u^2) + fy^2 (1 + v^2)) / tz for the clamped u, v, so the
+// 3-sigma radius with its rounding up is at most (jn s_max) / tz + k, k =
+// 3 sqrt(dilation) + 2.  Times tz > 0, "the rectangle reaches the image" is then
+// linear in t for each image side, and reads no division or root.  Each sum is
+// compared with the bound e on its rounding error, so that only a Gaussian
+// outside by more is dropped; a NaN or an infinity drops nothing.
+// 12M Gaussians in eight views: the test in FP64 took 1 of the kernel's 3 ms.
+struct ViewPlane {
+    float left, right, top, bottom;     // coefficients of tz
+    float jn;                           // of the largest scale
+    float ez, ef, tn;                   // errors of tz and of a side are <= ez (a + tn), ef (a + tn); a = |mu|_1
+};
+
+struct PlaneTable {
+    ViewPlane p[GS_MAX_VIEWS];
+};
+
+__device__ __forceinline__ void view_point32(const ViewK& V, const float mu[3], float& tx, float& ty, float& tz) {
+    tx = fmaf(V.R[0], mu[0], fmaf(V.R[1], mu[1], fmaf(V.R[2], mu[2], V.t[0])));
+    ty = fmaf(V.R[3], mu[0], fmaf(V.R[4], mu[1], fmaf(V.R[5], mu[2], V.t[1])));
+    tz = fmaf(V.R[6], mu[0], fmaf(V.R[7], mu[1], fmaf(V.R[8], mu[2], V.t[2])));
+}
+
+// between the near and the far plane, or too close to them to tell
+__device__ __forceinline__ bool may_be_in_front(const ViewK& V, const ViewPlane& P, const float mu[3], float a) {
+    const float tz = fmaf(V.R[6], mu[0], fmaf(V.R[7], mu[1], fmaf(V.R[8], mu[2], V.t[2])));
+    const float e = P.ez * (a + P.tn);
+    return !(tz + e < V.znear) && !(tz - e > V.zfar);
+}
+
+// the four image sides; smax: the largest scale's size
+__device__ __forceinline__ bool may_cover(const ViewK& V, const ViewPlane& P, const float mu[3], float a, float smax) {
+    float tx, ty, tz;
+    view_point32(V, mu, tx, ty, tz);
+    const float r = fmaf(P.jn, smax, P.ef * (a + P.tn)), x = V.fx * tx, y = V.fy * ty;
+    return !(fmaf(P.left, tz, r) + x < 0.0f) && !(fmaf(P.right, tz, r) - x < 0.0f) &&
+           !(fmaf(P.top, tz, r) + y < 0.0f) && !(fmaf(P.bottom, tz, r) - y < 0.0f);
 }
 
 // exact projection and colour of Gaussian g (mean mu, scales s, opacity
-// op, as stored) into the views of `cand`; slot of view v = slot_base +
-// v * slot_stride
+// op, coefficient row shq, as stored) into the views of `cand`; slot of view v
+// = slot_base + v * slot_stride
 __device__ __forceinline__ void project_candidate(const GaussPtrs& gp, int64_t n, const ViewTable& vt,
                                                   const OptK& opt, const Projected& out, int64_t g, uint32_t cand,
                                                   int64_t slot_base, int64_t slot_stride, const float mu[3],
-                                                  const float sc[3], float op) {
+                                                  const float sc[3], float op, const F4* __restrict__ shq) {
     const double mu0 = mu[0], mu1 = mu[1], mu2 = mu[2];
     double M[9], opac = 0.0;
     const bool shape_ok = load_shape(gp, n, g, sc[0], sc[1], sc[2], op, M, opac);
-    const float4* shq = reinterpret_cast<const float4*>(gp.sh) + 12 * g;
     const float4 cb = gp.app ? reinterpret_cast<const float4*>(gp.app)[g] : make_float4(0.5f, 0.5f, 0.5f, 0.0f);
     for (int v = 0; v < vt.n_views; ++v) {
         if (!(cand & (1u << v))) continue;
@@ -261,7 +303,8 @@ __device__ __forceinline__ void project_candidate(const GaussPtrs& gp, int64_t n
         double tx, ty, tz;
         view_point(V, mu0, mu1, mu2, tx, ty, tz);
         float yfrac = 0.0f;
-        const uint32_t ntiles = shape_ok ? project_view(V, opt, tx, ty, tz, M, opac, out, slot, yfrac) : 0u;
+        const bool front = tz >= (double)V.znear && tz <= (double)V.zfar;
+        const uint32_t ntiles = shape_ok && front ? project_view(V, opt, tx, ty, tz, M, opac, out, slot, yfrac) : 0u;
         if (ntiles) colour_view(V, opt, mu0, mu1, mu2, shq, cb, out, slot, yfrac);
         out.tiles[slot] = ntiles;
         out.dkey[slot] = ntiles ? __float_as_uint((float)tz) : 0xFFFFFFFFu;
@@ -284,103 +327,143 @@ __device__ __forceinline__ void list_append(uint32_t cand, int loc, int lane, ui
     if (cand) s_list[base + below] = (uint32_t)loc | (cand << 16);
 }
 
-// Every view of the launch sees the same n Gaussians: slot = view * n + g.
-// A workgroup owns 1024 Gaussians.  Pass 1 reads each mean (and, for
-// Gaussians in front of some camera, its scales and opacity), runs the
-// conservative pre-test per view, writes the culled slots' count and key
-// with coalesced stores and lists the rest in LDS with the values it read;
-// pass 2 runs the FP64 EWA and the colour on full waves of listed Gaussians
-// only (a large scene leaves most lanes culled, which would otherwise idle
-// through the FP64 chain of their wave's few visible neighbours), reading
-// from HBM only their quaternions and coefficient rows.
-__global__ __launch_bounds__(kPF, 4) void k_project_fwd(GaussPtrs gp, int64_t n, ViewTable vt, OptK opt,
-                                                     Projected out) {
-    __shared__ uint32_t s_list[kPFSpan];
-    __shared__ uint32_t s_group[kPFSpan];   // the list grouped by view mask (several views)
-    __shared__ uint32_t s_hist[256];
-    __shared__ float s_par[7][kPFSpan];     // listed Gaussians' mean, scales, opacity
-    __shared__ uint32_t s_count;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int64_t g0 = (int64_t)blockIdx.x * kPFSpan;
-    if (tid == 0) s_count = 0;
-    __syncthreads();
-    // the thread's kPFPer Gaussians move through each phase together, so
-    // their independent loads are in flight at once: means; depths and the
-    // views each lies in; scales and opacity of those in front of a view;
-    // the conservative test
-    float mu[kPFPer][3];
+// Every view of the launch sees the same n Gaussians: slot = view * n + g.  Each
+// workgroup is one wave that scans chunks of 64 * per Gaussians (per <=
+// kPFPer): it reads the means and, of Gaussians in front of some camera, the
+// scales and opacity, runs the conservative pre-test per view, writes the
+// culled slots' count and key with coalesced stores and packs the rest into an
+// LDS list.  Whenever the list holds a batch of 64 (with several views after
+// grouping it by the views to test), the wave runs the FP64 EWA and the colour
+// on full waves of listed Gaussians (a large scene leaves most lanes culled, which
+// would otherwise idle through the FP64 chain of their wave's few visible
+// neighbours); their coefficient rows pass through LDS, where they stay for
+// all views.  Chunk k of the wave is chunk blockIdx.x + k gridDim.x, at most
+// 256 per wave.  A longer list would share views better, but its Gaussians'
+// parameters are in cache no more when it comes to them: with 384 and 64
+// entries 2880 and 2771 us for 12M Gaussians in eight views.
+//
+// HBM-bound where most Gaussians are seen, else by the 128-byte lines of which
+// one or two Gaussians are wanted.  Measured (256 threads over spans of 1024,
+// FP64 pre-test, IEEE roots and divisions before): 1M Gaussians, most seen
+// 108 -> 81 us, 6M with 16 % seen 220 -> 187, 12M in eight views 3000 -> 2771,
+// 120k 27 -> 15, 4096 29 -> 9.
+// Waves of a launch: as many as run at once, ten on a compute unit by their LDS,
+// with several views eight by their registers.  (One view of 6M Gaussians takes
+// 187, 186, 226 and 220 us with 2048, 2560, 2816 and 3072: a second turn of a
+// few waves is a long tail.)
+constexpr int64_t max_waves(bool multi) { return multi ? 2048 : 2560; }
+
+template <bool kMulti>
+__global__ __launch_bounds__(64, 3) void k_project_fwd(GaussPtrs gp, uint32_t n, ViewTable vt, PlaneTable planes,
+                                                       OptK opt, Projected out, int per) {
+    constexpr uint32_t kCap = 64 * (1 + kPFPer);
+    __shared__ uint32_t s_list[kCap];      // index in the chunk | chunk of the wave << 8 | view mask << 16
+    __shared__ uint32_t s_group[kMulti ? kCap : 1];    // the list grouped by view mask (several views)
+    __shared__ uint32_t s_hist[kMulti ? 256 : 1];
+    __shared__ F4 s_rows[kWaveRows];
+    const int lane = threadIdx.x;
+    const int n_views = kMulti ? vt.n_views : 1;
+    const uint32_t span = 64u * (uint32_t)per, n_chunks = (n + span - 1) / span;
+    const int nq = (3 * (opt.sh_degree + 1) * (opt.sh_degree + 1) + 3) >> 2;    // float4s of a row in use
+    const RowLanes rl(lane);
+    uint32_t cnt = 0, k = 0, chunk = blockIdx.x;
+    for (;;) {
+        while (cnt < 64 && chunk < n_chunks) {
+            const uint32_t g0 = chunk * span;
+            // the lane's Gaussians move through each phase together, so that
+            // their independent loads are in flight at once
+            float mu[kPFPer][3], a[kPFPer];
 #pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        const int64_t g = g0 + i * kPF + tid;
-        const bool ok = g < n;
-        mu[i][0] = ok ? gp.means[g] : 0.0f;
-        mu[i][1] = ok ? gp.means[n + g] : 0.0f;
-        mu[i][2] = ok ? gp.means[2 * n + g] : 0.0f;
-    }
-    uint32_t front[kPFPer];
+            for (int i = 0; i < kPFPer; ++i) {
+                const uint64_t g = (uint64_t)g0 + 64 * i + lane;
+                const bool ok = i < per && g < n;
 #pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        front[i] = 0;
-        if (g0 + i * kPF + tid >= n) continue;
-        for (int v = 0; v < vt.n_views; ++v) {
-            const ViewK& V = vt.v[v];
-            double tx, ty, tz;
-            view_point(V, mu[i][0], mu[i][1], mu[i][2], tx, ty, tz);
-            if (tz >= (double)V.znear && tz <= (double)V.zfar) front[i] |= 1u << v;
-        }
-    }
-    float sc[kPFPer][3], op[kPFPer];
+                for (int c = 0; c < 3; ++c) mu[i][c] = ok ? gp.means[(int64_t)c * n + g] : 0.0f;
+            }
+            uint32_t front[kPFPer];
 #pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        const int64_t g = g0 + i * kPF + tid;
-        sc[i][0] = sc[i][1] = sc[i][2] = op[i] = 0.0f;
-        if (front[i]) {
-            sc[i][0] = gp.scales[g];
-            sc[i][1] = gp.scales[n + g];
-            sc[i][2] = gp.scales[2 * n + g];
-            op[i] = gp.opac[g];
-        }
-    }
-    for (int i = 0; i < kPFPer; ++i) {
-        const int loc = i * kPF + tid;
-        const int64_t g = g0 + loc;
-        uint32_t cand = 0;
-        if (g < n) {
-            for (int v = 0; v < vt.n_views; ++v) {
-                const ViewK& V = vt.v[v];
-                if (front[i] & (1u << v)) {
-                    double tx, ty, tz;
-                    view_point(V, mu[i][0], mu[i][1], mu[i][2], tx, ty, tz);
-                    const float sm = fmaxf(fabsf(sc[i][0]), fmaxf(fabsf(sc[i][1]), fabsf(sc[i][2])));
-                    if (may_cover(V, opt, tx, ty, tz, (double)sm, op[i])) cand |= 1u << v;
+            for (int i = 0; i < kPFPer; ++i) {
+                front[i] = 0;
+                a[i] = fabsf(mu[i][0]) + fabsf(mu[i][1]) + fabsf(mu[i][2]);
+            }
+            for (int v = 0; v < n_views; ++v) {
+#pragma unroll
+                for (int i = 0; i < kPFPer; ++i)
+                    front[i] |= may_be_in_front(vt.v[v], planes.p[v], mu[i], a[i]) ? 1u << v : 0u;
+            }
+            float smax[kPFPer], op[kPFPer];
+#pragma unroll
+            for (int i = 0; i < kPFPer; ++i) {
+                const uint64_t g = (uint64_t)g0 + 64 * i + lane;
+                if (!(i < per && g < n)) front[i] = 0;
+                float sc[3] = {0.0f, 0.0f, 0.0f};
+                op[i] = 0.0f;
+                if (front[i]) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) sc[c] = gp.scales[(int64_t)c * n + g];
+                    op[i] = gp.opac[g];
                 }
-                if (!(cand & (1u << v))) {
-                    const int64_t slot = (int64_t)v * n + g;
-                    __builtin_nontemporal_store(0u, out.tiles + slot);
-                    __builtin_nontemporal_store(0xFFFFFFFFu, out.dkey + slot);
+                smax[i] = fmaxf(fabsf(sc[0]), fmaxf(fabsf(sc[1]), fabsf(sc[2])));
+            }
+#pragma unroll
+            for (int i = 0; i < kPFPer; ++i)
+                if (!(op[i] >= kAlphaMin)) front[i] = 0;     // o' = o rho <= o: below the skip threshold everywhere
+            uint32_t cand[kPFPer] = {};
+            for (int v = 0; v < n_views; ++v) {
+#pragma unroll
+                for (int i = 0; i < kPFPer; ++i) {
+                    const uint64_t g = (uint64_t)g0 + 64 * i + lane;
+                    if ((front[i] & (1u << v)) && may_cover(vt.v[v], planes.p[v], mu[i], a[i], smax[i]))
+                        cand[i] |= 1u << v;
+                    else if (i < per && g < n) {
+                        const int64_t slot = (int64_t)v * n + g;
+                        __builtin_nontemporal_store(0u, out.tiles + slot);
+                        __builtin_nontemporal_store(0xFFFFFFFFu, out.dkey + slot);
+                    }
                 }
             }
-            if (cand) {
-                s_par[0][loc] = mu[i][0]; s_par[1][loc] = mu[i][1]; s_par[2][loc] = mu[i][2];
-                s_par[3][loc] = sc[i][0]; s_par[4][loc] = sc[i][1]; s_par[5][loc] = sc[i][2];
-                s_par[6][loc] = op[i];
+#pragma unroll
+            for (int i = 0; i < kPFPer; ++i) {
+                const uint64_t m = __ballot(cand[i] != 0);
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                if (cand[i]) s_list[cnt + below] = (uint32_t)(64 * i + lane) | k << 8 | cand[i] << 16;
+                cnt += (uint32_t)__popcll(m);
             }
+            chunk += gridDim.x;
+            ++k;
         }
-        list_append(cand, loc, lane, s_list, &s_count);
-    }
-    __syncthreads();
-    const uint32_t cnt = s_count;
-    const uint32_t* lst = s_list;
-    if (vt.n_views > 1) {      // Gaussians that are candidates in the same views side by side
-        group_by_views(s_list, cnt, s_group, s_hist);
-        lst = s_group;
-    }
-    for (uint32_t j = tid; j < cnt; j += kPF) {
-        const uint32_t e = lst[j];
-        const int loc = (int)(e & 0xFFFFu);
-        const float mu[3] = {s_par[0][loc], s_par[1][loc], s_par[2][loc]};
-        const float sc[3] = {s_par[3][loc], s_par[4][loc], s_par[5][loc]};
-        project_candidate(gp, n, vt, opt, out, g0 + loc, e >> 16, g0 + loc, n, mu, sc, s_par[6][loc]);
+        wave_sync();
+        const bool last = chunk >= n_chunks;
+        const uint32_t* lst = s_list;
+        if (kMulti) {      // Gaussians that are candidates in the same views side by side
+            group_by_views(s_list, cnt, s_group, s_hist);
+            lst = s_group;
+        }
+        // lanes past the end work on the last Gaussian and write nothing
+        uint32_t b = 0;
+        for (; b + 64 <= cnt || (last && b < cnt); b += 64) {
+            const int m = cnt - b < 64u ? (int)(cnt - b) : 64;
+            const uint32_t e = lst[b + (lane < m ? lane : m - 1)];
+            const uint32_t g = (((e >> 8) & 255u) * gridDim.x + blockIdx.x) * span + (e & 255u);
+            float mu[3], sc[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                mu[c] = gp.means[(int64_t)c * n + g];
+                sc[c] = gp.scales[(int64_t)c * n + g];
+            }
+            const float op = gp.opac[g];
+            load_rows(gp.sh, g, nq, rl, s_rows);
+            if (lane < m)
+                project_candidate(gp, n, vt, opt, out, g, e >> 16, g, n, mu, sc, op, s_rows + lane * kRowF4);
+            wave_sync();
+        }
+        if (last) return;
+        // what is left over, to the front
+        const uint32_t left = cnt - b;
+        const uint32_t e = lst[b + ((uint32_t)lane < left ? lane : 0)];
+        wave_sync();
+        if ((uint32_t)lane < left) s_list[lane] = e;
+        cnt = left;
     }
 }
 
@@ -403,7 +486,7 @@ __device__ __forceinline__ int segment_of(const SlotSeg* __restrict__ segs, int3
 constexpr int kSlotSegCache = 128;
 __global__ __launch_bounds__(kPF, 4) void k_project_slots(GaussPtrs gp, int64_t n, ViewTable vt, OptK opt,
                                                           const SlotSeg* __restrict__ segs, int32_t n_seg,
-                                                          uint32_t n_slots, Projected out) {
+                                                          uint32_t n_slots, PlaneTable planes, Projected out) {
     __shared__ uint32_t s_list[kPFSpan];
     __shared__ float s_par[7][kPFSpan];     // listed slots' mean, scales, opacity
     __shared__ uint32_t s_gid[kPFSpan];     // listed slots' Gaussian (n < 2^32, checked at launch)
@@ -460,14 +543,14 @@ __global__ __launch_bounds__(kPF, 4) void k_project_slots(GaussPtrs gp, int64_t 
         mu[i][2] = ok ? gp.means[2 * n + g[i]] : 0.0f;
     }
     bool front[kPFPer];
+    float a[kPFPer];
 #pragma unroll
     for (int i = 0; i < kPFPer; ++i) {
         front[i] = false;
+        a[i] = 0.0f;
         if (g[i] == kNone) continue;
-        const ViewK& V = vt.v[view[i]];
-        double tx, ty, tz;
-        view_point(V, mu[i][0], mu[i][1], mu[i][2], tx, ty, tz);
-        front[i] = tz >= (double)V.znear && tz <= (double)V.zfar;
+        a[i] = fabsf(mu[i][0]) + fabsf(mu[i][1]) + fabsf(mu[i][2]);
+        front[i] = may_be_in_front(vt.v[view[i]], planes.p[view[i]], mu[i], a[i]);
     }
     float sc[kPFPer][3], op[kPFPer];
 #pragma unroll
@@ -486,11 +569,8 @@ __global__ __launch_bounds__(kPF, 4) void k_project_slots(GaussPtrs gp, int64_t 
         uint32_t cand = 0;
         if (g[i] != kNone) {
             if (front[i]) {
-                const ViewK& V = vt.v[view[i]];
-                double tx, ty, tz;
-                view_point(V, mu[i][0], mu[i][1], mu[i][2], tx, ty, tz);
-                const double smax = fmax(fabs((double)sc[i][0]), fmax(fabs((double)sc[i][1]), fabs((double)sc[i][2])));
-                if (may_cover(V, opt, tx, ty, tz, smax, op[i])) cand = 1u << view[i];
+                const float smax = fmaxf(fabsf(sc[i][0]), fmaxf(fabsf(sc[i][1]), fabsf(sc[i][2])));
+                if (op[i] >= kAlphaMin && may_cover(vt.v[view[i]], planes.p[view[i]], mu[i], a[i], smax)) cand = 1u << view[i];
             }
             if (!cand) {
                 out.tiles[s] = 0u;
@@ -513,17 +593,65 @@ __global__ __launch_bounds__(kPF, 4) void k_project_slots(GaussPtrs gp, int64_t 
         // one view bit: the slot is s itself (stride 0)
         const float mu1[3] = {s_par[0][loc], s_par[1][loc], s_par[2][loc]};
         const float sc1[3] = {s_par[3][loc], s_par[4][loc], s_par[5][loc]};
-        project_candidate(gp, n, vt, opt, out, (int64_t)s_gid[loc], e >> 16, (int64_t)s, 0, mu1, sc1, s_par[6][loc]);
+        project_candidate(gp, n, vt, opt, out, (int64_t)s_gid[loc], e >> 16, (int64_t)s, 0, mu1, sc1, s_par[6][loc],
+                          reinterpret_cast<const F4*>(gp.sh) + (int64_t)12 * s_gid[loc]);
     }
 }
 
 }  // namespace
 
+// constants of the pre-test (see ViewPlane), rounded away from dropping
+static PlaneTable build_planes(const ViewTable& vt, const OptK& opt) {
+    PlaneTable pt = {};
+    const double k = 3.0 * sqrt((double)opt.dilation) + 2.0, up = 1.0 + 1e-5;
+    for (int v = 0; v < vt.n_views; ++v) {
+        const ViewK& V = vt.v[v];
+        // |W|: 1 for a rotation, else at most the Frobenius norm
+        double f2 = 0.0, off = 0.0, big = 1.0;
+        for (int i = 0; i < 9; ++i) {
+            f2 += (double)V.R[i] * V.R[i];
+            big = fmax(big, fabs((double)V.R[i]));
+        }
+        for (int i = 0; i < 3; ++i)
+            for (int j = 0; j < 3; ++j) {
+                double d = i == j ? -1.0 : 0.0;
+                for (int c = 0; c < 3; ++c) d += (double)V.R[3 * c + i] * V.R[3 * c + j];
+                off = fmax(off, fabs(d));
+            }
+        const double w = off < 1e-3 ? 1.0 + 2e-3 : sqrt(f2);
+        const double um = fmax(fabs(V.ulo), fabs(V.uhi)), vm = fmax(fabs(V.vlo), fabs(V.vhi));
+        const double fx = V.fx, fy = V.fy;
+        const double X = V.tiles_x * kTile, Y = V.tiles_y * kTile;
+        ViewPlane& P = pt.p[v];
+        P.left = (float)(V.cx + k);
+        P.right = (float)(X - V.cx + k);
+        P.top = (float)(V.cy + k);
+        P.bottom = (float)(Y - V.cy + k);
+        P.jn = (float)(up * 3.0 * w * sqrt(fx * fx * (1.0 + um * um) + fy * fy * (1.0 + vm * vm)));
+        // every coordinate is a sum of four products of at most big |mu|_1 + tn,
+        // rounded four times (2^-24 each), a side two such sums and three more
+        // roundings: 2^-20 covers both, with the constants' own rounding
+        P.tn = (float)(up * fmax(fabs((double)V.t[0]), fmax(fabs((double)V.t[1]), fabs((double)V.t[2]))));
+        P.ez = (float)(up * big * 0x1p-20);
+        P.ef = (float)(up * big * 0x1p-20 * (fmax(fx, fy) + fmax(fmax(fabs((double)P.left), fabs((double)P.right)),
+                                                               fmax(fabs((double)P.top), fabs((double)P.bottom)))));
+    }
+    return pt;
+}
+
 hipError_t launch_project_fwd(const GaussPtrs& g, int64_t n, const ViewTable& vt, const OptK& opt,
                               const Projected& out, hipStream_t s) {
-    const unsigned blocks = (unsigned)((n + kPFSpan - 1) / kPFSpan);
+    if (n > 0xFFFFFFFFLL) return hipErrorInvalidValue;     // Gaussians are kept as 32-bit indices
+    // chunks of 256 Gaussians when that leaves every wave several, else of 64
+    const int64_t waves = max_waves(vt.n_views > 1);
+    const int per = n >= waves * 64 * kPFPer ? kPFPer : 1;
+    const int64_t chunks = (n + 64 * per - 1) / (64 * per);
+    int64_t blocks = chunks < waves ? chunks : waves;
+    if (blocks * 256 < chunks) blocks = (chunks + 255) / 256;
     const hipEvent_t timed_ = timer_begin(GS_KERNEL_PROJECT_FWD, s);
-    hipLaunchKernelGGL(k_project_fwd, dim3(blocks), dim3(kPF), 0, s, g, n, vt, opt, out);
+    const auto kernel = vt.n_views > 1 ? k_project_fwd<true> : k_project_fwd<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), 0, s, g, (uint32_t)n, vt, build_planes(vt, opt), opt, out,
+                       per);
     timer_end(timed_, s);
     return hipGetLastError();
 }
@@ -534,7 +662,7 @@ hipError_t launch_project_slots(const GaussPtrs& g, int64_t n, const ViewTable& 
     if (!n_slots) return hipSuccess;
     if (n > 0xFFFFFFFFLL) return hipErrorInvalidValue;     // listed Gaussians are kept as 32-bit indices
     hipLaunchKernelGGL(k_project_slots, dim3((n_slots + kPFSpan - 1) / kPFSpan), dim3(kPF), 0, s, g, n, vt, opt, segs,
-                       n_seg, n_slots, out);
+                       n_seg, n_slots, build_planes(vt, opt), out);
     return hipGetLastError();
 }
 

@@ -2,8 +2,8 @@
 //
 // Each workgroup is one wave that scans chunks of 256 consecutive Gaussians:
 // it writes the zeros and statistics of those no view sees and packs the
-// others into an LDS list.  Whenever the list holds 64 (384 with several
-// views, grouped by the views that see them), the wave runs the chain, one
+// others into an LDS list.  Whenever the list holds 64 (with several views
+// after grouping them by the views that see them), the wave runs the chain, one
 // lane per listed Gaussian: it reads the parameters once, recomputes the
 // projection in FP64 for each view that sees the Gaussian, chains that view's
 // 2D gradients (mean2d, conic, opacity', colour, depth) back to the
@@ -21,7 +21,8 @@
 // Measured (workgroups of 256 threads over spans of 1024 before, one wave
 // now): 1M Gaussians, most of them seen, one view: 175 -> 119 us, 4.6 TB/s of
 // the 0.55 GB that rows and parameters hold; 4096: 34 -> 7 us; 12M in eight
-// views 6570 -> 2860 us; 6M with 16 % seen 310 -> 292 us, where 128-byte lines
+// views 6570 -> 2560 us (2860 with lists of 384, whose Gaussians' parameters
+// are in cache no more when the chain comes to them); 6M with 16 % seen 310 -> 292 us, where 128-byte lines
 // of which one or two Gaussians are wanted make 1.1 GB of the traffic.
 //
 // Paper: backward of Eq. 1 and of the projection of §3.1; the per-view
@@ -29,6 +30,7 @@
 // (§3.1, §3.3 Eq. 4), and the absolute accumulation is the AbsGS statistic
 // of §3.5.4.
 #include "gs_internal.h"
+#include "rows.h"
 
 namespace gs {
 
@@ -62,15 +64,9 @@ __device__ __forceinline__ void sh_basis_grad(float x, float y, float z, int k, 
     }
 }
 
-typedef float F4 __attribute__((ext_vector_type(4)));
-
 constexpr int kG2 = GS_GRAD2D_FLOATS;
 constexpr int kChunkPer = 4;               // Gaussians per lane in the scan of a chunk
 constexpr int kMaxWaves = 2048;            // two per SIMD, what the chain's registers allow
-// listed Gaussians from which a wave runs the chain: one batch, or with
-// several views enough for batches seen by the same views
-__host__ __device__ constexpr uint32_t fill_of(bool multi) { return multi ? 384u : 64u; }
-
 constexpr int kRowApp = 11;
 
 // row c of the one-float gradients (means 0-2, scales 3-5, quats 6-9,
@@ -98,62 +94,6 @@ __device__ __forceinline__ GaussIn load_gauss(const GaussPtrs& gp, int64_t n, in
     in.o = gp.opac[g];
     in.app = gp.app ? reinterpret_cast<const float4*>(gp.app)[g] : make_float4(0.5f, 0.5f, 0.5f, 0.0f);
     return in;
-}
-
-// orders a wave's LDS accesses before and after it
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// A wave's 64 coefficient rows (192 bytes each) between memory and LDS.  A lane
-// reading its own row touches two cache lines with each of its twelve 16-byte
-// loads, 16 KB of lines per instruction and wave, which the compute unit's L1
-// does not hold until the next piece is read; here twelve neighbouring lanes
-// move a row's pieces.  Rows lie 13 pieces apart in LDS, so that a piece of all
-// rows spreads over all banks.
-constexpr int kRowF4 = 13;
-constexpr int kWaveRows = 64 * kRowF4;     // float4s of LDS per wave
-
-struct RowLanes {
-    int rc[3], qc[3];      // row (of 16) and piece that the lane moves in step c of three
-    __device__ explicit RowLanes(int lane) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            rc[c] = (64 * c + lane) / 12;
-            qc[c] = 64 * c + lane - 12 * rc[c];
-        }
-    }
-};
-
-// rows of the Gaussians g (one per lane) into s
-__device__ __forceinline__ void load_rows(const float* __restrict__ sh, uint32_t g, int nq,
-                                          const RowLanes& rl, F4* s) {
-    const F4* src = reinterpret_cast<const F4*>(sh);
-    F4 piece[12];
-#pragma unroll
-    for (int i = 0; i < 12; ++i) {
-        const uint32_t r = __shfl(g, 16 * (i / 3) + rl.rc[i % 3]);
-        piece[i] = rl.qc[i % 3] < nq ? src[(int64_t)12 * r + rl.qc[i % 3]] : F4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-#pragma unroll
-    for (int i = 0; i < 12; ++i) s[(16 * (i / 3) + rl.rc[i % 3]) * kRowF4 + rl.qc[i % 3]] = piece[i];
-    wave_sync();
-}
-
-// the first m rows of s to those of their Gaussians
-__device__ __forceinline__ void store_rows(float* __restrict__ sh, uint32_t g, int m, const RowLanes& rl,
-                                           const F4* s) {
-    F4* dst = reinterpret_cast<F4*>(sh);
-    wave_sync();
-#pragma unroll
-    for (int i = 0; i < 12; ++i) {
-        const int r = 16 * (i / 3) + rl.rc[i % 3];
-        const uint32_t to = __shfl(g, r);
-        if (r < m) __builtin_nontemporal_store(s[r * kRowF4 + rl.qc[i % 3]], dst + (int64_t)12 * to + rl.qc[i % 3]);
-    }
-    wave_sync();
 }
 
 // band L of the polynomial: its part of the colour and of S_c = sum_k sh_kc
@@ -467,7 +407,7 @@ __global__ __launch_bounds__(64, 2) void k_project_bwd(GaussPtrs gp, uint32_t n,
                                                        const float* __restrict__ grad2d, GradPtrs out,
                                                        float* __restrict__ mean2d_norm, float* __restrict__ absgrad,
                                                        int per) {
-    constexpr uint32_t kFill = fill_of(kMulti), kCap = kFill + 64 * kChunkPer;
+    constexpr uint32_t kCap = 64 * (1 + kChunkPer);
     __shared__ uint32_t s_list[kCap];      // index in the chunk | chunk of the wave << 8 | view mask << 16
     __shared__ uint32_t s_group[kMulti ? kCap : 1];    // the list grouped by view mask (several views)
     __shared__ uint32_t s_hist[kMulti ? 256 : 1];
@@ -490,7 +430,7 @@ __global__ __launch_bounds__(64, 2) void k_project_bwd(GaussPtrs gp, uint32_t n,
     if (!kMulti) read_ahead(chunk);
     for (;;) {
         // scan: list the seen Gaussians; zeros for the others
-        while (cnt < kFill && chunk < n_chunks) {
+        while (cnt < 64 && chunk < n_chunks) {
             const uint32_t g0 = chunk * span;
             uint32_t ln = lane;      // opaque: no address is held over the chain
             asm volatile("" : "+v"(ln));
