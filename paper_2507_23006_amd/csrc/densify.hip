@@ -115,25 +115,43 @@ __global__ __launch_bounds__(kDT) void k_dens_mark_all(const uint32_t* __restric
     action[i] = grow_kind(scales, n, i, thr);
 }
 
-// rate = max(rate if `accumulate`, max over the table's views holding the mean of fx / depth)
-__global__ __launch_bounds__(kDT) void k_filter_rate(const float* __restrict__ means, int64_t n, ViewTable vt,
+// rate = max(rate if `accumulate`, max over the table's views holding the mean of fx / depth).
+// Bound by FP64 issue, so the camera's constants arrive as doubles (converting
+// them took as many instructions as the transform), a view is two distances
+// |x - c z| <= h z, and the maximum is the smallest z / fx, inverted once at the
+// end.  Four means a thread cover the latency of the FP64 chain.  6M means, 40
+// cameras: 195 us, 411 with three launches of up to 16 views and a division each.
+constexpr int kRatePer = 4;
+__global__ __launch_bounds__(kDT) void k_filter_rate(const float* __restrict__ means, int64_t n, RateTable tab,
                                                      int accumulate, float* __restrict__ rate) {
-    const int64_t i = (int64_t)blockIdx.x * kDT + threadIdx.x;
-    if (i >= n) return;
-    const double m0 = means[i], m1 = means[n + i], m2 = means[2 * n + i];
-    double best = 0.0;
-    for (int v = 0; v < vt.n_views; ++v) {
-        const ViewK& V = vt.v[v];
-        const double tz = (double)V.R[6] * m0 + (double)V.R[7] * m1 + (double)V.R[8] * m2 + (double)V.t[2];
-        if (!(tz >= (double)V.znear && tz <= (double)V.zfar)) continue;
-        const double tx = (double)V.R[0] * m0 + (double)V.R[1] * m1 + (double)V.R[2] * m2 + (double)V.t[0];
-        const double ty = (double)V.R[3] * m0 + (double)V.R[4] * m1 + (double)V.R[5] * m2 + (double)V.t[1];
-        // x / z within [ulo, uhi] as products (z >= near > 0): one division per camera
-        if (tx >= V.ulo * tz && tx <= V.uhi * tz && ty >= V.vlo * tz && ty <= V.vhi * tz)
-            best = fmax(best, (double)V.fx / tz);
+    const int64_t i0 = (int64_t)blockIdx.x * (kDT * kRatePer) + threadIdx.x;
+    double m[kRatePer][3], best[kRatePer];
+#pragma unroll
+    for (int j = 0; j < kRatePer; ++j) {
+        const int64_t i = i0 + j * kDT < n ? i0 + j * kDT : n - 1;      // (no branch between the loads)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m[j][c] = (double)means[c * n + i];
+        best[j] = __builtin_huge_val();
     }
-    const float r = (float)best;
-    rate[i] = accumulate ? fmaxf(rate[i], r) : r;
+    for (int v = 0; v < tab.n_cams; ++v) {
+        const RateCam& C = tab.c[v];
+#pragma unroll
+        for (int j = 0; j < kRatePer; ++j) {
+            const double x = fma(C.R[2], m[j][2], fma(C.R[1], m[j][1], C.R[0] * m[j][0])) + C.t[0];
+            const double y = fma(C.R[5], m[j][2], fma(C.R[4], m[j][1], C.R[3] * m[j][0])) + C.t[1];
+            const double z = fma(C.R[8], m[j][2], fma(C.R[7], m[j][1], C.R[6] * m[j][0])) + C.t[2];
+            const double ex = fma(C.hu, z, -fabs(fma(-C.cu, z, x))), ey = fma(C.hv, z, -fabs(fma(-C.cv, z, y)));
+            const double s = z * C.ifx;
+            if (s < best[j] && z >= C.znear && z <= C.zfar && ex >= 0.0 && ey >= 0.0) best[j] = s;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kRatePer; ++j) {
+        const int64_t i = i0 + j * kDT;
+        if (i >= n) continue;
+        const float r = (float)(1.0 / best[j]);      // 0 where no camera holds the mean
+        rate[i] = accumulate ? fmaxf(rate[i], r) : r;
+    }
 }
 
 // filter variance (s_f / rate)^2, 0 for an unseen Gaussian
@@ -220,9 +238,11 @@ hipError_t launch_dens_mark(const uint32_t* sidx, uint32_t k, const uint32_t* ca
     return hipGetLastError();
 }
 
-hipError_t launch_filter_rate(const float* means, int64_t n, const ViewTable& vt, bool accumulate, float* rate,
+hipError_t launch_filter_rate(const float* means, int64_t n, const RateTable& tab, bool accumulate, float* rate,
                               hipStream_t s) {
-    hipLaunchKernelGGL(k_filter_rate, dim3(blocks_of(n)), dim3(kDT), 0, s, means, n, vt, accumulate ? 1 : 0, rate);
+    const int64_t per = kDT * kRatePer;
+    hipLaunchKernelGGL(k_filter_rate, dim3((unsigned)((n + per - 1) / per)), dim3(kDT), 0, s, means, n, tab,
+                       accumulate ? 1 : 0, rate);
     return hipGetLastError();
 }
 

@@ -129,12 +129,31 @@ int gs_filter3d_rate(const float* means, int64_t n, const gs_camera* cams, int32
         GS_REQUIRE(n >= 1, "n=%lld must be >= 1", (long long)n);
         GS_REQUIRE(means && rate && cams, "NULL argument");
         GS_REQUIRE(n_cams >= 1, "need at least one camera");
+        RateTable tab = {};
+        bool started = false;
         for (int32_t b = 0; b < n_cams; b += GS_MAX_VIEWS) {
             const int32_t m = n_cams - b < GS_MAX_VIEWS ? n_cams - b : GS_MAX_VIEWS;
             ViewTable vt;
             int rc = build_views(cams + b, m, &vt);
             if (rc) return rc;
-            GS_HIP(launch_filter_rate(means, n, vt, b > 0, rate, (hipStream_t)stream));
+            for (int32_t v = 0; v < m; ++v) {
+                const ViewK& V = vt.v[v];
+                RateCam& C = tab.c[tab.n_cams++];
+                for (int k = 0; k < 9; ++k) C.R[k] = V.R[k];
+                for (int k = 0; k < 3; ++k) C.t[k] = V.t[k];
+                C.cu = 0.5 * (V.ulo + V.uhi);
+                C.hu = 0.5 * (V.uhi - V.ulo);
+                C.cv = 0.5 * (V.vlo + V.vhi);
+                C.hv = 0.5 * (V.vhi - V.vlo);
+                C.znear = V.znear;
+                C.zfar = V.zfar;
+                C.ifx = 1.0 / (double)V.fx;
+                if (tab.n_cams == kRateCams || b + v + 1 == n_cams) {
+                    GS_HIP(launch_filter_rate(means, n, tab, started, rate, (hipStream_t)stream));
+                    started = true;
+                    tab.n_cams = 0;
+                }
+            }
         }
         return GS_OK;
     } catch (...) {

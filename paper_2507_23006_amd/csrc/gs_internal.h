@@ -344,7 +344,17 @@ hipError_t launch_dens_compact(const uint32_t* cand, const uint32_t* pos, const 
                                uint32_t* ckey, uint32_t* cidx, hipStream_t s);
 hipError_t launch_dens_mark(const uint32_t* sidx, uint32_t k, const uint32_t* cand, bool all, const float* scales,
                             int64_t n, float split_scale, uint8_t* action, hipStream_t s);
-hipError_t launch_filter_rate(const float* means, int64_t n, const ViewTable& vt, bool accumulate, float* rate,
+// cameras of one k_filter_rate launch (a kernel's arguments hold 4 KB): image
+// bounds as |x / z - cu| <= hu, |y / z - cv| <= hv; ifx = 1 / fx
+struct RateCam {
+    double R[9], t[3], cu, hu, cv, hv, znear, zfar, ifx;
+};
+constexpr int kRateCams = 24;
+struct RateTable {
+    RateCam c[kRateCams];
+    int32_t n_cams;
+};
+hipError_t launch_filter_rate(const float* means, int64_t n, const RateTable& tab, bool accumulate, float* rate,
                               hipStream_t s);
 hipError_t launch_filter_fwd(const float* scales, const float* opac, const float* rate, int64_t n, float s_f,
                              float* scales_out, float* opac_out, hipStream_t s);
