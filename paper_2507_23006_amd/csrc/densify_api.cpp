@@ -10,33 +10,23 @@ using namespace gs::host;
 
 namespace {
 
-struct DensWs {
-    uint32_t *cand, *pos, *pruned, *ppos, *key, *ckey, *cidx, *ckey_alt, *cidx_alt, *hist, *scan_tmp;
-    unsigned long long* total;   // [0] candidates, [8] pruned (separate 64-byte lines)
-};
-
-size_t dens_layout(int64_t n, void* base, DensWs* w) {
-    const uint32_t N = (uint32_t)(n < 1 ? 1 : n);
+size_t dens_layout(int64_t n, void* base, DensSelect* w) {
+    const int64_t N = n < 1 ? 1 : n;
     Carver c(base);
-    w->cand = c.take<uint32_t>(N);
-    w->pos = c.take<uint32_t>(N);
-    w->pruned = c.take<uint32_t>(N);
-    w->ppos = c.take<uint32_t>(N);
-    w->key = c.take<uint32_t>(N);
-    w->ckey = c.take<uint32_t>(N);
-    w->cidx = c.take<uint32_t>(N);
-    w->ckey_alt = c.take<uint32_t>(N);
-    w->cidx_alt = c.take<uint32_t>(N);
-    w->hist = c.take<uint32_t>(radix_hist_elems(N));
-    w->scan_tmp = c.take<uint32_t>(scan_tmp_elems(N));
-    w->total = c.take<unsigned long long>(16);
+    w->cand = c.take<uint2>(dens_cand_elems(N));
+    w->counts = c.take<uint2>(dens_blocks(N));
+    w->ties = c.take<uint32_t>(dens_blocks(N));
+    w->hist = c.take<uint32_t>(dens_hist_elems());
+    w->sel = c.take<char>(dens_sel_bytes());
     return c.off;
 }
 
+// the calling thread's two totals, written by a kernel and read after the
+// stream has run
 unsigned long long* pinned_pair() {
     thread_local unsigned long long* p = nullptr;
-    if (!p && hipHostMalloc(reinterpret_cast<void**>(&p), 16 * sizeof(unsigned long long), hipHostMallocDefault) !=
-                  hipSuccess)
+    if (!p && hipHostMalloc(reinterpret_cast<void**>(&p), 2 * sizeof(unsigned long long),
+                            hipHostMallocMapped | hipHostMallocPortable) != hipSuccess)
         p = nullptr;
     return p;
 }
@@ -64,7 +54,7 @@ int gs_densify_accumulate(const uint32_t* tiles, const float* grad_norm, const f
 }
 
 size_t gs_densify_workspace_size(int64_t n) {
-    DensWs w;
+    DensSelect w;
     return dens_layout(n, nullptr, &w);
 }
 
@@ -80,7 +70,7 @@ int gs_densify_select(const float* accum, const int32_t* count, const float* mea
         GS_REQUIRE(p->budget >= 0, "budget must be >= 0");
         for (int k = 0; k < 3; ++k) GS_REQUIRE(p->box_min[k] <= p->box_max[k], "empty partition box");
         hipStream_t s = (hipStream_t)stream;
-        DensWs w;
+        DensSelect w;
         dens_layout(n, ws, &w);
         DensParams dp;
         for (int k = 0; k < 3; ++k) {
@@ -91,28 +81,16 @@ int gs_densify_select(const float* accum, const int32_t* count, const float* mea
         dp.eta = p->eta;
         dp.d_max = p->d_max;
         dp.prune_opacity = p->prune_opacity;
-        const uint32_t N = (uint32_t)n;
-        GS_HIP(launch_dens_classify(accum, count, means, opacities, n, dp, action, w.cand, w.pruned, w.key, s));
-        GS_HIP(exclusive_scan_u32(w.cand, w.pos, N, w.scan_tmp, w.total, s));
-        GS_HIP(exclusive_scan_u32(w.pruned, w.ppos, N, w.scan_tmp, w.total + 8, s));
         unsigned long long* host = pinned_pair();
         if (!host) return fail(GS_ERR_HIP, "pinned host buffer unavailable");
-        GS_HIP(hipMemcpyAsync(host, w.total, 16 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+        GS_HIP(launch_dens_classify(accum, count, means, opacities, n, dp, action, w, host, s));
         GS_HIP(hipStreamSynchronize(s));
-        const int64_t E = (int64_t)host[0], pruned = (int64_t)host[8];
+        const int64_t E = (int64_t)host[0], pruned = (int64_t)host[1];
         if (E > n || pruned > n) return fail(GS_ERR_INTERNAL, "inconsistent totals");
         int64_t K = p->budget - (n - pruned);
         if (K < 0) K = 0;
         const int64_t grown = K < E ? K : E;
-        if (grown == E && E > 0) {
-            GS_HIP(launch_dens_mark(nullptr, 0, w.cand, true, scales, n, p->split_scale, action, s));
-        } else if (grown > 0) {
-            GS_HIP(launch_dens_compact(w.cand, w.pos, w.key, n, w.ckey, w.cidx, s));
-            bool alt = false;
-            GS_HIP(radix_sort_pairs(w.ckey, w.cidx, w.ckey_alt, w.cidx_alt, (uint32_t)E, 0, 32, w.hist, s, &alt));
-            GS_HIP(launch_dens_mark(alt ? w.cidx_alt : w.cidx, (uint32_t)grown, nullptr, false, scales, n,
-                                    p->split_scale, action, s));
-        }
+        if (grown > 0) GS_HIP(launch_dens_grow(w, (uint32_t)grown, grown == E, scales, n, p->split_scale, action, s));
         counts[0] = E;
         counts[1] = pruned;
         counts[2] = grown;

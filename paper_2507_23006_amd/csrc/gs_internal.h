@@ -202,11 +202,9 @@ hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, 
                             bool* result_in_alt, const uint32_t* n_dev = nullptr, bool small_tiles = false,
                             bool vals_are_positions = false);
 size_t scan_tmp_elems(uint32_t n);
-hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                              unsigned long long* total, hipStream_t s);
-// the same without a total, with the sums of every kScanTileElems elements
-// given (written by the kernel that wrote the elements); the elements count
-// items, and chunk_first[c] gets the element that holds item c * chunk
+// exclusive scan, with the sums of every kScanTileElems elements given (written
+// by the kernel that wrote the elements); the elements count items, and
+// chunk_first[c] gets the element that holds item c * chunk
 constexpr int kScanTileElems = 2048;
 hipError_t exclusive_scan_sums_u32(const uint32_t* in, uint32_t* out, uint32_t n, const uint32_t* n_dev,
                                    const uint32_t* tile_sums, uint32_t* chunk_first, uint32_t chunk, hipStream_t s);
@@ -337,13 +335,25 @@ struct DensParams {
 hipError_t launch_dens_accumulate(const uint32_t* tiles, const float* grad_norm, const float* absgrad,
                                   int32_t n_views, int64_t n, const DensViewScale& sc, float* accum, int32_t* count,
                                   hipStream_t s);
+// scratch of the budgeted selection over n Gaussians
+struct DensSelect {
+    uint2* cand;          // [dens_cand_elems(n)] (key, index)
+    uint2* counts;        // [dens_blocks(n)] candidates, pruned
+    uint32_t* ties;       // [dens_blocks(n)]
+    uint32_t* hist;       // [dens_hist_elems()]
+    void* sel;            // dens_sel_bytes()
+};
+uint32_t dens_blocks(int64_t n);
+size_t dens_cand_elems(int64_t n);
+size_t dens_hist_elems();
+size_t dens_sel_bytes();
+// total[2], host-visible: candidates, pruned
 hipError_t launch_dens_classify(const float* accum, const int32_t* count, const float* means, const float* opac,
-                                int64_t n, const DensParams& p, uint8_t* action, uint32_t* cand, uint32_t* pruned,
-                                uint32_t* key, hipStream_t s);
-hipError_t launch_dens_compact(const uint32_t* cand, const uint32_t* pos, const uint32_t* key, int64_t n,
-                               uint32_t* ckey, uint32_t* cidx, hipStream_t s);
-hipError_t launch_dens_mark(const uint32_t* sidx, uint32_t k, const uint32_t* cand, bool all, const float* scales,
-                            int64_t n, float split_scale, uint8_t* action, hipStream_t s);
+                                int64_t n, const DensParams& p, uint8_t* action, const DensSelect& w,
+                                unsigned long long* total, hipStream_t s);
+// marks the `grown` candidates with the largest scores (equal ones in index order), or all
+hipError_t launch_dens_grow(const DensSelect& w, uint32_t grown, bool all, const float* scales, int64_t n,
+                            float split_scale, uint8_t* action, hipStream_t s);
 // cameras of one k_filter_rate launch (a kernel's arguments hold 4 KB): image
 // bounds as |x / z - cu| <= hu, |y / z - cv| <= hv; ifx = 1 / fx
 struct RateCam {

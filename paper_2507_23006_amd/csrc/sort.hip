@@ -296,40 +296,19 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
     return x;
 }
 
-// tile sums
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ in, uint32_t n,
-                                                              uint32_t* __restrict__ tsum) {
-    __shared__ uint32_t s_w[4];
-    const uint32_t base = blockIdx.x * kScanTile;
-    uint32_t acc = 0;
-#pragma unroll
-    for (int r = 0; r < kScanIpt; ++r) {
-        const uint32_t idx = base + r * kScanThreads + threadIdx.x;
-        acc += idx < n ? in[idx] : 0u;
-    }
-    const uint32_t w = wave_incl_scan(acc);
-    if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = w;
-    __syncthreads();
-    if (threadIdx.x == 0) tsum[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-}
-
 // per-tile exclusive scan plus the tile's offset; items are blocked per
 // thread (consecutive) so that the in-thread prefix is sequential.  The
 // tile's offset is the sum of the earlier tiles' sums, which every
 // workgroup adds up itself (64-bit, at most a few thousand values) rather
-// than waiting for a separate one-workgroup launch; the last workgroup
-// that holds elements (the first, for none) writes the 64-bit total.
+// than waiting for a separate one-workgroup launch.
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* __restrict__ in,
                                                             uint32_t* __restrict__ out, uint32_t n_max,
                                                             const uint32_t* __restrict__ n_dev,
                                                             const uint32_t* __restrict__ tsum,
-                                                            unsigned long long* __restrict__ total,
                                                             uint32_t* __restrict__ chunk_first, uint32_t chunk) {
     __shared__ uint32_t s_buf[kScanTile];
     const uint32_t n = count_of(n_max, n_dev);
-    const uint32_t n_act = (uint32_t)(((uint64_t)n + kScanTile - 1) / kScanTile);
-    const uint32_t last_wg = n_act > 0 ? n_act - 1 : 0;
-    if (blockIdx.x > last_wg) return;
+    if ((uint64_t)blockIdx.x * kScanTile >= n) return;
     __shared__ uint32_t s_w[4];
     __shared__ unsigned long long s_off[4];
     const uint32_t base = blockIdx.x * kScanTile;
@@ -357,15 +336,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* __re
     if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = incl;
     __syncthreads();
     const unsigned long long tile_off = s_off[0] + s_off[1] + s_off[2] + s_off[3];
-    if (blockIdx.x == last_wg && threadIdx.x == 0 && total)
-        *total = tile_off + s_w[0] + s_w[1] + s_w[2] + s_w[3];
     uint32_t pre = (uint32_t)tile_off + incl - acc;
     for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) pre += s_w[w];
 #pragma unroll
     for (int r = 0; r < kScanIpt; ++r) {
         s_buf[threadIdx.x * kScanIpt + r] = pre;
         // the chunks of the counted items that start in this element's
-        if (chunk_first && v[r])
+        if (v[r])
             for (uint32_t c = (pre + chunk - 1) / chunk; c <= (pre + v[r] - 1) / chunk; ++c)
                 chunk_first[c] = base + threadIdx.x * kScanIpt + r;
         pre += v[r];
@@ -406,25 +383,12 @@ hipError_t fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                              unsigned long long* total, hipStream_t s) {
-    const uint32_t nt = (uint32_t)(((uint64_t)n + kScanTile - 1) / kScanTile);
-    if (n == 0) {
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t*)total, 0u, (size_t)2);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nt), dim3(kScanThreads), 0, s, in, n, tmp);
-    hipLaunchKernelGGL(k_scan_down, dim3(nt), dim3(kScanThreads), 0, s, in, out, n, (const uint32_t*)nullptr, tmp,
-                       total, (uint32_t*)nullptr, 1u);
-    return hipGetLastError();
-}
-
 hipError_t exclusive_scan_sums_u32(const uint32_t* in, uint32_t* out, uint32_t n, const uint32_t* n_dev,
                                    const uint32_t* tile_sums, uint32_t* chunk_first, uint32_t chunk, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const uint32_t nt = (uint32_t)(((uint64_t)n + kScanTile - 1) / kScanTile);
     hipLaunchKernelGGL(k_scan_down, dim3(nt), dim3(kScanThreads), 0, s, in, out, n, n_dev, tile_sums,
-                       (unsigned long long*)nullptr, chunk_first, chunk);
+                       chunk_first, chunk);
     return hipGetLastError();
 }
 
