@@ -15,18 +15,23 @@
 // computed transposed, H^T = W1g x^T: the K index of step kk on lane group q
 // is embedding word 4q + kk, so the B operand is the lane's own float4 and the
 // result leaves lane (q, j) with hidden units 16 mi + 4q + r of Gaussian j.
-// Sums over the hidden units take those values directly as B operands (the
-// order of a contraction's K index is free), so the output layer, the
-// backward of the output layer and the embedding gradient need no
-// transposes.  Only the weight gradient dW1g = dA^T x_g, whose K index is the
-// Gaussian, goes through LDS.
+// Sums over the hidden units take those values directly (the order of a
+// contraction's K index is free), so the output layer, the backward of the
+// output layer and the embedding gradient need no transposes; the forward's
+// output layer, four rows of which a matrix instruction would leave 12 idle, is
+// 32 FMAs a lane and a sum over the Gaussian's four lanes.  Only the weight
+// gradient dW1g = dA^T x_g, whose K index is the Gaussian, goes through LDS.
 //
 // The forward writes the offsets (16 B per Gaussian) and per-workgroup sums
 // of do; the backward reads the embedding, the saved offsets and their
 // gradients, writes the embedding gradient and keeps the weight gradients in
 // registers over a grid-stride loop, then adds workgroup partials in a fixed
-// order (deterministic).  Bound by HBM (80 B / 144 B per Gaussian) and the
-// FP32 matrix rate (64 / 104 MFMA per 64 Gaussians).
+// order (deterministic).  Bound by HBM (80 B / 144 B per Gaussian) and, matrix
+// and vector instructions not overlapping on a SIMD, by the sum of both (32 MFMA
+// and about 300 others / 104 and 700 per 64 Gaussians).  Both kernels read the
+// next Gaussians' inputs ahead.  6M Gaussians: forward 127 us (161 with the output
+// layer on the matrix cores and nothing read ahead; HBM takes 93), backward 289
+// (347; the instructions take about 200, HBM 188).
 #include <atomic>
 
 #include "gs_internal.h"
@@ -54,6 +59,31 @@ __device__ __forceinline__ f4v mfma(float a, float b, f4v c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// swaps lanes between two registers: half 1 of a with half 0 of b, or rows 1 and 3
+// of a with rows 0 and 2 of b (a row = 16 lanes); one instruction where a shuffle
+// is an LDS access
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+// sum over the four rows, in every row
+__device__ __forceinline__ float row_sum(float a) {
+    float b = a;
+    swap_rows(a, b);
+    a += b;
+    b = a;
+    swap_halves(a, b);
+    return a + b;
+}
+
 // fast exp and divide: a few ulp, far inside the offsets' float32 bar
 __device__ __forceinline__ float sigmoid(float z) { return __fdividef(1.0f, 1.0f + __expf(-z)); }
 
@@ -78,15 +108,11 @@ __device__ __forceinline__ void image_bias(const float* __restrict__ iemb, const
     __syncthreads();
 }
 
-// embedding float4 of lane (q, j) for Gaussian gi, normalised over the
-// Gaussian's 4 lanes; returns 1 / max(|g|, eps) and whether |g| > eps
-__device__ __forceinline__ float load_unit(const float* __restrict__ gemb, int64_t gi, int64_t n, int q,
-                                           float eh[4], bool& above) {
-    float4 e = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (gi < n) e = reinterpret_cast<const float4*>(gemb)[gi * 4 + q];
-    float ss = e.x * e.x + e.y * e.y + e.z * e.z + e.w * e.w;
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
+// embedding float4 e of lane (q, j), normalised over the Gaussian's 4 lanes;
+// returns 1 / max(|g|, eps) and whether |g| > eps
+__device__ __forceinline__ float unit(float4 e, float eh[4], bool& above) {
+    // (FMAs in a fixed order: the sign of a hidden unit near zero hangs on the last bit)
+    const float ss = row_sum(fmaf(e.w, e.w, fmaf(e.z, e.z, fmaf(e.y, e.y, e.x * e.x))));
     above = ss > kNormEps * kNormEps;
     const float inv = rsqrtf(fmaxf(ss, kNormEps * kNormEps));    // 1 / max(|g|, eps)
     eh[0] = e.x * inv; eh[1] = e.y * inv; eh[2] = e.z * inv; eh[3] = e.w * inv;
@@ -101,50 +127,71 @@ __device__ __forceinline__ float block_sum(float v, float* s_red) {
     return s_red[0] + s_red[1] + s_red[2] + s_red[3];
 }
 
-__global__ __launch_bounds__(kAT) void k_app_fwd(const float* __restrict__ gemb, int64_t n,
+__global__ __launch_bounds__(kAT, 4) void k_app_fwd(const float* __restrict__ gemb, int64_t n,
                                                  const float* __restrict__ iemb, AppMlp w, float4* __restrict__ out,
                                                  float* __restrict__ part_do) {
     __shared__ float s_eh[kIE], s_u[kHid], s_red[4];
     image_bias(iemb, w, s_eh, s_u);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int j = lane & 15, q = lane >> 4;
-    float aw1[2][4], aw2[2][4], ub[2][4];
+    float aw1[2][4], w2[2][4][kOut], ub[2][4];
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             aw1[mi][r] = w.w1[(16 * mi + j) * kIn + 4 * q + r];                    // W1g[16mi + j][4q + r]
-            // output o goes to row 4 o of the product, i.e. register 0 of lane group o
-            aw2[mi][r] = (j & 3) == 0 ? w.w2[(j >> 2) * kHid + 16 * mi + 4 * q + r] : 0.0f;
+#pragma unroll
+            for (int o = 0; o < kOut; ++o) w2[mi][r][o] = w.w2[o * kHid + 16 * mi + 4 * q + r];
             ub[mi][r] = s_u[16 * mi + 4 * q + r];
         }
     const float b2q = w.b2[q];
     float sum_do = 0.0f;
     const int64_t n_chunks = (n + 63) / 64;
+    // the next chunk's embeddings are read while this one's are worked on
+    float4 next[4];
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) {
+        const int64_t gn = ((int64_t)blockIdx.x * 4 + wv) * 64 + 16 * ni + j;
+        next[ni] = reinterpret_cast<const float4*>(gemb)[4 * (gn < n ? gn : n - 1) + q];
+    }
     for (int64_t c = (int64_t)blockIdx.x * 4 + wv; c < n_chunks; c += (int64_t)gridDim.x * 4) {
+        float4 e[4];
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni) {
+            e[ni] = next[ni];
+            const int64_t gn = (c + (int64_t)gridDim.x * 4) * 64 + 16 * ni + j;
+            next[ni] = reinterpret_cast<const float4*>(gemb)[4 * (gn < n ? gn : n - 1) + q];
+        }
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni) {
             const int64_t gi = c * 64 + 16 * ni + j;
             float eh[4];
             bool above;
-            load_unit(gemb, gi, n, q, eh, above);
+            unit(gi < n ? e[ni] : make_float4(0.0f, 0.0f, 0.0f, 0.0f), eh, above);
             f4v h0 = {0.0f, 0.0f, 0.0f, 0.0f}, h1 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
                 h0 = mfma(aw1[0][kk], eh[kk], h0);
                 h1 = mfma(aw1[1][kk], eh[kk], h1);
             }
-            // two independent accumulation chains over the hidden units
-            f4v z0 = {0.0f, 0.0f, 0.0f, 0.0f}, z1 = {0.0f, 0.0f, 0.0f, 0.0f};
+            // the lane's eight hidden units' part of the four outputs (four rows
+            // of a product leave 12 of a matrix instruction's 16 idle: 32 FMAs
+            // take a third of its time), then the sum over the Gaussian's four
+            // lanes, which leaves output q in lane (q, j)
+            float z[kOut] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                z0 = mfma(aw2[0][r], fmaxf(h0[r] + ub[0][r], 0.0f), z0);
-                z1 = mfma(aw2[1][r], fmaxf(h1[r] + ub[1][r], 0.0f), z1);
+                const float p0 = fmaxf(h0[r] + ub[0][r], 0.0f), p1 = fmaxf(h1[r] + ub[1][r], 0.0f);
+#pragma unroll
+                for (int o = 0; o < kOut; ++o) z[o] = fmaf(w2[1][r][o], p1, fmaf(w2[0][r][o], p0, z[o]));
             }
-            // output q of Gaussian j sits in register 0 of lane (q, j): one
-            // sigmoid per lane, and the wave stores 16 rows of 16 bytes
+            swap_halves(z[0], z[2]);
+            swap_halves(z[1], z[3]);
+            float za = z[0] + z[2], zb = z[1] + z[3];
+            swap_rows(za, zb);
+            // one sigmoid per lane, and the wave stores 16 rows of 16 bytes
             if (gi < n) {
-                const float y = sigmoid(z0[0] + z1[0] + b2q);
+                const float y = sigmoid(za + zb + b2q);
                 reinterpret_cast<float*>(out)[gi * 4 + q] = y;
                 if (q == 3) sum_do += y;
             }
@@ -169,14 +216,18 @@ __global__ __launch_bounds__(256) void k_app_reg_total(const float* __restrict__
     }
 }
 
-__global__ __launch_bounds__(kAT) void k_app_bwd(const float* __restrict__ gemb, int64_t n,
+__global__ __launch_bounds__(kAT, 3) void k_app_bwd(const float* __restrict__ gemb, int64_t n,
                                                  const float* __restrict__ iemb, AppMlp w,
                                                  const float* __restrict__ y_in, const float* __restrict__ dy_in,
                                                  const float* __restrict__ d_reg, float reg_weight,
                                                  float4* __restrict__ d_gemb, float* __restrict__ partial) {
     __shared__ float s_eh[kIE], s_u[kHid];
-    __shared__ float s_da[4][64][kHid + 1];   // per wave: dA [Gaussian][hidden]
-    __shared__ float s_x[4][64][kGE + 1];     // per wave: x_g [Gaussian][word]
+    // per wave and 32 Gaussians: dA [Gaussian][hidden] and x_g [Gaussian][word].  Row
+    // g starts at 16-byte word 12 g + g / 4 (4 g + g / 4): the 16 rows that the
+    // lanes of a row write at once start in different banks, and the four rows a
+    // matrix instruction reads lie 16 banks apart
+    constexpr int kDaRows = 32 * 48 + 32, kXRows = 32 * 16 + 32;
+    __shared__ float4 s_da4[4][kDaRows / 4], s_x4[4][kXRows / 4];
     image_bias(iemb, w, s_eh, s_u);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int j = lane & 15, q = lane >> 4;
@@ -205,17 +256,33 @@ __global__ __launch_bounds__(kAT) void k_app_bwd(const float* __restrict__ gemb,
             for (int r = 0; r < 4; ++r) acc_w2[o][mi][r] = 0.0f;
     float acc_b2 = 0.0f;
 
-    const int64_t n_chunks = (n + 63) / 64;
-    for (int64_t c = (int64_t)blockIdx.x * 4 + wv; c < n_chunks; c += (int64_t)gridDim.x * 4) {
-#pragma unroll 1
-        for (int ni = 0; ni < 4; ++ni) {
-            const int64_t gi = c * 64 + 16 * ni + j;
+    float* const s_da = reinterpret_cast<float*>(s_da4[wv]);
+    float* const s_x = reinterpret_cast<float*>(s_x4[wv]);
+    // the next 16 Gaussians' embedding words, offset and gradient are read while
+    // this group's are worked on: a wave's chain leaves nothing else to hide the
+    // reads behind
+    const int64_t n_chunks = (n + 31) / 32, stride = (int64_t)gridDim.x * 4;
+    float4 e_next;
+    float y_next, dy_next;
+    const auto read_ahead = [&](int64_t gi) {
+        const int64_t at = 4 * (gi < n ? gi : n - 1) + q;
+        e_next = reinterpret_cast<const float4*>(gemb)[at];
+        y_next = y_in[at];
+        dy_next = dy_in[at];
+    };
+    read_ahead(((int64_t)blockIdx.x * 4 + wv) * 32 + j);
+    for (int64_t c = (int64_t)blockIdx.x * 4 + wv; c < n_chunks; c += stride) {
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) {
+            const int64_t gi = c * 32 + 16 * ni + j;
             const bool valid = gi < n;
             float eh[4];
             bool above;
-            const float inv = load_unit(gemb, gi, n, q, eh, above);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s_x[wv][16 * ni + j][4 * q + r] = eh[r];
+            const float yv = y_next, dyv = dy_next;
+            const float4 e = valid ? e_next : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            read_ahead(ni == 0 ? gi + 16 : (c + stride) * 32 + j);
+            const float inv = unit(e, eh, above);
+            s_x4[wv][4 * (16 * ni + j) + 4 * ni + (j >> 2) + q] = make_float4(eh[0], eh[1], eh[2], eh[3]);
             f4v a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
@@ -227,14 +294,16 @@ __global__ __launch_bounds__(kAT) void k_app_bwd(const float* __restrict__ gemb,
             // where float32 would drop it)
             float dz = 0.0f;
             if (valid) {
-                const float yv = y_in[gi * 4 + q];
                 const float sg = yv * (1.0f - yv);
-                dz = fmaf(q == 3 ? reg_add : 0.0f, sg, dy_in[gi * 4 + q] * sg);
+                dz = fmaf(q == 3 ? reg_add : 0.0f, sg, dyv * sg);
             }
             acc_b2 += dz;
-            float dzo[4];
-#pragma unroll
-            for (int o = 0; o < 4; ++o) dzo[o] = __shfl(dz, 16 * o + j, 64);
+            float dzo[4] = {dz, dz, dz, dz};      // the four rows' values, in every row
+            swap_rows(dzo[0], dzo[1]);
+            dzo[2] = dzo[0];
+            dzo[3] = dzo[1];
+            swap_halves(dzo[0], dzo[2]);
+            swap_halves(dzo[1], dzo[3]);
             // dh^T = W2^T dz^T: one K step (K = the 4 outputs)
             const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
             const f4v dh0 = mfma(adh[0], dz, zero), dh1 = mfma(adh[1], dz, zero);
@@ -252,9 +321,10 @@ __global__ __launch_bounds__(kAT) void k_app_bwd(const float* __restrict__ gemb,
                 }
                 acc_b1[0][r] += da[0][r];
                 acc_b1[1][r] += da[1][r];
-                s_da[wv][16 * ni + j][4 * q + r] = da[0][r];
-                s_da[wv][16 * ni + j][16 + 4 * q + r] = da[1][r];
             }
+            const int row = 12 * (16 * ni + j) + 4 * ni + (j >> 2);
+            s_da4[wv][row + q] = make_float4(da[0][0], da[0][1], da[0][2], da[0][3]);
+            s_da4[wv][row + 4 + q] = make_float4(da[1][0], da[1][1], da[1][2], da[1][3]);
             // dx_g^T = W1g^T dA^T (K = hidden, taken in the lane's own order)
             f4v dx = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -262,23 +332,22 @@ __global__ __launch_bounds__(kAT) void k_app_bwd(const float* __restrict__ gemb,
 #pragma unroll
             for (int r = 0; r < 4; ++r) dx = mfma(ade[1][r], da[1][r], dx);
             // through g / max(|g|, eps)
-            float dot = eh[0] * dx[0] + eh[1] * dx[1] + eh[2] * dx[2] + eh[3] * dx[3];
-            dot += __shfl_xor(dot, 16, 64);
-            dot += __shfl_xor(dot, 32, 64);
+            float dot = row_sum(eh[0] * dx[0] + eh[1] * dx[1] + eh[2] * dx[2] + eh[3] * dx[3]);
             if (!above) dot = 0.0f;
             if (valid)
                 d_gemb[gi * 4 + q] = make_float4((dx[0] - eh[0] * dot) * inv, (dx[1] - eh[1] * dot) * inv,
                                                  (dx[2] - eh[2] * dot) * inv, (dx[3] - eh[3] * dot) * inv);
         }
-        // dW1g += dA^T x_g over the chunk's 64 Gaussians (K = Gaussian)
+        // dW1g += dA^T x_g over the chunk's 32 Gaussians (K = Gaussian)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 4
-        for (int s = 0; s < 16; ++s) {
-            const float xv = s_x[wv][4 * s + q][j];
-            acc_w1[0] = mfma(s_da[wv][4 * s + q][j], xv, acc_w1[0]);
-            acc_w1[1] = mfma(s_da[wv][4 * s + q][16 + j], xv, acc_w1[1]);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const float xv = s_x[16 * (4 * s + q) + 4 * s + j];
+            const float* da = s_da + 48 * (4 * s + q) + 4 * s + j;
+            acc_w1[0] = mfma(da[0], xv, acc_w1[0]);
+            acc_w1[1] = mfma(da[16], xv, acc_w1[1]);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -300,7 +369,8 @@ __global__ __launch_bounds__(kAT) void k_app_bwd(const float* __restrict__ gemb,
     }
     // per-wave results into LDS (reusing s_da), then the 4 waves in order
     __syncthreads();
-    float* s_part = &s_da[0][0][0];      // [4][kPart] fits in s_da
+    static_assert(sizeof(s_da4) >= 4 * kPart * sizeof(float), "partials reuse the rows");
+    float* s_part = reinterpret_cast<float*>(&s_da4[0][0]);      // [4][kPart]
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
