@@ -153,6 +153,8 @@ _lib = None
 def load() -> C.CDLL:
     """Loads libgs.so; raises if it has not been built (there is no fallback)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -178,7 +180,8 @@ def make_cameras(cams) -> C.Array:
     arr = (GsCamera * len(cams))()
     for i, c in enumerate(cams):
         arr[i].fx, arr[i].fy, arr[i].cx, arr[i].cy = float(c.fx), float(c.fy), float(c.cx), float(c.cy)
-        vm = [float(x) for row in c.viewmat for x in row]
+        m = c.viewmat.tolist() if hasattr(c.viewmat, "tolist") else c.viewmat     # one call for an array or a tensor
+        vm = [float(x) for row in m for x in row]
         for k in range(16):
             arr[i].viewmat[k] = vm[k]
         arr[i].width, arr[i].height = int(c.width), int(c.height)

@@ -36,7 +36,8 @@ def _ptr(t):
 
 
 def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current device's current stream, without building a Stream object
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _check_param(t: torch.Tensor, name: str, shape) -> None:
@@ -111,12 +112,35 @@ class Projected:
         return p
 
 
+class _Views(list):
+    """The cameras of one call, with their C array and extent computed once
+    for its stages (a training step converted each camera eight times, a
+    quarter of the host time of a small one).  Made per call and never kept
+    for another."""
+
+    _c = _extent = None
+
+    @property
+    def c(self):
+        if self._c is None:
+            self._c = L.make_cameras(self)
+        return self._c
+
+    @property
+    def extent(self) -> tuple:
+        if self._extent is None:
+            nt, npx = C.c_int64(), C.c_int64()
+            L.check(L.load().gs_views_extent(self.c, len(self), C.byref(nt), C.byref(npx)))
+            self._extent = (nt.value, npx.value)
+        return self._extent
+
+
+def _views(cams) -> _Views:
+    return cams if isinstance(cams, _Views) else _Views(cams)
+
+
 def views_extent(cams) -> tuple:
-    lib = L.load()
-    arr = L.make_cameras(cams)
-    nt, npx = C.c_int64(), C.c_int64()
-    L.check(lib.gs_views_extent(arr, len(cams), C.byref(nt), C.byref(npx)))
-    return nt.value, npx.value
+    return _views(cams).extent
 
 
 def project(means, scales, quats, opacities, sh, cams, opts: RenderOptions, app=None,
@@ -126,9 +150,10 @@ def project(means, scales, quats, opacities, sh, cams, opts: RenderOptions, app=
     lib = L.load()
     n = check_params(means, scales, quats, opacities, sh)
     check_app(app, n)
+    cams = _views(cams)
     S = n * len(cams)
     dev = means.device
-    n_tiles, _ = views_extent(cams)
+    n_tiles, _ = cams.extent
     out = Projected(torch.empty((S, L.REC_FLOATS), dtype=torch.float32, device=dev),
                     torch.empty((S, 2), dtype=torch.int32, device=dev),
                     torch.empty((S,), dtype=torch.int32, device=dev),
@@ -136,7 +161,7 @@ def project(means, scales, quats, opacities, sh, cams, opts: RenderOptions, app=
                     torch.empty((n_tiles,), dtype=torch.int32, device=dev),
                     torch.empty((S,), dtype=torch.int64, device=dev) if exact_cull else None)
     g = gaussians_struct(means, scales, quats, opacities, sh, app)
-    L.check(lib.gs_project(C.byref(g), L.make_cameras(cams), len(cams), C.byref(opts.c()), C.byref(out.c()),
+    L.check(lib.gs_project(C.byref(g), cams.c, len(cams), C.byref(opts.c()), C.byref(out.c()),
                            _stream()))
     return out
 
@@ -200,7 +225,9 @@ class PairCount:
 
 
 def _pair_capacity(P: int) -> int:
-    return int(P * 1.25) + 4096
+    # a quarter of headroom; twice for small scenes, whose counts move more from
+    # step to step and where the room costs nothing
+    return int(P * 1.25) + 4096 if P >= 1 << 20 else 2 * P + 4096
 
 
 def bin_sort(proj: Projected, cams, n: int, ws: Workspace | None = None, capacity_hint: int | None = None,
@@ -212,23 +239,23 @@ def bin_sort(proj: Projected, cams, n: int, ws: Workspace | None = None, capacit
     sync=False nothing waits: pair_vals is the whole capacity buffer and P a
     PairCount to check later.  pair_vals is a fresh tensor (torch's caching
     allocator), so results of several calls can be alive at once; the
-    workspace remembers, per (slots, tiles), a capacity 25 % above the last
-    count it read."""
+    workspace remembers, per (slots, tiles), a capacity 25 % (below 2^20
+    pairs: 100 %) above the last count it read."""
     lib = L.load()
     ws = ws or _default_ws
     dev = proj.rec.device
+    cams = _views(cams)
     S = n * len(cams)
-    n_tiles, _ = views_extent(cams)
+    n_tiles, _ = cams.extent
     key = (S, n_tiles)
     cap = int(capacity_hint or ws.pair_caps.get(key, 0) or max(1 << 20, 4 * S))
     ranges = torch.empty((n_tiles, 2), dtype=torch.int32, device=dev)
-    cams_c = L.make_cameras(cams)
     npairs = torch.empty((1,), dtype=torch.int64, device=dev)
     for _ in range(3):
         pairs = torch.empty((max(cap, 1),), dtype=torch.int32, device=dev)
         wsz = lib.gs_bin_workspace_size(S, cap)
         wbuf = ws.get("bin", wsz + 256, dev)
-        L.check(lib.gs_bin_sort(C.byref(proj.c()), cams_c, len(cams), n, cap, _ptr(pairs), _ptr(ranges),
+        L.check(lib.gs_bin_sort(C.byref(proj.c()), cams.c, len(cams), n, cap, _ptr(pairs), _ptr(ranges),
                                 C.c_void_p(npairs.data_ptr()), C.c_void_p(Workspace.aligned(wbuf)), wsz, _stream()))
         if not sync:
             return pairs, ranges, PairCount(npairs, cap)
@@ -259,25 +286,26 @@ def _seg_args(seg: torch.Tensor):
 
 
 def render_fwd(proj: Projected, pair_vals, ranges, cams, opts: RenderOptions, seg=None, ws: Workspace | None = None) -> dict:
-    """Compositing.  Lists longer than 512 positions are walked in segments
-    by separate workgroups (gs_render_fwd_seg) in a workspace area; with
+    """Compositing.  Lists longer than a segment (512 positions, 128 for
+    launches of up to 4096 tiles) are walked in segments by separate workgroups (gs_render_fwd_seg) in a workspace area; with
     `seg` (from seg_workspace) in that area, whose segment states the
     backward can then read (pass it to render_bwd).  seg=False: every list
     walked whole by one workgroup (gs_render_fwd)."""
+    cams = _views(cams)
     if seg is None:
         ws = ws or _default_ws
-        n_tiles, _ = views_extent(cams)
+        n_tiles, _ = cams.extent
         seg = ws.get("seg_fwd", L.load().gs_seg_workspace_size(n_tiles, int(pair_vals.numel())) + 256,
                      proj.rec.device)
     lib = L.load()
     dev = proj.rec.device
-    _, npx = views_extent(cams)
+    _, npx = cams.extent
     out = {"rgb": torch.empty((npx, 3), dtype=torch.float32, device=dev),
            "depth": torch.empty((npx,), dtype=torch.float32, device=dev),
            "alpha": torch.empty((npx,), dtype=torch.float32, device=dev),
            "T": torch.empty((npx,), dtype=torch.float32, device=dev),
            "last": torch.empty((npx,), dtype=torch.int32, device=dev)}
-    args = (C.byref(proj.c()), _ptr(pair_vals), _ptr(ranges), L.make_cameras(cams), len(cams), C.byref(opts.c()),
+    args = (C.byref(proj.c()), _ptr(pair_vals), _ptr(ranges), cams.c, len(cams), C.byref(opts.c()),
             _ptr(out["rgb"]), _ptr(out["depth"]), _ptr(out["alpha"]), _ptr(out["T"]), _ptr(out["last"]))
     if seg is False:
         L.check(lib.gs_render_fwd(*args, _stream()))
@@ -290,9 +318,10 @@ def render_count(proj: Projected, pair_vals, ranges, cams) -> torch.Tensor:
     """Per-pixel numbers of list entries the forward [:, 0] and the backward
     [:, 1] compositing evaluate (measurement)."""
     lib = L.load()
-    _, npx = views_extent(cams)
+    cams = _views(cams)
+    _, npx = cams.extent
     out = torch.empty((npx, 2), dtype=torch.int32, device=proj.rec.device)
-    L.check(lib.gs_render_count(C.byref(proj.c()), _ptr(pair_vals), _ptr(ranges), L.make_cameras(cams), len(cams),
+    L.check(lib.gs_render_count(C.byref(proj.c()), _ptr(pair_vals), _ptr(ranges), cams.c, len(cams),
                                 _ptr(out), _stream()))
     return out
 
@@ -391,6 +420,7 @@ def render_bwd(params, cams, opts: RenderOptions, proj: Projected, pair_vals, ra
     means, scales, quats, opacities, sh = params
     n = check_params(means, scales, quats, opacities, sh)
     check_app(app, n)
+    cams = _views(cams)
     V = len(cams)
     dev = means.device
     norm = torch.empty((V, n), dtype=torch.float32, device=dev)
@@ -400,14 +430,14 @@ def render_bwd(params, cams, opts: RenderOptions, proj: Projected, pair_vals, ra
     wbuf = ws.get("bwd", wsz + 256, dev)
     g2 = C.c_void_p(Workspace.aligned(wbuf))
     if seg is None:
-        n_tiles, _ = views_extent(cams)
+        n_tiles, _ = cams.extent
         ssz = lib.gs_seg_workspace_size(n_tiles, int(pair_vals.numel()))
         seg_ptr, seg_bytes, seg_ready = *_seg_args(ws.get("seg", ssz + 256, dev)), 0
     else:
         seg_ptr, seg_bytes, seg_ready = *_seg_args(seg), 1
     cont = lambda t: t.contiguous() if t is not None else None
     d_rgb, d_depth, d_alpha = cont(d_rgb), cont(d_depth), cont(d_alpha)
-    cams_c, opt_c, proj_c = L.make_cameras(cams), opts.c(), proj.c()
+    cams_c, opt_c, proj_c = cams.c, opts.c(), proj.c()
     _mark("bwd_begin")
     main = torch.cuda.current_stream(dev)
     beside = n >= FILL_BESIDE_MIN
@@ -468,6 +498,7 @@ class GsRasterize(torch.autograd.Function):
         params = tuple(t.detach().contiguous() for t in (means, scales, quats, opacities, sh))
         app = app.detach().contiguous() if app is not None else None
         n = params[0].shape[-1]
+        cams = _Views(cams)
         proj = project(*params, cams, opts, app=app)
         _mark("project")
         # asynchronous once the workspace knows a pair capacity for this
@@ -483,7 +514,7 @@ class GsRasterize(torch.autograd.Function):
         _mark("render_fwd")
         ctx.save_for_backward(*params, proj.rec, proj.rect, proj.tiles, proj.depth_key, proj.tile_order, pair_vals,
                               ranges, out["T"], out["last"], app)
-        ctx.cams, ctx.opts, ctx.stats, ctx.n_pairs, ctx.n_slots = list(cams), opts, stats, P, n * len(cams)
+        ctx.cams, ctx.opts, ctx.stats, ctx.n_pairs, ctx.n_slots = cams, opts, stats, P, n * len(cams)
         ctx.seg = seg
         if stats is not None:
             stats.n_pairs = P
