@@ -167,17 +167,24 @@ __global__ __launch_bounds__(kVisThreads) void k_compact_visible(
         s_off[wave] = off;
         s_p[wave] = P;
     }
-    // the gathers of all the thread's slots, before the first use
-    uint32_t k[kVisIpt];
-    uint2 rc[kVisIpt];
-    uint64_t m[kVisIpt];
+    // half of the thread's slots at a time, the gathers of the first before the
+    // barrier: with all in flight at once the kernel needs 88 registers, and beside
+    // a compositing kernel, whose ending waves free 72, it waits for that kernel's end
+    constexpr int kHalf = kVisIpt / 2;
+    uint32_t k[kHalf];
+    uint2 rc[kHalf];
+    uint64_t m[kHalf];
+    const auto gather = [&](int first) {
 #pragma unroll
-    for (int r = 0; r < kVisIpt; ++r) {
-        const uint32_t i = base + r * kVisThreads;
-        k[r] = t[r] ? dkey[i] : 0u;
-        rc[r] = t[r] ? rect[i] : make_uint2(0u, 0u);
-        m[r] = t[r] && mask ? mask[i] : 0ull;
-    }
+        for (int r = 0; r < kHalf; ++r) {
+            const uint32_t i = base + (first + r) * kVisThreads;
+            const bool on = t[first + r] != 0u;
+            k[r] = on ? dkey[i] : 0u;
+            rc[r] = on ? rect[i] : make_uint2(0u, 0u);
+            m[r] = on && mask ? mask[i] : 0ull;
+        }
+    };
+    gather(0);
     __syncthreads();
     uint32_t pos[kVisIpt], run = s_off[0] + s_off[1] + s_off[2] + s_off[3];
 #pragma unroll
@@ -189,12 +196,17 @@ __global__ __launch_bounds__(kVisThreads) void k_compact_visible(
     }
     if (last && threadIdx.x == 0) write_counts(run, s_p[0] + s_p[1] + s_p[2] + s_p[3], capacity, n_pairs_out, counts);
 #pragma unroll
-    for (int r = 0; r < kVisIpt; ++r) {
-        if (!t[r]) continue;
-        const uint32_t d = pos[r];
-        keys[d] = k[r];
-        desc[2 * (size_t)d] = make_uint4(rc[r].x, rc[r].y, (uint32_t)m[r], (uint32_t)(m[r] >> 32));
-        desc[2 * (size_t)d + 1] = make_uint4(t[r], base + r * kVisThreads, 0u, 0u);
+    for (int h = 0; h < 2; ++h) {
+        if (h) gather(kHalf);
+#pragma unroll
+        for (int r = 0; r < kHalf; ++r) {
+            const int j = h * kHalf + r;
+            if (!t[j]) continue;
+            const uint32_t d = pos[j];
+            keys[d] = k[r];
+            desc[2 * (size_t)d] = make_uint4(rc[r].x, rc[r].y, (uint32_t)m[r], (uint32_t)(m[r] >> 32));
+            desc[2 * (size_t)d + 1] = make_uint4(t[j], base + j * kVisThreads, 0u, 0u);
+        }
     }
 }
 

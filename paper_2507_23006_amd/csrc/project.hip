@@ -311,21 +311,7 @@ __device__ __forceinline__ void project_candidate(const GaussPtrs& gp, int64_t n
     }
 }
 
-constexpr int kPF = 256;                 // threads per workgroup
-constexpr int kPFPer = 4;                // items per thread in the pre-test
-constexpr int kPFSpan = kPF * kPFPer;    // items per workgroup
-
-// appends the lanes with cand != 0 to the workgroup's LDS list as
-// (local index | cand << 16)
-__device__ __forceinline__ void list_append(uint32_t cand, int loc, int lane, uint32_t* s_list, uint32_t* s_count) {
-    const uint64_t m = __ballot(cand != 0);
-    if (!m) return;
-    const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-    uint32_t base = 0;
-    if (lane == 0) base = atomicAdd(s_count, (uint32_t)__popcll(m));
-    base = __shfl(base, 0);
-    if (cand) s_list[base + below] = (uint32_t)loc | (cand << 16);
-}
+constexpr int kPFPer = 4;                // items per lane in the scan of a chunk
 
 // Every view of the launch sees the same n Gaussians: slot = view * n + g.  Each
 // workgroup is one wave that scans chunks of 64 * per Gaussians (per <=
@@ -477,124 +463,161 @@ __device__ __forceinline__ int segment_of(const SlotSeg* __restrict__ segs, int3
     return lo;
 }
 
+// the same by a whole wave for one slot, 64 probes at a time
+__device__ __forceinline__ int segment_of_wave(const SlotSeg* __restrict__ segs, int32_t n_seg, uint32_t s, int lane) {
+    int lo = 0, hi = n_seg;
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) / 64, q = lo + lane * step;
+        const bool le = lane == 0 || (q < hi && segs[q].slot_start <= s);
+        const int last = 63 - __clzll(__ballot(le));       // lanes 0 .. last hold
+        lo += last * step;
+        hi = min(hi, lo + step);
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
 // Views with their own selections of Gaussians (served requests): slot s
 // maps to Gaussian gstart + (s - slot_start) of its segment, seen by the
-// segment's view.  Same two passes as k_project_fwd, over 1024 slots, with
-// the values pass 1 read kept in LDS for pass 2; the segments that the
-// workgroup's slots fall in are staged in LDS when there are at most
-// kSlotSegCache of them (else each slot searches them in global memory).
-constexpr int kSlotSegCache = 128;
-__global__ __launch_bounds__(kPF, 4) void k_project_slots(GaussPtrs gp, int64_t n, ViewTable vt, OptK opt,
-                                                          const SlotSeg* __restrict__ segs, int32_t n_seg,
-                                                          uint32_t n_slots, PlaneTable planes, Projected out) {
-    __shared__ uint32_t s_list[kPFSpan];
-    __shared__ float s_par[7][kPFSpan];     // listed slots' mean, scales, opacity
-    __shared__ uint32_t s_gid[kPFSpan];     // listed slots' Gaussian (n < 2^32, checked at launch)
-    __shared__ SlotSeg s_seg[kSlotSegCache];
-    __shared__ int32_t s_seg_lo, s_seg_n;
-    __shared__ uint32_t s_count;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const uint32_t s0 = blockIdx.x * kPFSpan;
-    // the segments of this workgroup's slots, staged in LDS when few
-    if (tid == 0) {
-        s_count = 0;
-        const int32_t lo = segment_of(segs, n_seg, s0);
-        const int32_t hi = segment_of(segs, n_seg, min(s0 + (uint32_t)kPFSpan, n_slots) - 1u);
-        s_seg_lo = lo;
-        s_seg_n = hi - lo + 1;
-    }
-    __syncthreads();
-    const int32_t seg_lo = s_seg_lo, seg_n = s_seg_n;
-    const bool staged = seg_n <= kSlotSegCache;
-    if (staged)
-        for (int k = tid; k < seg_n; k += kPF) s_seg[k] = segs[seg_lo + k];
-    __syncthreads();
-    // the thread's kPFSpan / kPF slots move through each phase together, so
-    // that their independent loads are in flight at once
-    constexpr uint32_t kNone = 0xFFFFFFFFu;      // no slot (n < 2^32, so no Gaussian has this index)
-    uint32_t g[kPFPer], view[kPFPer];
+// segment's view.  The scan and the batches of k_project_fwd, over chunks of
+// slots; a chunk's segments are held one per lane when it has fewer than 64 (else
+// each slot searches them).  Batches of 8 views of 6M Gaussians, beside the
+// compositing of the batch before: 405 us where 256 threads over spans of 1024
+// took 967.  More waves than run at once (2304): beside another stream's kernel
+// waves that end make room for it (2304, 1536, 1024 and 512 waves: 40 requests take
+// 10.4, 10.7, 10.5 and 11.4 ms, 16384: 10.2).
+constexpr int64_t kSlotWaves = 16384;
+__global__ __launch_bounds__(64, 3) void k_project_slots(GaussPtrs gp, int64_t n, ViewTable vt, PlaneTable planes,
+                                                         OptK opt, const SlotSeg* __restrict__ segs, int32_t n_seg,
+                                                         uint32_t n_slots, Projected out, int per) {
+    constexpr uint32_t kCap = 64 * (1 + kPFPer);
+    __shared__ uint32_t s_slot[kCap], s_gid[kCap];      // listed slots and their Gaussians (n < 2^32, checked at launch)
+    __shared__ uint8_t s_view[kCap];
+    __shared__ F4 s_rows[kWaveRows];
+    const int lane = threadIdx.x;
+    const uint32_t span = 64u * (uint32_t)per;
+    const uint32_t n_chunks = (uint32_t)(((uint64_t)n_slots + span - 1) / span);
+    const int nq = (3 * (opt.sh_degree + 1) * (opt.sh_degree + 1) + 3) >> 2;    // float4s of a row in use
+    const RowLanes rl(lane);
+    constexpr uint32_t kNone = 0xFFFFFFFFu;      // view of a lane without a slot
+    uint32_t cnt = 0, chunk = blockIdx.x;
+    for (;;) {
+        while (cnt < 64 && chunk < n_chunks) {
+            const uint32_t s0 = chunk * span, s1 = n_slots - s0 < span ? n_slots : s0 + span;
+            const int seg0 = segment_of_wave(segs, n_seg, s0, lane);
+            SlotSeg mine = {};
+            mine.slot_start = kNone;
+            if (seg0 + lane < n_seg) mine = segs[seg0 + lane];
+            const int n_in = __popcll(__ballot(mine.slot_start < s1));      // segments of the chunk, from lane 0 on
+            uint32_t g[kPFPer], view[kPFPer];
 #pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        const uint32_t s = s0 + i * kPF + tid;
-        g[i] = kNone;
-        view[i] = 0;
-        if (s < n_slots) {
-            SlotSeg sg;
-            if (staged) {
-                int lo = 0, hi = seg_n;      // invariant: s_seg[lo].slot_start <= s, answer in [lo, hi)
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_seg[mid].slot_start <= s) lo = mid; else hi = mid;
+            for (int i = 0; i < kPFPer; ++i) {
+                const uint32_t s = s0 + 64 * i + lane;
+                const bool in = i < per && (uint64_t)s0 + 64 * i + lane < s1;
+                SlotSeg sg;
+                if (n_in < 64) {
+                    int k = 0;
+                    for (int j = 1; j < n_in; ++j)
+                        if (s >= (uint32_t)__builtin_amdgcn_readlane((int)mine.slot_start, j)) k = j;
+                    sg.slot_start = __shfl(mine.slot_start, k);
+                    sg.view = __shfl(mine.view, k);
+                    sg.gstart = __shfl(mine.gstart, k);
+                } else {
+                    sg = segs[seg0 + segment_of(segs + seg0, n_seg - seg0, in ? s : s0)];
                 }
-                sg = s_seg[lo];
-            } else {
-                sg = segs[seg_lo + segment_of(segs + seg_lo, seg_n, s)];
+                g[i] = in ? (uint32_t)(sg.gstart + (int64_t)(s - sg.slot_start)) : 0u;
+                view[i] = in ? (uint32_t)sg.view : kNone;
             }
-            g[i] = (uint32_t)(sg.gstart + (int64_t)(s - sg.slot_start));
-            view[i] = sg.view;
-        }
-    }
-    float mu[kPFPer][3];
+            float mu[kPFPer][3], a[kPFPer];
 #pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        const bool ok = g[i] != kNone;
-        mu[i][0] = ok ? gp.means[g[i]] : 0.0f;
-        mu[i][1] = ok ? gp.means[n + g[i]] : 0.0f;
-        mu[i][2] = ok ? gp.means[2 * n + g[i]] : 0.0f;
-    }
-    bool front[kPFPer];
-    float a[kPFPer];
+            for (int i = 0; i < kPFPer; ++i) {
 #pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        front[i] = false;
-        a[i] = 0.0f;
-        if (g[i] == kNone) continue;
-        a[i] = fabsf(mu[i][0]) + fabsf(mu[i][1]) + fabsf(mu[i][2]);
-        front[i] = may_be_in_front(vt.v[view[i]], planes.p[view[i]], mu[i], a[i]);
-    }
-    float sc[kPFPer][3], op[kPFPer];
-#pragma unroll
-    for (int i = 0; i < kPFPer; ++i) {
-        sc[i][0] = sc[i][1] = sc[i][2] = op[i] = 0.0f;
-        if (front[i]) {
-            sc[i][0] = gp.scales[g[i]];
-            sc[i][1] = gp.scales[n + g[i]];
-            sc[i][2] = gp.scales[2 * n + g[i]];
-            op[i] = gp.opac[g[i]];
-        }
-    }
-    for (int i = 0; i < kPFPer; ++i) {
-        const int loc = i * kPF + tid;
-        const uint32_t s = s0 + (uint32_t)loc;
-        uint32_t cand = 0;
-        if (g[i] != kNone) {
-            if (front[i]) {
-                const float smax = fmaxf(fabsf(sc[i][0]), fmaxf(fabsf(sc[i][1]), fabsf(sc[i][2])));
-                if (op[i] >= kAlphaMin && may_cover(vt.v[view[i]], planes.p[view[i]], mu[i], a[i], smax)) cand = 1u << view[i];
+                for (int c = 0; c < 3; ++c) mu[i][c] = view[i] != kNone ? gp.means[c * n + g[i]] : 0.0f;
+                a[i] = fabsf(mu[i][0]) + fabsf(mu[i][1]) + fabsf(mu[i][2]);
             }
-            if (!cand) {
-                out.tiles[s] = 0u;
-                out.dkey[s] = 0xFFFFFFFFu;
-            } else {
-                s_par[0][loc] = mu[i][0]; s_par[1][loc] = mu[i][1]; s_par[2][loc] = mu[i][2];
-                s_par[3][loc] = sc[i][0]; s_par[4][loc] = sc[i][1]; s_par[5][loc] = sc[i][2];
-                s_par[6][loc] = op[i];
-                s_gid[loc] = g[i];
+            // views one after another, with their constants in scalar registers (a
+            // chunk rarely has more than one)
+            const auto of_view = [&](uint32_t v) {
+                bool any = false;
+#pragma unroll
+                for (int i = 0; i < kPFPer; ++i) any |= view[i] == v;
+                return __ballot(any) != 0;
+            };
+            bool cand[kPFPer];
+#pragma unroll
+            for (int i = 0; i < kPFPer; ++i) cand[i] = false;
+            for (uint32_t v = 0; v < (uint32_t)vt.n_views; ++v) {
+                if (!of_view(v)) continue;
+#pragma unroll
+                for (int i = 0; i < kPFPer; ++i)
+                    if (view[i] == v) cand[i] = may_be_in_front(vt.v[v], planes.p[v], mu[i], a[i]);
             }
+            float smax[kPFPer];
+#pragma unroll
+            for (int i = 0; i < kPFPer; ++i) {
+                float sc[3] = {0.0f, 0.0f, 0.0f}, op = 0.0f;
+                if (cand[i]) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) sc[c] = gp.scales[c * n + g[i]];
+                    op = gp.opac[g[i]];
+                }
+                smax[i] = fmaxf(fabsf(sc[0]), fmaxf(fabsf(sc[1]), fabsf(sc[2])));
+                cand[i] = op >= kAlphaMin;      // o' = o rho <= o: else below the skip threshold everywhere
+            }
+            for (uint32_t v = 0; v < (uint32_t)vt.n_views; ++v) {
+                if (!of_view(v)) continue;
+#pragma unroll
+                for (int i = 0; i < kPFPer; ++i)
+                    if (view[i] == v) cand[i] = cand[i] && may_cover(vt.v[v], planes.p[v], mu[i], a[i], smax[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < kPFPer; ++i) {
+                const uint32_t s = s0 + 64 * i + lane;
+                const uint64_t m = __ballot(cand[i]);
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                if (cand[i]) {
+                    s_slot[cnt + below] = s;
+                    s_gid[cnt + below] = g[i];
+                    s_view[cnt + below] = (uint8_t)view[i];
+                } else if (view[i] != kNone) {
+                    __builtin_nontemporal_store(0u, out.tiles + s);
+                    __builtin_nontemporal_store(0xFFFFFFFFu, out.dkey + s);
+                }
+                cnt += (uint32_t)__popcll(m);
+            }
+            chunk += gridDim.x;
         }
-        list_append(cand, loc, lane, s_list, &s_count);
-    }
-    __syncthreads();
-    const uint32_t cnt = s_count;
-    for (uint32_t j = tid; j < cnt; j += kPF) {
-        const uint32_t e = s_list[j];
-        const int loc = (int)(e & 0xFFFFu);
-        const uint32_t s = s0 + (uint32_t)loc;
-        // one view bit: the slot is s itself (stride 0)
-        const float mu1[3] = {s_par[0][loc], s_par[1][loc], s_par[2][loc]};
-        const float sc1[3] = {s_par[3][loc], s_par[4][loc], s_par[5][loc]};
-        project_candidate(gp, n, vt, opt, out, (int64_t)s_gid[loc], e >> 16, (int64_t)s, 0, mu1, sc1, s_par[6][loc],
-                          reinterpret_cast<const F4*>(gp.sh) + (int64_t)12 * s_gid[loc]);
+        wave_sync();
+        const bool last = chunk >= n_chunks;
+        // lanes past the end work on the last slot and write nothing
+        uint32_t b = 0;
+        for (; b + 64 <= cnt || (last && b < cnt); b += 64) {
+            const int m = cnt - b < 64u ? (int)(cnt - b) : 64;
+            const uint32_t j = b + (lane < m ? lane : m - 1), g = s_gid[j];
+            float mu[3], sc[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                mu[c] = gp.means[c * n + g];
+                sc[c] = gp.scales[c * n + g];
+            }
+            const float op = gp.opac[g];
+            load_rows(gp.sh, g, nq, rl, s_rows);
+            // one view bit: the slot is s itself (stride 0)
+            if (lane < m)
+                project_candidate(gp, n, vt, opt, out, g, 1u << s_view[j], s_slot[j], 0, mu, sc, op, s_rows + lane * kRowF4);
+            wave_sync();
+        }
+        if (last) return;
+        // what is left over, to the front
+        const uint32_t left = cnt - b, at = b + ((uint32_t)lane < left ? lane : 0);
+        const uint32_t slot = s_slot[at], gid = s_gid[at];
+        const uint8_t v = s_view[at];
+        wave_sync();
+        if ((uint32_t)lane < left) {
+            s_slot[lane] = slot;
+            s_gid[lane] = gid;
+            s_view[lane] = v;
+        }
+        cnt = left;
     }
 }
 
@@ -661,8 +684,11 @@ hipError_t launch_project_slots(const GaussPtrs& g, int64_t n, const ViewTable& 
                                 hipStream_t s) {
     if (!n_slots) return hipSuccess;
     if (n > 0xFFFFFFFFLL) return hipErrorInvalidValue;     // listed Gaussians are kept as 32-bit indices
-    hipLaunchKernelGGL(k_project_slots, dim3((n_slots + kPFSpan - 1) / kPFSpan), dim3(kPF), 0, s, g, n, vt, opt, segs,
-                       n_seg, n_slots, build_planes(vt, opt), out);
+    // chunks of 256 slots when the waves that run at once (2304) each have several, else of 64
+    const int per = (int64_t)n_slots >= 2304 * 64 * kPFPer ? kPFPer : 1;
+    const int64_t chunks = ((int64_t)n_slots + 64 * per - 1) / (64 * per);
+    hipLaunchKernelGGL(k_project_slots, dim3((unsigned)(chunks < kSlotWaves ? chunks : kSlotWaves)), dim3(64), 0, s, g, n, vt,
+                       build_planes(vt, opt), opt, segs, n_seg, n_slots, out, per);
     return hipGetLastError();
 }
 

@@ -33,7 +33,6 @@ constexpr int kMaxRadixBits = 8;
 constexpr uint32_t kSmallSortMax = 1u << 21;
 constexpr int kMinSortTile = kSortThreads * 4;      // digit tables are sized for this
 constexpr uint32_t kFewTiles = 64;
-constexpr uint32_t kLongRow = 4096;      // tiles from which the row scan takes 1024 threads
 
 __device__ __forceinline__ unsigned long long lanemask_lt() {
     const unsigned lane = __lane_id();
@@ -95,14 +94,14 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_upsweep(const uint32_t* 
 
 // One workgroup per digit: exclusive scan of its row of the table (one count
 // per tile) in place; its total goes to row_total.  A row is walked in chunks
-// of 8 per thread, one after another: long rows (76M pairs: 37k tiles) take
-// 1024 threads (4 waves walk such a row in 39 us).
-constexpr int kRowIpt = 8;
-template <int kThreads>
-__global__ __launch_bounds__(kThreads) void k_radix_rowscan(uint32_t* __restrict__ hist, uint32_t n_max,
+// of 8 per thread, one after another.  (1024 threads walk the long rows of 76M
+// pairs' 37k tiles in 17 us where 256 take 19, but beside a compositing kernel
+// their 16 waves wait for that many slots of one compute unit: 137 us.)
+constexpr int kRowIpt = 8, kRowThreads = 256;
+__global__ __launch_bounds__(kRowThreads) void k_radix_rowscan(uint32_t* __restrict__ hist, uint32_t n_max,
                                                             const uint32_t* __restrict__ n_dev, uint32_t sort_tile,
                                                             uint32_t* __restrict__ row_total) {
-    constexpr int kWaves = kThreads / 64;
+    constexpr int kWaves = kRowThreads / 64;
     __shared__ uint32_t s_w[2][kWaves];
     const uint32_t n = count_of(n_max, n_dev);
     const uint32_t n_tab = (uint32_t)(((uint64_t)n + sort_tile - 1) / sort_tile);
@@ -118,14 +117,14 @@ __global__ __launch_bounds__(kThreads) void k_radix_rowscan(uint32_t* __restrict
         for (int r = 0; r < kRowIpt; ++r) v[r] = i0 + r < n_tab ? row[i0 + r] : 0u;
     };
     load(0);
-    for (uint32_t c0 = 0; c0 < n_tab; c0 += kThreads * kRowIpt) {
+    for (uint32_t c0 = 0; c0 < n_tab; c0 += kRowThreads * kRowIpt) {
         uint32_t cur[kRowIpt], sum = 0;
 #pragma unroll
         for (int r = 0; r < kRowIpt; ++r) {
             cur[r] = v[r];
             sum += v[r];
         }
-        load(c0 + kThreads * kRowIpt);      // the next chunk, beside this one's scan
+        load(c0 + kRowThreads * kRowIpt);      // the next chunk, beside this one's scan
         uint32_t incl = sum;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -420,12 +419,8 @@ hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, 
     uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
     bool iota = vals_are_positions;
     auto rowscan = [&](int bits) {
-        if (tiles < kLongRow)
-            hipLaunchKernelGGL(k_radix_rowscan<256>, dim3(1u << bits), dim3(256), 0, s, hist, n, n_dev, sort_tile,
-                               row_total);
-        else
-            hipLaunchKernelGGL(k_radix_rowscan<1024>, dim3(1u << bits), dim3(1024), 0, s, hist, n, n_dev, sort_tile,
-                               row_total);
+        hipLaunchKernelGGL(k_radix_rowscan, dim3(1u << bits), dim3(kRowThreads), 0, s, hist, n, n_dev, sort_tile,
+                           row_total);
     };
     int shift = begin_bit;
     for (int p = 0; p < passes; ++p) {
