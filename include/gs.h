@@ -206,7 +206,8 @@ int gs_render_count(const gs_projected *proj, const uint32_t *pair_vals, const u
  * per-slot 2D gradients, optionally followed (gs_render_bwd) or given
  * separately (gs_composite_bwd's seg_ws) by gs_seg_workspace_size(n_tiles,
  * n_pairs) bytes for the segmented walk: tile lists longer than a segment
- * (512 positions, 128 for launches of at most 4096 tiles) are then walked in
+ * (128 positions for launches of at most 4096 tiles, 512 to 12288, 1024 to 28672,
+ * else 2048) are then walked in
  * segments by separate workgroups, each starting from the transmittance and colour behind it
  * (folded from per-segment states a pre-pass computes), so the longest
  * lists no longer serialise the launch.  A smaller or absent segment area
@@ -214,8 +215,8 @@ int gs_render_count(const gs_projected *proj, const uint32_t *pair_vals, const u
 size_t gs_render_bwd_workspace_size(int64_t n_slots);
 size_t gs_seg_workspace_size(int64_t n_tiles, int64_t n_pairs);
 
-/* Compositing (Eq. 2) with long lists split into segments (512 positions,
- * 128 for launches of at most 4096 tiles) walked by several workgroups, in the segment area
+/* Compositing (Eq. 2) with long lists split into segments (128 to 2048 positions,
+ * by the launch's tiles as above) walked by several workgroups, in the segment area
  * seg_ws (gs_seg_workspace_size(n_tiles, n_pairs) bytes, 256-byte aligned;
  * a smaller area, or one too small for the states, walks every list whole
  * as gs_render_fwd does).  A long list's workgroup walks its first two

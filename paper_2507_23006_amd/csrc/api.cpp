@@ -230,9 +230,17 @@ constexpr size_t kSegStateBytes = (size_t)kSegFields * 256 * sizeof(float);
 // wave per SIMD), so a launch of few tiles takes short segments: 4096 Gaussians
 // at 160x120 (80 tiles, lists to 600) k_render_bwd 78 -> 34 us; 250k Gaussians
 // in three views (2720 tiles, lists to 4000) 103 -> 50 us and the forward
-// passes 138 -> 62 us.  From about 4096 tiles on the waves fill the device
-// either way, and a segment's set-up and 6 KB of states count instead.
-int32_t seg_len_of(int64_t n_tiles) { return n_tiles <= 4096 ? kSegLenSmall : kSegLen; }
+// passes 138 -> 62 us.  The more tiles there are, the more waves fill the device
+// without segments, whose set-up, 6 KB of states and second walk of the one a
+// pixel stops in then only cost: renders and training steps of 6M Gaussians,
+// with 512 | 1024 | 2048 positions,
+//    8160 tiles (1920x1080)      0.84 | 0.89 | -       1.74 | 1.74 | -     ms
+//   16320 (two of them)          2.56 | 2.49 | 2.62    5.17 | 5.00 | 5.08
+//   32400 (3840x2160)            1.25 | 1.25 | 1.11    2.95 | 2.90 | 2.75
+//   64800 (two of them)          3.75 | 3.53 | 3.41    7.93 | 7.68 | 7.52
+int32_t seg_len_of(int64_t n_tiles) {
+    return n_tiles <= 4096 ? kSegLenSmall : n_tiles <= 12288 ? kSegLen : n_tiles <= 28672 ? kSegLenLarge : kSegLenHuge;
+}
 
 // a plan over `base` (NULL or too small: no segments)
 void seg_layout(void* base, size_t bytes, int64_t n_tiles, int32_t seg_len, SegPlan* plan, uint32_t* capacity) {

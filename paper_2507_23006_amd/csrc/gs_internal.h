@@ -251,9 +251,11 @@ hipError_t launch_tile_order(const uint32_t* ranges, uint32_t n_tiles, uint32_t*
 // b), D_seg and (int) the position of the segment's last entry; stop_seg
 // [T][256] (by tile) is the segment a pixel stops in, -1 for none, for the
 // segmented forward.
-constexpr int kSegLen = 512;          // segments of a large launch (seg_len_of)
-constexpr int kSegLenSmall = 128;     // and of a small one
-constexpr int kHeadLen = 1024;        // a multiple of both
+constexpr int kSegLenSmall = 128;     // segments of a small launch (seg_len_of),
+constexpr int kSegLen = 512;          // of one full-HD view, and of served batches,
+constexpr int kSegLenLarge = 1024;    // of a few views,
+constexpr int kSegLenHuge = 2048;     // and of more
+constexpr int kHeadLen = 1024;        // a multiple of the first three
 constexpr int kPlanLong = 0;          // SegPlan::info: launch positions up to the last one with several segments
 constexpr int kPlanHead = 1;          // segments in the head
 constexpr int kSegFields = 6;

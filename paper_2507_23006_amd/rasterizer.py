@@ -286,8 +286,8 @@ def _seg_args(seg: torch.Tensor):
 
 
 def render_fwd(proj: Projected, pair_vals, ranges, cams, opts: RenderOptions, seg=None, ws: Workspace | None = None) -> dict:
-    """Compositing.  Lists longer than a segment (512 positions, 128 for
-    launches of up to 4096 tiles) are walked in segments by separate workgroups (gs_render_fwd_seg) in a workspace area; with
+    """Compositing.  Lists longer than a segment (128 to 2048 positions, by the
+    launch's tiles) are walked in segments by separate workgroups (gs_render_fwd_seg) in a workspace area; with
     `seg` (from seg_workspace) in that area, whose segment states the
     backward can then read (pass it to render_bwd).  seg=False: every list
     walked whole by one workgroup (gs_render_fwd)."""
