@@ -1083,99 +1083,131 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
     flush(r0, r1);
 }
 
-// exclusive scan of v over the 1024 threads of the workgroup; *total gets the sum
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_wave, uint32_t* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t x = v;
+// Segments per tile in launch order (ceil(L / seg_len) for a list of L > seg_len
+// positions, else 1) and the stored states (segments 1 .. n - 1); exclusive
+// prefix sums into work_off / state_off.  When the states would exceed
+// `capacity`, every tile keeps a single segment.  A workgroup takes kPlanSpan
+// positions, kPlanPer consecutive ones per thread, so that the order is read and
+// the offsets are written in whole lines; with several workgroups a first launch
+// leaves their sums, which each then adds up itself.  100k tiles: 153 -> 14 us,
+// 8160: 17 -> 12 (one workgroup walked the positions, bound by one compute unit's
+// range gathers).
+constexpr int kPlanThreads = 256, kPlanPer = 8, kPlanSpan = kPlanThreads * kPlanPer;
+
+struct PlanSum {
+    uint32_t items, most, end_long;      // segments, most of a list, position after the last list with several
+};
+
+// of positions i0 .. i0 + kPlanPer - 1; c: their segments (0 past the end)
+__device__ __forceinline__ PlanSum plan_positions(const uint2* __restrict__ ranges,
+                                                  const uint32_t* __restrict__ tile_order, const ViewTable& vt,
+                                                  uint32_t seg_len, uint32_t i0, uint32_t c[kPlanPer]) {
+    const uint32_t n_tiles = (uint32_t)vt.total_tiles;
+    int t[kPlanPer];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
+    for (int u = 0; u < kPlanPer; ++u) t[u] = i0 + u < n_tiles ? order_tile(tile_order, vt, i0 + u) : -1;
+    uint2 r[kPlanPer];
+#pragma unroll
+    for (int u = 0; u < kPlanPer; ++u) r[u] = t[u] >= 0 ? ranges[t[u]] : make_uint2(0u, 0u);
+    PlanSum s{0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < kPlanPer; ++u) {
+        const uint32_t L = r[u].y - r[u].x;
+        c[u] = t[u] < 0 ? 0u : L > seg_len ? (L + seg_len - 1) / seg_len : 1u;
+        if (c[u] > 1u) s.end_long = i0 + u + 1;
+        s.most = max(s.most, c[u]);
+        s.items += c[u];
     }
-    if (lane == 63) s_wave[wave] = x;
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    for (int w = 0; w < 16; ++w) {
-        const uint32_t t = s_wave[w];
-        before += w < wave ? t : 0u;
-        all += t;
-    }
-    __syncthreads();
-    *total = all;
-    return before + x - v;
+    return s;
 }
 
-// One workgroup: segments per tile in launch order (ceil(L / seg_len) for a
-// list of L > seg_len positions, else 1) and the stored states (segments
-// 1 .. n - 1); exclusive prefix sums into work_off / state_off.  When the
-// states would exceed `capacity`, every tile keeps a single segment.  The
-// positions are taken kPlanPer consecutive ones per thread, 8192 at a time, so
-// that the order is read and the offsets are written in whole lines and a
-// chunk waits for one round of range gathers (100k tiles: 300 -> 159 us; the gathers of one compute unit bound it).
-constexpr int kPlanPer = 8;
-__global__ __launch_bounds__(1024) void k_seg_plan(const uint2* __restrict__ ranges,
-                                                   const uint32_t* __restrict__ tile_order, ViewTable vt,
-                                                   uint32_t seg_len, uint32_t capacity,
-                                                   uint32_t* __restrict__ work_off,
-                                                   uint32_t* __restrict__ state_off, uint32_t* __restrict__ info) {
-    __shared__ uint32_t s_wave[16];
-    __shared__ uint32_t s_long, s_max;
-    const uint32_t n_tiles = (uint32_t)vt.total_tiles;
-    if (threadIdx.x == 0) s_long = s_max = 0;
-    uint32_t end_long = 0, most = 0, before = 0;      // segments of the earlier chunks
-    for (uint32_t c0 = 0; c0 < n_tiles; c0 += 1024 * kPlanPer) {
-        const uint32_t i0 = c0 + threadIdx.x * kPlanPer;
-        int t[kPlanPer];
-#pragma unroll
-        for (int u = 0; u < kPlanPer; ++u) t[u] = i0 + u < n_tiles ? order_tile(tile_order, vt, i0 + u) : -1;
-        uint2 r[kPlanPer];
-#pragma unroll
-        for (int u = 0; u < kPlanPer; ++u) r[u] = t[u] >= 0 ? ranges[t[u]] : make_uint2(0u, 0u);
-        uint32_t c[kPlanPer], mine = 0;
-#pragma unroll
-        for (int u = 0; u < kPlanPer; ++u) {
-            const uint32_t L = r[u].y - r[u].x;
-            c[u] = t[u] < 0 ? 0u : L > seg_len ? (L + seg_len - 1) / seg_len : 1u;
-            if (c[u] > 1u) end_long = i0 + u + 1;
-            most = max(most, c[u]);
-            mine += c[u];
-        }
-        uint32_t total = 0;
-        uint32_t w = before + block_excl_scan(mine, s_wave, &total);
-        before += total;
-#pragma unroll
-        for (int u = 0; u < kPlanPer; ++u) {
-            if (t[u] < 0) break;
-            work_off[i0 + u] = w;
-            state_off[i0 + u] = w - (i0 + u);
-            w += c[u];
-        }
-    }
+// over the workgroup, in every thread (s: one a wave)
+__device__ __forceinline__ PlanSum plan_reduce(PlanSum v, PlanSum* s) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
-        end_long = max(end_long, (uint32_t)__shfl_xor((int)end_long, off, 64));
-        most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
-    }
-    __syncthreads();      // s_long and s_max are zero
-    if ((threadIdx.x & 63) == 0) {
-        atomicMax(&s_long, end_long);
-        atomicMax(&s_max, most);
+        v.items += (uint32_t)__shfl_xor((int)v.items, off, 64);
+        v.most = max(v.most, (uint32_t)__shfl_xor((int)v.most, off, 64));
+        v.end_long = max(v.end_long, (uint32_t)__shfl_xor((int)v.end_long, off, 64));
     }
     __syncthreads();
-    const uint32_t need = before - n_tiles;
-    const bool on = need <= capacity;      // do the states fit?
-    if (!on)
-        for (uint32_t i = threadIdx.x; i < n_tiles; i += 1024) {
-            work_off[i] = i;
-            state_off[i] = 0;
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = s[0];
+#pragma unroll
+    for (int w = 1; w < kPlanThreads / 64; ++w) {
+        v.items += s[w].items;
+        v.most = max(v.most, s[w].most);
+        v.end_long = max(v.end_long, s[w].end_long);
+    }
+    return v;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void k_seg_sums(const uint2* __restrict__ ranges,
+                                                           const uint32_t* __restrict__ tile_order, ViewTable vt,
+                                                           uint32_t seg_len, PlanSum* __restrict__ sums) {
+    __shared__ PlanSum s_red[kPlanThreads / 64];
+    uint32_t c[kPlanPer];
+    const PlanSum v = plan_reduce(plan_positions(ranges, tile_order, vt, seg_len,
+                                                 blockIdx.x * kPlanSpan + threadIdx.x * kPlanPer, c), s_red);
+    if (threadIdx.x == 0) sums[blockIdx.x] = v;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void k_seg_plan(const uint2* __restrict__ ranges,
+                                                           const uint32_t* __restrict__ tile_order, ViewTable vt,
+                                                           uint32_t seg_len, uint32_t capacity,
+                                                           const PlanSum* __restrict__ sums,
+                                                           uint32_t* __restrict__ work_off,
+                                                           uint32_t* __restrict__ state_off, uint32_t* __restrict__ info) {
+    __shared__ PlanSum s_red[kPlanThreads / 64];
+    __shared__ uint32_t s_wave[kPlanThreads / 64];
+    const uint32_t n_tiles = (uint32_t)vt.total_tiles;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t i0 = blockIdx.x * kPlanSpan + threadIdx.x * kPlanPer;
+    uint32_t c[kPlanPer];
+    const PlanSum mine = plan_positions(ranges, tile_order, vt, seg_len, i0, c);
+    // segments of the earlier workgroups, and of all
+    PlanSum all = mine;
+    uint32_t before = 0;
+    if (gridDim.x > 1) {
+        PlanSum early{0u, 0u, 0u};
+        all = PlanSum{0u, 0u, 0u};
+        for (uint32_t b = threadIdx.x; b < gridDim.x; b += kPlanThreads) {
+            const PlanSum x = sums[b];
+            if (b < blockIdx.x) early.items += x.items;
+            all.items += x.items;
+            all.most = max(all.most, x.most);
+            all.end_long = max(all.end_long, x.end_long);
         }
-    if (threadIdx.x == 0) {
-        work_off[n_tiles] = on ? before : n_tiles;
+        before = plan_reduce(early, s_red).items;
+    }
+    all = plan_reduce(all, s_red);
+    // exclusive scan over the workgroup's threads
+    uint32_t incl = mine.items;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t w = before + incl - mine.items;
+    for (int k = 0; k < wave; ++k) w += s_wave[k];
+    const uint32_t need = all.items - n_tiles;
+    const bool on = need <= capacity;      // do the states fit?
+#pragma unroll
+    for (int u = 0; u < kPlanPer; ++u) {
+        if (i0 + u >= n_tiles) break;
+        work_off[i0 + u] = on ? w : i0 + u;
+        state_off[i0 + u] = on ? w - (i0 + u) : 0u;
+        w += c[u];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        work_off[n_tiles] = on ? all.items : n_tiles;
         state_off[n_tiles] = on ? need : 0u;
-        info[kPlanLong] = on ? (s_max > 1u ? s_long : 0u) : 0u;
+        info[kPlanLong] = on && all.most > 1u ? all.end_long : 0u;
         // lists up to kHeadLen are composited by the head alone when none is
         // longer: the later passes cost more than a head that long
-        info[kPlanHead] = s_max * seg_len > (uint32_t)kHeadLen ? 2u : (uint32_t)kHeadLen / seg_len;
+        info[kPlanHead] = all.most * seg_len > (uint32_t)kHeadLen ? 2u : (uint32_t)kHeadLen / seg_len;
     }
 }
 
@@ -1285,8 +1317,14 @@ hipError_t launch_render_count(const Projected& proj, const uint32_t* pair_vals,
 
 hipError_t launch_seg_plan(const Projected& proj, const uint2* ranges, const ViewTable& vt, uint32_t capacity,
                            const SegPlan& plan, hipStream_t s) {
-    hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(1024), 0, s, ranges, proj.tile_order, vt, plan.seg_len, capacity,
-                       plan.work_off, plan.state_off, plan.info);
+    const unsigned blocks = (unsigned)((vt.total_tiles + kPlanSpan - 1) / kPlanSpan);
+    // the sums lie where the forward's stop_seg will (1 KB a tile)
+    PlanSum* sums = reinterpret_cast<PlanSum*>(plan.stop_seg);
+    if (blocks > 1)
+        hipLaunchKernelGGL(k_seg_sums, dim3(blocks), dim3(kPlanThreads), 0, s, ranges, proj.tile_order, vt, plan.seg_len,
+                           sums);
+    hipLaunchKernelGGL(k_seg_plan, dim3(blocks ? blocks : 1u), dim3(kPlanThreads), 0, s, ranges, proj.tile_order, vt,
+                       plan.seg_len, capacity, sums, plan.work_off, plan.state_off, plan.info);
     return hipGetLastError();
 }
 
