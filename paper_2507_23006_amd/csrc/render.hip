@@ -10,9 +10,10 @@
 // recovering T_i = T_{i+1} / (1 - alpha_i).
 //
 // Backward: the gradient fields of an entry are sums over a quadrant's pixels
-// and run on the FP32 matrix cores as a contraction over the pixels; after
-// each chunk the wave adds the sums to the per-slot 2D gradient buffer with
-// one float atomic per nonzero field.
+// of products with two per-pixel values, which pass through LDS so that a lane
+// sums a row of pixels of one entry in registers; after each chunk the wave
+// adds the sums to the per-slot 2D gradient buffer with one float atomic per
+// nonzero field.
 #include "gs_internal.h"
 
 namespace gs {
@@ -808,15 +809,17 @@ __device__ __forceinline__ int stage_gathered_bwd(const GatherBwd& e, int pos, c
 // that depend on the pixel and the entry's mean alone: dp times 1, dx, dy,
 // dx^2, dx dy, dy^2 and w times the pixel's upstream gradient.  The walk only
 // leaves dp and w in LDS; every 8 entries they are read back transposed, lane
-// (y, entry) taking the 8 pixels of row y, which it sums in registers with the
-// row's moments in X (the pixel centre relative to the quadrant's centre;
-// |X| <= 3.5 keeps the shift to dx near the size of what it yields) and with dy
-// constant.  Three exchanges over the 8 rows finish the sums.  That is about
-// 12 VALU instructions per entry; a sum of each field over the wave by lane
-// exchanges takes 30 and its products 14 more (0.60 ms at 6M Gaussians, 1080p,
-// bound by VALU issue).  The FP32 matrix instructions were measured too: they
-// share the vector units' time (an fma beside v_mfma_f32_16x16x4_f32 adds its
-// own) and fill a third of a product here, 27 ns per entry against 14.
+// (y, entry) taking the 8 pixels of row y, whose dp, dp dx and dp dx^2 it sums in
+// registers; dy is constant in a row.  Three exchanges over the 8 rows finish the
+// sums.  That is about 14 VALU instructions per entry; a sum of each field over the
+// wave by lane exchanges takes 30 and its products 14 more (6M Gaussians, 1080p,
+// bound by VALU issue: 0.67 ms, 0.55 now).  (Moments about the quadrant's centre,
+// shifted to the mean after the sum, save two more instructions and 1 % of the
+// time, but cancel: for Gaussians of pixel size near a quadrant's corner dp dx^2
+// came out with 26 times the rounding error of its products.)  The FP32 matrix
+// instructions were measured too: they share the vector units' time (an fma beside
+// v_mfma_f32_16x16x4_f32 adds its own) and fill a third of a product here, 27 ns
+// per entry against 14.
 // The AbsGS sums (kAbs) come from the same rows: |dp| |2 qa dx + qb dy| and
 // |dp| |qb dx + 2 qc dy| per pixel.
 //
@@ -921,30 +924,31 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
         const float4 a = st.r[k][0], b = st.r[k][1];
         const float* q = &st.q[tj * kQRow + 8 * ty];
         const float4 p0 = *reinterpret_cast<const float4*>(q), p1 = *reinterpret_cast<const float4*>(q + 4);
-        const float mx = a.x - pc.qcx, dy = Yc - a.y;
-        float v[12];
-        {
-            // moments of dp over the row, from its values at +-X
-            const float s0 = p1.x + p0.w, s1 = p1.y + p0.z, s2 = p1.z + p0.y, s3 = p1.w + p0.x;
-            const float d0 = p1.x - p0.w, d1 = p1.y - p0.z, d2 = p1.z - p0.y, d3 = p1.w - p0.x;
-            const float m0 = (s0 + s1) + (s2 + s3);
-            const float m1 = fmaf(3.5f, d3, fmaf(2.5f, d2, fmaf(1.5f, d1, 0.5f * d0)));
-            const float m2 = fmaf(12.25f, s3, fmaf(6.25f, s2, fmaf(2.25f, s1, 0.25f * s0)));
-            const float sx = fmaf(-mx, m0, m1), sy = dy * m0;       // sums of dp dx, dp dy
-            v[0] = -kLn2 * fmaf(a.z + a.z, sx, a.w * sy);
-            v[1] = -kLn2 * fmaf(a.w, sx, (b.x + b.x) * sy);
-            v[2] = -0.5f * fmaf(-mx, m1 + sx, m2);                  // dp dx^2
-            v[3] = -dy * sx;
-            v[4] = -0.5f * dy * sy;
-            v[5] = m0 * __builtin_amdgcn_rcpf(b.y);                 // dp = dL/d opacity' opacity'
+        const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+        // the mean from the quadrant's left edge: exact where a pixel may lie near it
+        const float mx = a.x - (pc.qcx - 4.0f), dy = Yc - a.y;
+        float m0 = 0.0f, sx = 0.0f, sxx = 0.0f;      // sums of dp, dp dx, dp dx^2
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const float dx = ((float)x + 0.5f) - mx, px = pv[x] * dx;
+            m0 += pv[x];
+            sx += px;
+            sxx = fmaf(px, dx, sxx);
         }
+        const float sy = dy * m0;
+        float v[12];
+        v[0] = -kLn2 * fmaf(a.z + a.z, sx, a.w * sy);
+        v[1] = -kLn2 * fmaf(a.w, sx, (b.x + b.x) * sy);
+        v[2] = -0.5f * sxx;
+        v[3] = -dy * sx;
+        v[4] = -0.5f * dy * sy;
+        v[5] = m0 * __builtin_amdgcn_rcpf(b.y);                 // dp = dL/d opacity' opacity'
         if (kAbs) {
             const float qb = 0.5f * a.w, hx0 = qb * dy, hy0 = b.x * dy;
-            const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
             float ax = 0.0f, ay = 0.0f;
 #pragma unroll
             for (int x = 0; x < 8; ++x) {
-                const float dx = ((float)x - 3.5f) - mx;
+                const float dx = ((float)x + 0.5f) - mx;
                 ax = fmaf(fabsf(pv[x]), fabsf(fmaf(a.z, dx, hx0)), ax);
                 ay = fmaf(fabsf(pv[x]), fabsf(fmaf(qb, dx, hy0)), ay);
             }
