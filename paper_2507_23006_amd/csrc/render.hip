@@ -1022,10 +1022,11 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
 
     // One entry at the lane's pixel, as far as it does not depend on the
     // entries behind it.  An entry the pixel did not composite takes alpha =
-    // 0, which leaves T and S unchanged exactly.
+    // 0, which leaves T and S unchanged exactly; its dp is left out, not
+    // multiplied by 0 (kr is not finite where the gradient of alpha is not).
     struct Step {
-        float al, alp, r, kr, gc;
-        bool any;
+        float al, r, kr, gc;
+        bool grad, any;
     };
     const float K = gA * (T * Q);      // dL/dalpha_i holds g_alpha T_final / (1 - alpha_i)
     auto step = [&](const float4& a, const float4& b, const float4& c) {
@@ -1034,7 +1035,7 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
         const bool con = __float_as_int(c.w) <= last && e.keep;      // c.w: 1-based position
         p.any = __ballot(con) != 0;
         p.al = con ? e.alpha : 0.0f;
-        p.alp = e.raw < kAlphaMax ? p.al : 0.0f;                     // no gradient through the clamp
+        p.grad = con && e.raw < kAlphaMax;                           // no gradient through the clamp
         p.r = __builtin_amdgcn_rcpf(1.0f - p.al);
         p.kr = K * p.r;
         p.gc = fmaf(gC0, c.x, fmaf(gC1, c.y, fmaf(gC2, c.z, gD * b.z)));   // g . (colour, depth)
@@ -1066,7 +1067,7 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
             const float4 a = rn[0], b = rn[1], c = rn[2];
             const float Ti = T * p.r;
             const float df = p.gc - S;
-            const float dp = fmaf(Ti, df, p.kr) * p.alp;       // dL/d power (natural-log units)
+            const float dp = p.grad ? fmaf(Ti, df, p.kr) * p.al : 0.0f;       // dL/d power (natural-log units)
             q[0] = dp;
             q[kQW] = p.al * Ti;
             S = fmaf(p.al, df, S);
