@@ -242,6 +242,11 @@ int32_t seg_len_of(int64_t n_tiles) {
     return n_tiles <= 4096 ? kSegLenSmall : n_tiles <= 12288 ? kSegLen : n_tiles <= 28672 ? kSegLenLarge : kSegLenHuge;
 }
 
+// every list of L positions leaves ceil(L / seg_len) - 1 states
+size_t seg_bytes_for(int64_t n_tiles, int64_t n_pairs, int32_t seg_len) {
+    return seg_fixed_bytes(n_tiles) + ((size_t)n_pairs / seg_len + 1) * kSegStateBytes;
+}
+
 // a plan over `base` (NULL or too small: no segments)
 void seg_layout(void* base, size_t bytes, int64_t n_tiles, int32_t seg_len, SegPlan* plan, uint32_t* capacity) {
     *plan = SegPlan{nullptr, nullptr, nullptr, (uint32_t)n_tiles, nullptr, 0u, nullptr, (uint32_t)seg_len};
@@ -533,7 +538,7 @@ const float* gs_render_bwd_grad2d(void* ws) { return static_cast<const float*>(w
 size_t gs_seg_workspace_size(int64_t n_tiles, int64_t n_pairs) {
     if (n_tiles < 1) n_tiles = 1;
     if (n_pairs < 0) n_pairs = 0;
-    return seg_fixed_bytes(n_tiles) + ((size_t)n_pairs / seg_len_of(n_tiles) + 1) * kSegStateBytes;
+    return seg_bytes_for(n_tiles, n_pairs, seg_len_of(n_tiles));
 }
 
 int gs_render_fwd_seg(const gs_projected* proj, const uint32_t* pair_vals, const uint32_t* tile_ranges,

@@ -58,6 +58,8 @@ size_t seg_fixed_bytes(int64_t n_tiles);
 void seg_layout(void* base, size_t bytes, int64_t n_tiles, int32_t seg_len, SegPlan* plan, uint32_t* capacity);
 // positions per segment for a launch of n_tiles tiles
 int32_t seg_len_of(int64_t n_tiles);
+// bytes of an area that holds every state of lists with n_pairs positions in all
+size_t seg_bytes_for(int64_t n_tiles, int64_t n_pairs, int32_t seg_len);
 
 // workspace bytes of bin_sort_slots
 size_t bin_workspace_bytes(int64_t n_slots, int64_t pair_capacity);

@@ -361,7 +361,7 @@ int alloc_set(gs_server* s, BufSet& b) {
     GS_HIP(dev_alloc(&b.last, (size_t)X));
     GS_HIP(dev_alloc(&b.npairs_dev, 1));
     GS_HIP(dev_alloc(&b.work, 1));
-    b.seg_bytes = gs_seg_workspace_size(s->tile_cap, Pc);
+    b.seg_bytes = seg_bytes_for(s->tile_cap, Pc, kSegLen);     // the length that launch_batch plans with
     GS_HIP(hipMalloc(&b.seg, b.seg_bytes));
     GS_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.npairs_host), sizeof(int64_t), hipHostMallocDefault));
     GS_HIP(hipEventCreateWithFlags(&b.prepped, hipEventDisableTiming));
@@ -430,10 +430,13 @@ int launch_batch(Worker* w, BufSet& b, Request* r, int nb, bool full_bound = fal
     }
     // long lists composited in segments (one workgroup per tile when the
     // compositing is persistent), of one length whatever the batch: their
-    // length groups the products, and an image does not depend on its batch
+    // length groups the products, and an image does not depend on its batch.  The
+    // area holds the states of pair_capacity positions; the launches over states
+    // are sized by those of the batch's pair bound
     SegPlan plan;
     uint32_t cap = 0;
     seg_layout(b.seg, b.seg_bytes, vt.total_tiles, kSegLen, &plan, &cap);
+    cap = plan.capacity = (uint32_t)std::min<int64_t>(cap, b.pair_bound / kSegLen + 1);
     const bool segmented = plan.work_off && slots > 0 && s->cfg.persistent_ctas == 0;
     if (segmented)
         GS_HIP(launch_seg_plan(b.proj, reinterpret_cast<const uint2*>(b.ranges), vt, cap, plan, w->render));
