@@ -213,13 +213,13 @@ size_t bin_layout(int64_t n_slots, int64_t cap, void* base, BinWs* w) {
 
 }  // namespace
 
-// segment area: work_off [T + 1] | state_off [T + 1] | info [2] |
+// segment area: work_off [T + 1] | state_off [T + 1] | info [kPlanInfo] |
 // stop_seg [T][256] | states [capacity][kSegFields][256]
 size_t seg_fixed_bytes(int64_t n_tiles) {
     Carver c(nullptr);
     c.take<uint32_t>((size_t)n_tiles + 1);
     c.take<uint32_t>((size_t)n_tiles + 1);
-    c.take<uint32_t>(2);
+    c.take<uint32_t>(kPlanInfo);
     c.take<int32_t>((size_t)n_tiles * 256);
     return c.off;
 }
@@ -242,9 +242,17 @@ int32_t seg_len_of(int64_t n_tiles) {
     return n_tiles <= 4096 ? kSegLenSmall : n_tiles <= 12288 ? kSegLen : n_tiles <= 28672 ? kSegLenLarge : kSegLenHuge;
 }
 
-// every list of L positions leaves ceil(L / seg_len) - 1 states
+// Every list of L positions leaves ceil(L / seg_len) - 1 states.  Short segments
+// are for launches whose waves do not fill the device: their states are bounded by
+// kSegStatesSmall (200 MB; with 8 waves of four quadrants per SIMD 2048 states are
+// in work at once), and the plan takes kSegLen where more would be stored.  Unbounded
+// they took 48 bytes for each pair of room, 1.15 GB for the 24M of a first binning of
+// 6M Gaussians where this is 0.29, and launches of four times the workgroups.
 size_t seg_bytes_for(int64_t n_tiles, int64_t n_pairs, int32_t seg_len) {
-    return seg_fixed_bytes(n_tiles) + ((size_t)n_pairs / seg_len + 1) * kSegStateBytes;
+    size_t states = (size_t)n_pairs / seg_len + 1;
+    if (seg_len == kSegLenSmall)
+        states = std::max(std::min(states, (size_t)kSegStatesSmall), (size_t)n_pairs / kSegLen + 1);
+    return seg_fixed_bytes(n_tiles) + states * kSegStateBytes;
 }
 
 // a plan over `base` (NULL or too small: no segments)
@@ -256,7 +264,7 @@ void seg_layout(void* base, size_t bytes, int64_t n_tiles, int32_t seg_len, SegP
     Carver c(base);
     plan->work_off = c.take<uint32_t>((size_t)n_tiles + 1);
     plan->state_off = c.take<uint32_t>((size_t)n_tiles + 1);
-    plan->info = c.take<uint32_t>(2);
+    plan->info = c.take<uint32_t>(kPlanInfo);
     plan->stop_seg = c.take<int32_t>((size_t)n_tiles * 256);
     plan->state = reinterpret_cast<float*>(static_cast<char*>(base) + fixed);
     *capacity = (uint32_t)std::min<size_t>((bytes - fixed) / kSegStateBytes, 1u << 24);

@@ -256,8 +256,11 @@ constexpr int kSegLen = 512;          // of one full-HD view, and of served batc
 constexpr int kSegLenLarge = 1024;    // of a few views,
 constexpr int kSegLenHuge = 2048;     // and of more
 constexpr int kHeadLen = 1024;        // a multiple of the first three
+constexpr int kSegStatesSmall = 1 << 15;     // stored states of a launch in segments of kSegLenSmall at most
 constexpr int kPlanLong = 0;          // SegPlan::info: launch positions up to the last one with several segments
 constexpr int kPlanHead = 1;          // segments in the head
+constexpr int kPlanLen = 2;           // list positions per segment
+constexpr int kPlanInfo = 3;
 constexpr int kSegFields = 6;
 struct SegPlan {
     uint32_t* work_off;    // null: one work item per tile, no segments
@@ -266,8 +269,9 @@ struct SegPlan {
     uint32_t n_tiles;
     int32_t* stop_seg;
     uint32_t capacity;     // stored states the area holds
-    uint32_t* info;        // [2]: kPlanLong, kPlanHead
-    uint32_t seg_len;      // list positions per segment (a power of two, at least 64)
+    uint32_t* info;        // [kPlanInfo]: kPlanLong, kPlanHead, kPlanLen
+    uint32_t seg_len;      // list positions per segment (a power of two, at least 64); kSegLenSmall
+                           // becomes kSegLen where it would take more than kSegStatesSmall states
 };
 // plans the segments of every tile (segments disabled when they need more
 // than `capacity` stored states)

@@ -475,9 +475,10 @@ __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict_
     const int tile = launch_tile(tile_order, vt);
     int32_t* head_stop = nullptr;
     float* head_states = nullptr;
-    uint32_t head_len = kHeadLen;
+    uint32_t seg_len = kSegLen, head_len = kHeadLen;
     if (plan.work_off) {
-        head_len = plan.info[kPlanHead] * plan.seg_len;
+        seg_len = plan.info[kPlanLen];
+        head_len = plan.info[kPlanHead] * seg_len;
         const uint32_t i = blockIdx.x;
         if (plan.work_off[i + 1] - plan.work_off[i] > 1u) {
             head_stop = plan.stop_seg + (size_t)tile * 256;
@@ -485,8 +486,7 @@ __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict_
         }
     }
     render_fwd_quadrant(rec, pair_vals, ranges, vt, opt, tile, wave, lane, stage[wave], rgb, depth, alpha_out, T_out,
-                        last_out, head_stop, head_states, plan.seg_len,
-                        head_len);
+                        last_out, head_stop, head_states, seg_len, head_len);
 }
 
 // Pass 2, one workgroup per stored segment: the segment's state for the
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256, 7) void k_fwd_segments(const float4* __restric
     const PixelCoords pc = pixel_coords(vt, tile, wave, lane);
     const bool on = pc.inside && plan.stop_seg[(size_t)tile * 256 + pc.ly * kTile + pc.lx] == kSegAlive;
     if (__ballot(on) == 0) return;
-    render_fwd_segment(rec, pair_vals, ranges[tile], pc, on, it.seg, plan.seg_len, lane, stage[wave],
+    render_fwd_segment(rec, pair_vals, ranges[tile], pc, on, it.seg, plan.info[kPlanLen], lane, stage[wave],
                        plan.state + (size_t)b * kSegFields * 256);
 }
 
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ r
         D0 = depth[p];
         last = last_out[p];
     }
-    const uint32_t lo = rg.x + (uint32_t)it.seg * plan.seg_len, hi = min(lo + plan.seg_len, rg.y);
+    const uint32_t seg_len = plan.info[kPlanLen], lo = rg.x + (uint32_t)it.seg * seg_len, hi = min(lo + seg_len, rg.y);
     float Tl = 1.0f, l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, Dl = 0.0f;
     Gather cur = load_entry(rec, load_slot(pair_vals, lo + lane, hi));
     uint32_t s_next = load_slot(pair_vals, lo + kChunk + lane, hi);
@@ -888,9 +888,9 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
     // entry are the identity).
     int lo = 0, hi = maxlast;
     if (nseg > 1) {
-        const int px = pc.ly * kTile + pc.lx;
+        const int px = pc.ly * kTile + pc.lx, seg_len = (int)plan.info[kPlanLen];
         for (int j = nseg - 1; j > seg; --j) {
-            if (j * (int)plan.seg_len >= last) continue;
+            if (j * seg_len >= last) continue;
             const float* sj = plan.state + (size_t)(st0 + (uint32_t)(j - 1)) * kSegFields * 256;
             const float Ts = sj[0 * 256 + px];
             const float gcs = fmaf(gC0, sj[1 * 256 + px],
@@ -899,8 +899,8 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
             T = T / Ts;
             Q = Q * Ts;
         }
-        lo = seg * (int)plan.seg_len;
-        hi = min(lo + (int)plan.seg_len, maxlast);
+        lo = seg * seg_len;
+        hi = min(lo + seg_len, maxlast);
     }
     if (hi <= lo) return;
 
@@ -1096,7 +1096,8 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
 
 // Segments per tile in launch order (ceil(L / seg_len) for a list of L > seg_len
 // positions, else 1) and the stored states (segments 1 .. n - 1); exclusive
-// prefix sums into work_off / state_off.  When the states would exceed
+// prefix sums into work_off / state_off.  kSegLenSmall gives way to kSegLen where
+// it would store more than kSegStatesSmall states.  When the states would exceed
 // `capacity`, every tile keeps a single segment.  A workgroup takes kPlanSpan
 // positions, kPlanPer consecutive ones per thread, so that the order is read and
 // the offsets are written in whole lines; with several workgroups a first launch
@@ -1106,13 +1107,22 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
 constexpr int kPlanThreads = 256, kPlanPer = 8, kPlanSpan = kPlanThreads * kPlanPer;
 
 struct PlanSum {
-    uint32_t items, most, end_long;      // segments, most of a list, position after the last list with several
-};
+    uint32_t longest;                    // list
+    uint32_t items[2], end_long[2];      // segments, position after the last list with several; of seg_len
+};                                       // positions, and of the length that seg_len may give way to
 
-// of positions i0 .. i0 + kPlanPer - 1; c: their segments (0 past the end)
+__device__ __forceinline__ uint32_t plan_alternative(uint32_t seg_len) {
+    return seg_len == (uint32_t)kSegLenSmall ? (uint32_t)kSegLen : seg_len;
+}
+
+__device__ __forceinline__ uint32_t segments_of(uint32_t L, uint32_t seg_len) {
+    return L > seg_len ? (L + seg_len - 1) >> __builtin_ctz(seg_len) : 1u;
+}
+
+// of positions i0 .. i0 + kPlanPer - 1; L: their lists' lengths
 __device__ __forceinline__ PlanSum plan_positions(const uint2* __restrict__ ranges,
                                                   const uint32_t* __restrict__ tile_order, const ViewTable& vt,
-                                                  uint32_t seg_len, uint32_t i0, uint32_t c[kPlanPer]) {
+                                                  uint32_t seg_len, uint32_t i0, uint32_t L[kPlanPer]) {
     const uint32_t n_tiles = (uint32_t)vt.total_tiles;
     int t[kPlanPer];
 #pragma unroll
@@ -1120,36 +1130,51 @@ __device__ __forceinline__ PlanSum plan_positions(const uint2* __restrict__ rang
     uint2 r[kPlanPer];
 #pragma unroll
     for (int u = 0; u < kPlanPer; ++u) r[u] = t[u] >= 0 ? ranges[t[u]] : make_uint2(0u, 0u);
-    PlanSum s{0u, 0u, 0u};
+    PlanSum s{0u, {0u, 0u}, {0u, 0u}};
 #pragma unroll
     for (int u = 0; u < kPlanPer; ++u) {
-        const uint32_t L = r[u].y - r[u].x;
-        c[u] = t[u] < 0 ? 0u : L > seg_len ? (L + seg_len - 1) / seg_len : 1u;
-        if (c[u] > 1u) s.end_long = i0 + u + 1;
-        s.most = max(s.most, c[u]);
-        s.items += c[u];
+        L[u] = r[u].y - r[u].x;
+        s.longest = max(s.longest, L[u]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t c = t[u] < 0 ? 0u : segments_of(L[u], k ? plan_alternative(seg_len) : seg_len);
+            if (c > 1u) s.end_long[k] = i0 + u + 1;
+            s.items[k] += c;
+        }
     }
     return s;
+}
+
+// of two parts of the positions
+__device__ __forceinline__ PlanSum plan_join(PlanSum a, const PlanSum& b) {
+    a.longest = max(a.longest, b.longest);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        a.items[k] += b.items[k];
+        a.end_long[k] = max(a.end_long[k], b.end_long[k]);
+    }
+    return a;
 }
 
 // over the workgroup, in every thread (s: one a wave)
 __device__ __forceinline__ PlanSum plan_reduce(PlanSum v, PlanSum* s) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
-        v.items += (uint32_t)__shfl_xor((int)v.items, off, 64);
-        v.most = max(v.most, (uint32_t)__shfl_xor((int)v.most, off, 64));
-        v.end_long = max(v.end_long, (uint32_t)__shfl_xor((int)v.end_long, off, 64));
+        PlanSum y;
+        y.longest = (uint32_t)__shfl_xor((int)v.longest, off, 64);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            y.items[k] = (uint32_t)__shfl_xor((int)v.items[k], off, 64);
+            y.end_long[k] = (uint32_t)__shfl_xor((int)v.end_long[k], off, 64);
+        }
+        v = plan_join(v, y);
     }
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
     __syncthreads();
     v = s[0];
 #pragma unroll
-    for (int w = 1; w < kPlanThreads / 64; ++w) {
-        v.items += s[w].items;
-        v.most = max(v.most, s[w].most);
-        v.end_long = max(v.end_long, s[w].end_long);
-    }
+    for (int w = 1; w < kPlanThreads / 64; ++w) v = plan_join(v, s[w]);
     return v;
 }
 
@@ -1157,9 +1182,9 @@ __global__ __launch_bounds__(kPlanThreads) void k_seg_sums(const uint2* __restri
                                                            const uint32_t* __restrict__ tile_order, ViewTable vt,
                                                            uint32_t seg_len, PlanSum* __restrict__ sums) {
     __shared__ PlanSum s_red[kPlanThreads / 64];
-    uint32_t c[kPlanPer];
+    uint32_t L[kPlanPer];
     const PlanSum v = plan_reduce(plan_positions(ranges, tile_order, vt, seg_len,
-                                                 blockIdx.x * kPlanSpan + threadIdx.x * kPlanPer, c), s_red);
+                                                 blockIdx.x * kPlanSpan + threadIdx.x * kPlanPer, L), s_red);
     if (threadIdx.x == 0) sums[blockIdx.x] = v;
 }
 
@@ -1174,26 +1199,27 @@ __global__ __launch_bounds__(kPlanThreads) void k_seg_plan(const uint2* __restri
     const uint32_t n_tiles = (uint32_t)vt.total_tiles;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t i0 = blockIdx.x * kPlanSpan + threadIdx.x * kPlanPer;
-    uint32_t c[kPlanPer];
-    const PlanSum mine = plan_positions(ranges, tile_order, vt, seg_len, i0, c);
+    uint32_t L[kPlanPer];
+    const PlanSum mine = plan_positions(ranges, tile_order, vt, seg_len, i0, L);
     // segments of the earlier workgroups, and of all
-    PlanSum all = mine;
-    uint32_t before = 0;
+    PlanSum all = mine, early{0u, {0u, 0u}, {0u, 0u}};
     if (gridDim.x > 1) {
-        PlanSum early{0u, 0u, 0u};
-        all = PlanSum{0u, 0u, 0u};
+        all = early;
         for (uint32_t b = threadIdx.x; b < gridDim.x; b += kPlanThreads) {
             const PlanSum x = sums[b];
-            if (b < blockIdx.x) early.items += x.items;
-            all.items += x.items;
-            all.most = max(all.most, x.most);
-            all.end_long = max(all.end_long, x.end_long);
+            if (b < blockIdx.x) early = plan_join(early, x);
+            all = plan_join(all, x);
         }
-        before = plan_reduce(early, s_red).items;
+        early = plan_reduce(early, s_red);
     }
     all = plan_reduce(all, s_red);
+    const bool other = all.items[0] - n_tiles > (uint32_t)kSegStatesSmall;
+    const uint32_t len = other ? plan_alternative(seg_len) : seg_len;
+    const uint32_t items = other ? all.items[1] : all.items[0];
+    const uint32_t end_long = other ? all.end_long[1] : all.end_long[0];
+    const uint32_t here = other ? mine.items[1] : mine.items[0];
     // exclusive scan over the workgroup's threads
-    uint32_t incl = mine.items;
+    uint32_t incl = here;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const uint32_t y = __shfl_up(incl, off, 64);
@@ -1201,24 +1227,25 @@ __global__ __launch_bounds__(kPlanThreads) void k_seg_plan(const uint2* __restri
     }
     if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
-    uint32_t w = before + incl - mine.items;
+    uint32_t w = (other ? early.items[1] : early.items[0]) + incl - here;
     for (int k = 0; k < wave; ++k) w += s_wave[k];
-    const uint32_t need = all.items - n_tiles;
+    const uint32_t need = items - n_tiles;
     const bool on = need <= capacity;      // do the states fit?
 #pragma unroll
     for (int u = 0; u < kPlanPer; ++u) {
         if (i0 + u >= n_tiles) break;
         work_off[i0 + u] = on ? w : i0 + u;
         state_off[i0 + u] = on ? w - (i0 + u) : 0u;
-        w += c[u];
+        w += segments_of(L[u], len);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        work_off[n_tiles] = on ? all.items : n_tiles;
+        work_off[n_tiles] = on ? items : n_tiles;
         state_off[n_tiles] = on ? need : 0u;
-        info[kPlanLong] = on && all.most > 1u ? all.end_long : 0u;
+        info[kPlanLong] = on ? end_long : 0u;
         // lists up to kHeadLen are composited by the head alone when none is
         // longer: the later passes cost more than a head that long
-        info[kPlanHead] = all.most * seg_len > (uint32_t)kHeadLen ? 2u : (uint32_t)kHeadLen / seg_len;
+        info[kPlanHead] = segments_of(all.longest, len) * len > (uint32_t)kHeadLen ? 2u : (uint32_t)kHeadLen / len;
+        info[kPlanLen] = len;
     }
 }
 
@@ -1246,7 +1273,7 @@ __global__ __launch_bounds__(256) void k_seg_prepass(const float4* __restrict__ 
     int maxlast = last;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, off, 64));
-    const int lo = j * (int)plan.seg_len, hi = min(lo + (int)plan.seg_len, maxlast);
+    const int seg_len = (int)plan.info[kPlanLen], lo = j * seg_len, hi = min(lo + seg_len, maxlast);
     float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, D = 0.0f;
     for (int b0 = lo; b0 < hi; b0 += kChunk) {
         const Gather e = load_entry(rec, load_slot(pair_vals, rg.x + (uint32_t)(b0 + lane), rg.x + (uint32_t)hi));
