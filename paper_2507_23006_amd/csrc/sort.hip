@@ -20,6 +20,7 @@
 // render of 120k Gaussians takes 176 instead of 182 us).
 // Stability: inside a wave items are ranked in (round, lane) order, waves
 // and tiles are concatenated in order, so equal keys keep input order.
+#include "chunks.h"
 #include "gs_internal.h"
 
 namespace gs {
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* __re
         s_buf[threadIdx.x * kScanIpt + r] = pre;
         // the chunks of the counted items that start in this element's
         if (v[r])
-            for (uint32_t c = (pre + chunk - 1) / chunk; c <= (pre + v[r] - 1) / chunk; ++c)
+            for (uint32_t c = first_chunk(pre, chunk); c <= (pre + v[r] - 1) / chunk; ++c)
                 chunk_first[c] = base + threadIdx.x * kScanIpt + r;
         pre += v[r];
     }
