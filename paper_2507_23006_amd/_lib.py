@@ -6,6 +6,9 @@ import ctypes as C
 import os
 import threading
 
+import numpy as np
+import torch
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libgs.so")
 
@@ -174,14 +177,31 @@ def check(rc: int) -> None:
         raise GsError(rc, load().gs_last_error().decode(errors="replace"))
 
 
+def _rows(m):
+    """Rows of a matrix: a plain array's or tensor's by one call (16 reads of
+    single elements take a quarter of a small step's host time), every other
+    form (sparse, masked, complex, with a column axis, nested sequences) as it
+    iterates."""
+    if type(m) is np.ndarray:
+        plain = m.ndim == 2 and m.dtype.kind in "fiub"
+    elif type(m) is torch.Tensor:
+        plain = m.dim() == 2 and m.layout is torch.strided and m.dtype in _REAL
+    else:
+        plain = False
+    return m.tolist() if plain else m
+
+
+_REAL = {torch.float64, torch.float32, torch.float16, torch.bfloat16, torch.int64, torch.int32, torch.int16,
+         torch.int8, torch.uint8, torch.bool}
+
+
 def make_cameras(cams) -> C.Array:
     """Camera objects with fx, fy, cx, cy, viewmat (4x4), width, height,
     near, far attributes -> gs_camera[n]."""
     arr = (GsCamera * len(cams))()
     for i, c in enumerate(cams):
         arr[i].fx, arr[i].fy, arr[i].cx, arr[i].cy = float(c.fx), float(c.fy), float(c.cx), float(c.cy)
-        m = c.viewmat.tolist() if hasattr(c.viewmat, "tolist") else c.viewmat     # one call for an array or a tensor
-        vm = [float(x) for row in m for x in row]
+        vm = [float(x) for row in _rows(c.viewmat) for x in row]
         for k in range(16):
             arr[i].viewmat[k] = vm[k]
         arr[i].width, arr[i].height = int(c.width), int(c.height)
