@@ -206,12 +206,17 @@ int gs_render_count(const gs_projected *proj, const uint32_t *pair_vals, const u
  * per-slot 2D gradients, optionally followed (gs_render_bwd) or given
  * separately (gs_composite_bwd's seg_ws) by gs_seg_workspace_size(n_tiles,
  * n_pairs) bytes for the segmented walk: tile lists longer than a segment
- * (128 positions for launches of at most 4096 tiles, 512 to 12288, 1024 to 28672,
- * else 2048) are then walked in
- * segments by separate workgroups, each starting from the transmittance and colour behind it
- * (folded from per-segment states a pre-pass computes), so the longest
- * lists no longer serialise the launch.  A smaller or absent segment area
- * walks every list whole; results agree to float rounding either way. */
+ * (128 positions for launches of at most 4096 tiles, 512 to 12288, 1024 to
+ * 28672, else 2048; 512 instead of 128 where the shorter ones would leave more
+ * than 32768 states) are then walked in segments by separate workgroups, each
+ * starting from the transmittance and colour behind it (folded from
+ * per-segment states a pre-pass computes), so the longest lists no longer
+ * serialise the launch.  A state takes 6 KB; the area holds one for each
+ * segment length of pairs, of 128 positions at most 32768, so its size does
+ * not grow with n_tiles throughout: an area for launches of several sizes
+ * takes the largest of theirs.  A smaller or absent segment area walks every
+ * list whole; results agree to float rounding either way, and the last bits
+ * of an image depend on the tiles of the launch that renders it. */
 size_t gs_render_bwd_workspace_size(int64_t n_slots);
 size_t gs_seg_workspace_size(int64_t n_tiles, int64_t n_pairs);
 
@@ -523,10 +528,12 @@ int gs_lod_select(const gs_lod_table *table, const gs_camera *cam, int64_t budge
  * current one (the other), ordered by events, with no host wait in between.
  * A batch whose pairs still overflow pair_capacity is split in halves and
  * re-rendered (counted in split_batches); a single request that overflows
- * completes with GS_ERR_CAPACITY.  The rendered image is the image
- * gs_render_fwd_seg gives for the selected Gaussians alone (with
- * persistent compositing, gs_render_fwd's), whatever the batch or the
- * pipeline depth. */
+ * completes with GS_ERR_CAPACITY.  The rendered image has the same bits
+ * whatever the batch or the pipeline depth.  It is composited in segments of
+ * 512 positions whatever its tiles: the image gs_render_fwd_seg gives for the
+ * selected Gaussians alone, bit for bit where that takes 512 as well (4097 to
+ * 12288 tiles), else to float rounding (with persistent compositing,
+ * gs_render_fwd's image bit for bit). */
 typedef struct gs_serve_config {
     int32_t max_views_per_batch;   /* 1..GS_MAX_VIEWS; 1 = one request per launch */
     int32_t n_streams;             /* worker threads, 1..8 */
@@ -535,8 +542,8 @@ typedef struct gs_serve_config {
     int64_t pixel_capacity;        /* pixels per batch */
     int32_t queue_capacity;        /* pending requests; gs_serve_submit returns GS_EAGAIN beyond */
     int32_t pipeline_depth;        /* batches in flight per worker (buffer sets), 1..4 */
-    int32_t persistent_ctas;       /* 0: lists longer than 512 positions composited in segments
-                                      (gs_render_fwd_seg); > 0: persistent compositing, every list walked
+    int32_t persistent_ctas;       /* 0: lists longer than 512 positions composited in segments of that
+                                      length; > 0: persistent compositing, every list walked
                                       whole, by at most this many workgroups taking tiles from a counter */
     double pairs_per_gaussian;     /* admission ratio for image sizes not yet rendered; 0 = 8 */
 } gs_serve_config;
