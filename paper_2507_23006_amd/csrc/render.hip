@@ -301,11 +301,14 @@ constexpr int32_t kSegAlive = 0x7fffffff;
 // ends there) get their outputs and stop_seg = -1, the others their state
 // after it (rgb without background, depth, T, last) and stop_seg =
 // kSegAlive.  The head also writes the backward's states of its segments from
-// 1 on (seg_len positions; head_states: the tile's first stored state) from the
-// pixel's (T, C, D) at the segment's ends: T_seg = T_end / T_start and
-// C_seg = (C_end - C_start) / T_start -- the segment's composite with T
-// restarted at 1; the backward uses C_seg scaled back by T_start, so the
-// subtraction's rounding stays at the size of C's.
+// 1 on (seg_len positions; head_states: the tile's first stored state): T_seg =
+// T_end / T_start and C_seg = C / T_start, C the segment's own part of the sum --
+// its composite with T restarted at 1.  So the sums restart at each segment (of
+// kSegLen positions in a walk of the whole list) and the parts are added up: the
+// difference of a running sum at the segment's ends would carry rounding at the
+// size of the whole sum, which is large beside a deep segment's part (4096
+// Gaussians at 160x120, several segments of 128 to a head: opacity and mean
+// gradients twice as far from float64, and the image 1.3 times).
 __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ rec,
                                                     const uint32_t* __restrict__ pair_vals,
                                                     const uint2* __restrict__ ranges, const ViewTable& vt,
@@ -323,7 +326,7 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
     float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, D = 0.0f;
     int last = 0;
     bool alive = pc.inside;
-    // (T, C, D) at the start of the current segment (head walks only)
+    // T at the start of the current segment, and the earlier ones' (C, D)
     float sT = 1.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, sD = 0.0f;
     int seg = 0;
     const int px = pc.ly * kTile + pc.lx;
@@ -331,22 +334,23 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
         float* o = head_states + (size_t)(seg - 1) * kSegFields * 256;
         const float inv = 1.0f / sT;
         o[0 * 256 + px] = T * inv;
-        o[1 * 256 + px] = (c0 - s0) * inv;
-        o[2 * 256 + px] = (c1 - s1) * inv;
-        o[3 * 256 + px] = (c2 - s2) * inv;
-        o[4 * 256 + px] = (D - sD) * inv;
+        o[1 * 256 + px] = c0 * inv;
+        o[2 * 256 + px] = c1 * inv;
+        o[3 * 256 + px] = c2 * inv;
+        o[4 * 256 + px] = D * inv;
     };
     Gather cur = load_entry(rec, load_slot(pair_vals, rg.x + lane, end));
     uint32_t s_next = load_slot(pair_vals, rg.x + kChunk + lane, end);
     for (uint32_t j0 = rg.x; j0 < end; j0 += kChunk) {
-        if (head_states && j0 != rg.x && ((j0 - rg.x) & (seg_len - 1u)) == 0) {
-            if (seg >= 1) seg_state();
+        if (j0 != rg.x && ((j0 - rg.x) & (seg_len - 1u)) == 0) {
+            if (head_states && seg >= 1) seg_state();
             ++seg;
             sT = T;
-            s0 = c0;
-            s1 = c1;
-            s2 = c2;
-            sD = D;
+            s0 += c0;
+            s1 += c1;
+            s2 += c2;
+            sD += D;
+            c0 = c1 = c2 = D = 0.0f;
         }
         if (__ballot(alive) == 0) break;     // every pixel of the quadrant has stopped
         const int n = stage_gathered(cur, (int)(j0 - rg.x) + lane + 1, pc, lane, st);
@@ -381,6 +385,10 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
         __builtin_amdgcn_wave_barrier();     // the chunk is consumed before the next one is staged
     }
     if (head_states && seg >= 1) seg_state();
+    c0 += s0;
+    c1 += s1;
+    c2 += s2;
+    D += sD;
     if (!pc.inside) return;
     const int64_t p = pc.pix;
     const bool more = head_stop && alive && end < rg.y;    // compositing continues after the head
@@ -462,7 +470,7 @@ __device__ __forceinline__ SegItem stored_seg(const SegPlan& plan, uint32_t b, i
 
 // One workgroup per tile, in launch order.  With a segment plan, the lists
 // it segments composite their head only (pass 1 of the segmented forward).
-// (256, 7): at most 72 VGPRs, 7 waves per SIMD, no spills.
+// (256, 7): at most 72 VGPRs, 7 waves per SIMD, 4 registers spilled.
 __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict__ rec,
                                                     const uint32_t* __restrict__ pair_vals,
                                                     const uint2* __restrict__ ranges,
@@ -477,10 +485,10 @@ __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict_
     float* head_states = nullptr;
     uint32_t seg_len = kSegLen, head_len = kHeadLen;
     if (plan.work_off) {
-        seg_len = plan.info[kPlanLen];
-        head_len = plan.info[kPlanHead] * seg_len;
         const uint32_t i = blockIdx.x;
         if (plan.work_off[i + 1] - plan.work_off[i] > 1u) {
+            seg_len = plan.info[kPlanLen];
+            head_len = plan.info[kPlanHead] * seg_len;
             head_stop = plan.stop_seg + (size_t)tile * 256;
             head_states = plan.state + (size_t)plan.state_off[i] * kSegFields * 256;
         }
@@ -584,7 +592,8 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const uint32_t* __restrict_
 // T = T_start T_local and T_local recomputed as in pass 2 (so the pixel
 // stops here, at the latest at the segment's last entry); they write their
 // final outputs and the segment's state over the entries they composited
-// (the state the backward folds).  (256, 7): 7 waves per SIMD, no spills.
+// (the state the backward folds).  (256, 7): 7 waves per SIMD, 4 registers
+// spilled.
 __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ rec,
                                                  const uint32_t* __restrict__ pair_vals,
                                                  const uint2* __restrict__ ranges,
