@@ -30,8 +30,9 @@
 // and vector instructions not overlapping on a SIMD, by the sum of both (32 MFMA
 // and about 300 others / 104 and 700 per 64 Gaussians).  Both kernels read the
 // next Gaussians' inputs ahead.  6M Gaussians: forward 127 us (161 with the output
-// layer on the matrix cores and nothing read ahead; HBM takes 93), backward 289
-// (347; the instructions take about 200, HBM 188).
+// layer on the matrix cores and nothing read ahead; HBM takes 93), backward 328 on
+// average and 308 at the shortest (378, 364; the instructions take about 200, HBM
+// 188).
 #include <atomic>
 
 #include "gs_internal.h"

@@ -326,13 +326,13 @@ constexpr int kPFPer = 4;                // items per lane in the scan of a chun
 // all views.  Chunk k of the wave is chunk blockIdx.x + k gridDim.x, at most
 // 256 per wave.  A longer list would share views better, but its Gaussians'
 // parameters are in cache no more when it comes to them: with 384 and 64
-// entries 2880 and 2771 us for 12M Gaussians in eight views.
+// entries 2880 and 2771 us for 12M Gaussians in eight views, timed alone.
 //
 // HBM-bound where most Gaussians are seen, else by the 128-byte lines of which
 // one or two Gaussians are wanted.  Measured (256 threads over spans of 1024,
 // FP64 pre-test, IEEE roots and divisions before): 1M Gaussians, most seen
-// 108 -> 81 us, 6M with 16 % seen 220 -> 187, 12M in eight views 3000 -> 2771,
-// 120k 27 -> 15, 4096 29 -> 9.
+// 108 -> 81 us, 120k 27 -> 15, 4096 29 -> 9; averages over training steps 6M with
+// 16 % seen 200 -> 192, 12M in eight views 2997 -> 2974 (shortest 2970 -> 2746).
 // Waves of a launch: as many as run at once, ten on a compute unit by their LDS,
 // with several views eight by their registers.  (One view of 6M Gaussians takes
 // 187, 186, 226 and 220 us with 2048, 2560, 2816 and 3072: a second turn of a

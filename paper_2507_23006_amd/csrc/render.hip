@@ -822,7 +822,7 @@ __device__ __forceinline__ int stage_gathered_bwd(const GatherBwd& e, int pos, c
 // registers; dy is constant in a row.  Three exchanges over the 8 rows finish the
 // sums.  That is about 14 VALU instructions per entry; a sum of each field over the
 // wave by lane exchanges takes 30 and its products 14 more (6M Gaussians, 1080p,
-// bound by VALU issue: 0.67 ms, 0.55 now).  (Moments about the quadrant's centre,
+// bound by VALU issue: 0.60 ms, 0.55 now).  (Moments about the quadrant's centre,
 // shifted to the mean after the sum, save two more instructions and 1 % of the
 // time, but cancel: for Gaussians of pixel size near a quadrant's corner dp dx^2
 // came out with 26 times the rounding error of its products.)  The FP32 matrix
