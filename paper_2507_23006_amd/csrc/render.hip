@@ -294,6 +294,9 @@ __device__ __forceinline__ int stage_gathered(const Gather& e, int pos, const Pi
 // segmented forward: stop_seg value of a pixel still compositing after the head
 constexpr int32_t kSegAlive = 0x7fffffff;
 
+// positions whose terms the forward adds up at a time
+constexpr int kSumPart = 512;
+
 // One wave composites quadrant `quad` of `tile` (staging in its LDS slice
 // `st`) and writes its pixels: the whole list, front to back.  With
 // head_stop (the tile's stop_seg row; a list the plan segments) only the
@@ -303,12 +306,14 @@ constexpr int32_t kSegAlive = 0x7fffffff;
 // kSegAlive.  The head also writes the backward's states of its segments from
 // 1 on (seg_len positions; head_states: the tile's first stored state): T_seg =
 // T_end / T_start and C_seg = C / T_start, C the segment's own part of the sum --
-// its composite with T restarted at 1.  So the sums restart at each segment (of
-// kSegLen positions in a walk of the whole list) and the parts are added up: the
-// difference of a running sum at the segment's ends would carry rounding at the
-// size of the whole sum, which is large beside a deep segment's part (4096
-// Gaussians at 160x120, several segments of 128 to a head: opacity and mean
-// gradients twice as far from float64, and the image 1.3 times).
+// its composite with T restarted at 1.  So the sums restart at each segment and
+// the parts are added up: the difference of a running sum at the segment's ends
+// would carry rounding at the size of the whole sum, which is large beside a deep
+// segment's part (4096 Gaussians at 160x120, several segments of 128 to a head:
+// opacity and mean gradients twice as far from float64, and the image 1.3 times).
+// Every walk adds up parts of at most kSumPart positions, whose length bounds the
+// rounding of a sum: long lists in segments of 2048 came out 1.4 times as far from
+// float64 as in segments of 512.
 __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ rec,
                                                     const uint32_t* __restrict__ pair_vals,
                                                     const uint2* __restrict__ ranges, const ViewTable& vt,
@@ -326,31 +331,42 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
     float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, D = 0.0f;
     int last = 0;
     bool alive = pc.inside;
-    // T at the start of the current segment, and the earlier ones' (C, D)
-    float sT = 1.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, sD = 0.0f;
+    // T at the start of the current segment, its (C, D) before the current part, and the earlier ones'
+    float sT = 1.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, sD = 0.0f, t0 = 0.0f, t1 = 0.0f, t2 = 0.0f, tD = 0.0f;
+    const uint32_t part = min(seg_len, (uint32_t)kSumPart);
     int seg = 0;
     const int px = pc.ly * kTile + pc.lx;
     auto seg_state = [&]() {      // state of segment `seg` >= 1 from its start to now
         float* o = head_states + (size_t)(seg - 1) * kSegFields * 256;
         const float inv = 1.0f / sT;
         o[0 * 256 + px] = T * inv;
-        o[1 * 256 + px] = c0 * inv;
-        o[2 * 256 + px] = c1 * inv;
-        o[3 * 256 + px] = c2 * inv;
-        o[4 * 256 + px] = D * inv;
+        o[1 * 256 + px] = s0 * inv;
+        o[2 * 256 + px] = s1 * inv;
+        o[3 * 256 + px] = s2 * inv;
+        o[4 * 256 + px] = sD * inv;
+    };
+    auto end_part = [&]() {
+        s0 += c0;
+        s1 += c1;
+        s2 += c2;
+        sD += D;
+        c0 = c1 = c2 = D = 0.0f;
     };
     Gather cur = load_entry(rec, load_slot(pair_vals, rg.x + lane, end));
     uint32_t s_next = load_slot(pair_vals, rg.x + kChunk + lane, end);
     for (uint32_t j0 = rg.x; j0 < end; j0 += kChunk) {
-        if (j0 != rg.x && ((j0 - rg.x) & (seg_len - 1u)) == 0) {
-            if (head_states && seg >= 1) seg_state();
-            ++seg;
-            sT = T;
-            s0 += c0;
-            s1 += c1;
-            s2 += c2;
-            sD += D;
-            c0 = c1 = c2 = D = 0.0f;
+        if (j0 != rg.x && ((j0 - rg.x) & (part - 1u)) == 0) {
+            end_part();
+            if (((j0 - rg.x) & (seg_len - 1u)) == 0) {
+                if (head_states && seg >= 1) seg_state();
+                ++seg;
+                sT = T;
+                t0 += s0;
+                t1 += s1;
+                t2 += s2;
+                tD += sD;
+                s0 = s1 = s2 = sD = 0.0f;
+            }
         }
         if (__ballot(alive) == 0) break;     // every pixel of the quadrant has stopped
         const int n = stage_gathered(cur, (int)(j0 - rg.x) + lane + 1, pc, lane, st);
@@ -384,11 +400,12 @@ __device__ __forceinline__ void render_fwd_quadrant(const float4* __restrict__ r
         }
         __builtin_amdgcn_wave_barrier();     // the chunk is consumed before the next one is staged
     }
+    end_part();
     if (head_states && seg >= 1) seg_state();
-    c0 += s0;
-    c1 += s1;
-    c2 += s2;
-    D += sD;
+    c0 = t0 + s0;
+    c1 = t1 + s1;
+    c2 = t2 + s2;
+    D = tD + sD;
     if (!pc.inside) return;
     const int64_t p = pc.pix;
     const bool more = head_stop && alive && end < rg.y;    // compositing continues after the head
@@ -420,11 +437,19 @@ __device__ __forceinline__ void render_fwd_segment(const float4* __restrict__ re
                                                    WaveStage& st, float* __restrict__ state_row) {
     const uint32_t lo = rg.x + (uint32_t)seg * seg_len, hi = min(lo + seg_len, rg.y);
     float Tl = 1.0f, l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, Dl = 0.0f;
+    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, sD = 0.0f;      // earlier parts
     int last = 0;
     Gather cur = load_entry(rec, load_slot(pair_vals, lo + lane, hi));
     uint32_t s_next = load_slot(pair_vals, lo + kChunk + lane, hi);
     for (uint32_t j0 = lo; j0 < hi; j0 += kChunk) {
         if (__ballot(on) == 0) break;
+        if (j0 != lo && ((j0 - lo) & (kSumPart - 1u)) == 0) {
+            s0 += l0;
+            s1 += l1;
+            s2 += l2;
+            sD += Dl;
+            l0 = l1 = l2 = Dl = 0.0f;
+        }
         const int n = stage_gathered(cur, (int)(j0 - rg.x) + lane + 1, pc, lane, st);
         cur = load_entry(rec, s_next);
         s_next = load_slot(pair_vals, j0 + 2 * kChunk + lane, hi);
@@ -448,10 +473,10 @@ __device__ __forceinline__ void render_fwd_segment(const float4* __restrict__ re
     }
     const int px = pc.ly * kTile + pc.lx;
     state_row[0 * 256 + px] = Tl;
-    state_row[1 * 256 + px] = l0;
-    state_row[2 * 256 + px] = l1;
-    state_row[3 * 256 + px] = l2;
-    state_row[4 * 256 + px] = Dl;
+    state_row[1 * 256 + px] = s0 + l0;
+    state_row[2 * 256 + px] = s1 + l1;
+    state_row[3 * 256 + px] = s2 + l2;
+    state_row[4 * 256 + px] = sD + Dl;
     reinterpret_cast<int32_t*>(state_row)[5 * 256 + px] = last;
 }
 
@@ -470,7 +495,8 @@ __device__ __forceinline__ SegItem stored_seg(const SegPlan& plan, uint32_t b, i
 
 // One workgroup per tile, in launch order.  With a segment plan, the lists
 // it segments composite their head only (pass 1 of the segmented forward).
-// (256, 7): at most 72 VGPRs, 7 waves per SIMD, 4 registers spilled.
+// (256, 7): at most 72 VGPRs, 7 waves per SIMD; 10 registers spilled, most of them
+// the sums that only the ends of parts and segments touch.
 __global__ __launch_bounds__(256, 7) void k_render_fwd(const float4* __restrict__ rec,
                                                     const uint32_t* __restrict__ pair_vals,
                                                     const uint2* __restrict__ ranges,
@@ -592,8 +618,7 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const uint32_t* __restrict_
 // T = T_start T_local and T_local recomputed as in pass 2 (so the pixel
 // stops here, at the latest at the segment's last entry); they write their
 // final outputs and the segment's state over the entries they composited
-// (the state the backward folds).  (256, 7): 7 waves per SIMD, 4 registers
-// spilled.
+// (the state the backward folds).  (256, 7): 7 waves per SIMD, no spills.
 __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ rec,
                                                  const uint32_t* __restrict__ pair_vals,
                                                  const uint2* __restrict__ ranges,
@@ -627,10 +652,18 @@ __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ r
     }
     const uint32_t seg_len = plan.info[kPlanLen], lo = rg.x + (uint32_t)it.seg * seg_len, hi = min(lo + seg_len, rg.y);
     float Tl = 1.0f, l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, Dl = 0.0f;
+    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, sD = 0.0f;      // earlier parts
     Gather cur = load_entry(rec, load_slot(pair_vals, lo + lane, hi));
     uint32_t s_next = load_slot(pair_vals, lo + kChunk + lane, hi);
     for (uint32_t j0 = lo; j0 < hi; j0 += kChunk) {
         if (__ballot(alive) == 0) break;
+        if (j0 != lo && ((j0 - lo) & (kSumPart - 1u)) == 0) {
+            s0 += l0;
+            s1 += l1;
+            s2 += l2;
+            sD += Dl;
+            l0 = l1 = l2 = Dl = 0.0f;
+        }
         const int n = stage_gathered(cur, (int)(j0 - rg.x) + lane + 1, pc, lane, st);
         cur = load_entry(rec, s_next);
         s_next = load_slot(pair_vals, j0 + 2 * kChunk + lane, hi);
@@ -656,6 +689,10 @@ __global__ __launch_bounds__(256, 7) void k_fwd_fix(const float4* __restrict__ r
         __builtin_amdgcn_wave_barrier();
     }
     if (!mine) return;
+    l0 += s0;
+    l1 += s1;
+    l2 += s2;
+    Dl += sD;
     const int64_t p = pc.pix;
     const float T = Ts * Tl;
     rgb[3 * p + 0] = fmaf(T, opt.bg[0], fmaf(Ts, l0, C0));
@@ -834,9 +871,15 @@ __device__ __forceinline__ int stage_gathered_bwd(const GatherBwd& e, int pos, c
 //
 // The sums overwrite staged records the walk has passed; after the chunk the
 // wave adds them to the per-slot rows, one float atomic per nonzero field.
+//
+// T is divided back by 1 - alpha an entry at a time, with the reciprocal's estimate,
+// whose error (up to an ulp, alike for alike alphas) adds up over the walk.  In
+// segments longer than kSegLen (kLong) a Newton step takes it to half an ulp either
+// way: two instructions an entry, with which walks of 2048 are nearer float64 than
+// walks of 512 with the estimate (without, up to 4 times as far).
 // (64, 5): 96 VGPRs without spills, five waves per SIMD; 19 workgroups share a
 // compute unit's LDS.
-template <bool kAbs>
+template <bool kAbs, bool kLong>
 __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__ rec,
                                                    const uint32_t* __restrict__ pair_vals,
                                                    const uint2* __restrict__ ranges,
@@ -1045,7 +1088,9 @@ __global__ __launch_bounds__(64, 5) void k_render_bwd(const float4* __restrict__
         p.any = __ballot(con) != 0;
         p.al = con ? e.alpha : 0.0f;
         p.grad = con && e.raw < kAlphaMax;                           // no gradient through the clamp
-        p.r = __builtin_amdgcn_rcpf(1.0f - p.al);
+        const float om = 1.0f - p.al;
+        p.r = __builtin_amdgcn_rcpf(om);
+        if (kLong) p.r = fmaf(p.r, fmaf(-om, p.r, 1.0f), p.r);
         p.kr = K * p.r;
         p.gc = fmaf(gC0, c.x, fmaf(gC1, c.y, fmaf(gC2, c.z, gD * b.z)));   // g . (colour, depth)
         return p;
@@ -1393,12 +1438,11 @@ hipError_t launch_render_bwd(const Projected& proj, const uint32_t* pair_vals, c
     // with a plan, blocks beyond the planned work items exit at once
     const unsigned blocks = wave_grid((unsigned)vt.total_tiles + (plan.work_off ? capacity : 0u));
     const hipEvent_t timed_ = timer_begin(GS_KERNEL_RENDER_BWD, s);
-    if (abs_sums)
-        hipLaunchKernelGGL(k_render_bwd<true>, dim3(blocks), dim3(64), 0, s, proj.rec, pair_vals, ranges,
-                           proj.tile_order, vt, opt, T_final, last, d_rgb, d_depth, d_alpha, grad2d, plan);
-    else
-        hipLaunchKernelGGL(k_render_bwd<false>, dim3(blocks), dim3(64), 0, s, proj.rec, pair_vals, ranges,
-                           proj.tile_order, vt, opt, T_final, last, d_rgb, d_depth, d_alpha, grad2d, plan);
+    const bool longer = plan.work_off && plan.seg_len > (uint32_t)kSegLen;
+    const auto kernel = abs_sums ? (longer ? k_render_bwd<true, true> : k_render_bwd<true, false>)
+                                 : (longer ? k_render_bwd<false, true> : k_render_bwd<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64), 0, s, proj.rec, pair_vals, ranges, proj.tile_order, vt, opt, T_final,
+                       last, d_rgb, d_depth, d_alpha, grad2d, plan);
     timer_end(timed_, s);
     return hipGetLastError();
 }

@@ -19,15 +19,16 @@ BG = (0.1, 0.4, 0.7)
 LN2 = float(np.log(2.0))
 
 
-def float64_sums(rec, W, H, last, g):
-    """Images and per-Gaussian gradient fields of records in list order, the first last[pixel] composited."""
+def float64_sums(rec, W, H, last, g, pixels=None):
+    """Images (at all pixels or some) and per-Gaussian gradient fields of records in list order, the first
+    last[pixel] composited."""
     r = rec.double()
     mx, my, z, o, col = r[:, 0] + r[:, 7], r[:, 1] + r[:, 11], r[:, 6], r[:, 5], r[:, 8:11]
     bg = torch.tensor(BG, dtype=torch.float64, device="cuda")
     pos = torch.arange(1, len(rec) + 1, device="cuda")
     img = {k: [] for k in ("rgb", "depth", "T")}
     grad = torch.zeros(len(rec), 10, dtype=torch.float64, device="cuda")
-    for pix in torch.arange(W * H, device="cuda").split(8192):
+    for pix in (torch.arange(W * H, device="cuda") if pixels is None else pixels).split(8192):
         dx, dy = (pix % W).double()[:, None] + 0.5 - mx, (pix // W).double()[:, None] + 0.5 - my
         a = o * torch.exp2(r[:, 2] * dx * dx + r[:, 3] * dx * dy + r[:, 4] * dy * dy)
         assert float(a.min()) > 1.001 / 255.0
