@@ -212,9 +212,10 @@ int gs_render_count(const gs_projected *proj, const uint32_t *pair_vals, const u
  * starting from the transmittance and colour behind it (folded from
  * per-segment states a pre-pass computes), so the longest lists no longer
  * serialise the launch.  A state takes 6 KB; the area holds one for each
- * segment length of pairs, of 128 positions at most 32768, so its size does
- * not grow with n_tiles throughout: an area for launches of several sizes
- * takes the largest of theirs.  A smaller or absent segment area walks every
+ * segment length of pairs, of 128 positions at most 32768 or, if that is
+ * more, as many as segments of 512 need, so its size does not grow with
+ * n_tiles throughout: an area for launches of several sizes takes the largest
+ * of theirs.  A smaller or absent segment area walks every
  * list whole; results agree to float rounding either way, and the last bits
  * of an image depend on the tiles of the launch that renders it. */
 size_t gs_render_bwd_workspace_size(int64_t n_slots);
