@@ -859,7 +859,7 @@ __device__ __forceinline__ int stage_gathered_bwd(const GatherBwd& e, int pos, c
 // registers; dy is constant in a row.  Three exchanges over the 8 rows finish the
 // sums.  That is about 14 VALU instructions per entry; a sum of each field over the
 // wave by lane exchanges takes 30 and its products 14 more (6M Gaussians, 1080p,
-// bound by VALU issue: 0.60 ms, 0.55 now).  (Moments about the quadrant's centre,
+// bound by VALU issue: 0.60 ms, 0.56 now).  (Moments about the quadrant's centre,
 // shifted to the mean after the sum, save two more instructions and 1 % of the
 // time, but cancel: for Gaussians of pixel size near a quadrant's corner dp dx^2
 // came out with 26 times the rounding error of its products.)  The FP32 matrix
@@ -876,7 +876,8 @@ __device__ __forceinline__ int stage_gathered_bwd(const GatherBwd& e, int pos, c
 // whose error (up to an ulp, alike for alike alphas) adds up over the walk.  In
 // segments longer than kSegLen (kLong) a Newton step takes it to half an ulp either
 // way: two instructions an entry, with which walks of 2048 are nearer float64 than
-// walks of 512 with the estimate (without, up to 4 times as far).
+// walks of 512 with the estimate (without, up to 4 times as far; 12M Gaussians in
+// eight views 5.86 -> 5.95 ms).
 // (64, 5): 96 VGPRs without spills, five waves per SIMD; 19 workgroups share a
 // compute unit's LDS.
 template <bool kAbs, bool kLong>
